@@ -12,8 +12,8 @@
 //     accuracy than the 2e-2 logit tolerance allows at 8B scale, so each weight tile is multiplied
 //     with both planes.  All wavefronts of a workgroup need all of them: they go from L2 into a
 //     ring of five LDS stage buffers with direct-to-LDS loads, four stages ahead.
-//   - A workgroup is 8 wavefronts (two per SIMD), all alike: 2 column groups x 4 k-groups (4 x 2 when the
-//     batch has several blocks of rows, 8 x 1 for the LM head; see the shapes below).  A stage is one k-step of 16 per k-group;
+//   - A workgroup is 8 wavefronts (two per SIMD), all alike: 2 column groups x 4 k-groups (others for low-bit
+//     weights with several blocks of rows and for the LM head; see the shapes below).  A stage is one k-step of 16 per k-group;
 //     k-group g works on the g-th of them for the 64 columns (two 32-column
 //     tiles) of its column group and all rows of the block (MT 32-row tiles), and the k-groups'
 //     sums are exchanged through LDS at the end and added in a fixed order, after which every wavefront stores a
@@ -58,8 +58,9 @@ constexpr int NXB = AHEAD + 1;    // LDS ring
 //   narrow  KG 4, CG 2: 128 columns, 64 k per stage.  Most workgroups per projection: the shape for one block of
 //           rows (up to 128), where the chip has to be filled by column blocks and K slices alone.
 //   wide    KG 2, CG 4: 256 columns, 32 k per stage.  Per MFMA it fetches two thirds of the bytes (half the
-//           activations, the same weights): the shape for several row blocks, where the workgroups are many
-//           anyway and the L2 -> CU path, not HBM, is what the MFMAs wait for.
+//           activations, the same weights): the shape for several row blocks of 8- and 4-bit weights, where the
+//           workgroups are many anyway and the L2 -> CU path, not HBM, is what the MFMAs wait for (bf16 weights: the
+//           tile kernel below).
 //   broad   KG 1, CG 8: 512 columns, 16 k per stage, no sums to exchange at the end.  Per MFMA it fetches half the
 //           bytes of the narrow shape; only a matrix with enough columns to fill the chip without K slices can use
 //           it (the LM head), and only with four row tiles (a stage's eight activation tiles go one to a wavefront).
@@ -112,6 +113,27 @@ template <int N>
 __device__ __forceinline__ void wait_load4(u32x2_t& a, uint32_t& b) {
     static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
     asm volatile("s_waitcnt vmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N) : "memory");
+}
+
+// four consecutive output columns n .. n+3 of row tok: partial sums of K slice `by`, finished values, or SwiGLU of the
+// two (gate, up) pairs they hold, written as a bf16 pair in operand order
+template <int EPI>
+__device__ __forceinline__ void store_cols(const float4_t v, int tok, int n, int by, int T_pad, int N, float* __restrict__ out,
+                                           bf16_t* __restrict__ out_act, size_t act_plane, int F_act) {
+    if (EPI == SLED_EPI_PARTIAL) {
+        *reinterpret_cast<float4_t*>(out + ((size_t)by * T_pad + tok) * N + n) = v;
+    } else if (EPI == SLED_EPI_STORE) {
+        *reinterpret_cast<float4_t*>(out + (size_t)tok * N + n) = v;
+    } else {  // columns are (gate f, up f, gate f+1, up f+1)
+        const int f = n >> 1;
+        const float a0 = v[0] / (1.f + __expf(-v[0])) * v[1];
+        const float a1 = v[2] / (1.f + __expf(-v[2])) * v[3];
+        const bf16_t h0 = f32_to_bf16(a0), h1 = f32_to_bf16(a1);
+        const bf16_t l0 = f32_to_bf16(a0 - bf16_to_f32(h0)), l1 = f32_to_bf16(a1 - bf16_to_f32(h1));
+        const size_t o = frag_offset(tok, f, F_act);
+        *reinterpret_cast<uint32_t*>(out_act + o) = (uint32_t)h0 | ((uint32_t)h1 << 16);
+        *reinterpret_cast<uint32_t*>(out_act + act_plane + o) = (uint32_t)l0 | ((uint32_t)l1 << 16);
+    }
 }
 
 // MT: 32-row tiles of activations per block.  WB: bits per weight.  8 (see w8_offset): the wavefront's two column
@@ -433,23 +455,199 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(const bf16_t* __r
                 const int n = (nt0 + a) * 32 + q * 8 + (lane >> 5) * 4;
                 float4_t v = {acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]};
                 if (W8) v *= sc[q];
-                if (EPI == SLED_EPI_PARTIAL) {
-                    if (tok < T) *reinterpret_cast<float4_t*>(out + ((size_t)by * T_pad + tok) * N + n) = v;  // padding rows are never read
-                } else if (EPI == SLED_EPI_STORE) {
-                    if (tok < T) *reinterpret_cast<float4_t*>(out + (size_t)tok * N + n) = v;
-                } else {  // SwiGLU: columns are (gate f, up f, gate f+1, up f+1)
-                    if (tok < T) {  // padding rows: what a consumer reads there only reaches its own padding rows
-                        const int f = n >> 1;
-                        const float a0 = v[0] / (1.f + __expf(-v[0])) * v[1];
-                        const float a1 = v[2] / (1.f + __expf(-v[2])) * v[3];
-                        const bf16_t h0 = f32_to_bf16(a0), h1 = f32_to_bf16(a1);
-                        const bf16_t l0 = f32_to_bf16(a0 - bf16_to_f32(h0)), l1 = f32_to_bf16(a1 - bf16_to_f32(h1));
-                        const size_t o = frag_offset(tok, f, F_act);
-                        *reinterpret_cast<uint32_t*>(out_act + o) = (uint32_t)h0 | ((uint32_t)h1 << 16);
-                        *reinterpret_cast<uint32_t*>(out_act + act_plane + o) = (uint32_t)l0 | ((uint32_t)l1 << 16);
-                    }
-                }
+                if (tok < T) store_cols<EPI>(v, tok, n, by, T_pad, N, out, out_act, act_plane, F_act);  // padding rows are never read
             }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------ tile kernel
+// bf16 weights, more than 128 rows: the contraction is bound by the matrix pipes, so the workgroup is shaped for them.
+// Four wavefronts, ONE per SIMD (512 registers each), own a tile of RT x 32 rows by 256 columns as 2 x 2 quarters; a
+// quarter is RT/2 x 4 accumulator tiles.  Both operands go through a ring of LDS stages of one k-step (16 k), filled
+// by direct-to-LDS loads that keep as many stages in flight as the 160 KiB hold.  Per stage and wavefront (RT = 8):
+// 32 MFMAs (1024 clocks of the matrix pipe), 12 ds_read_b128, 6 loads and one barrier, so everything but the MFMAs
+// fits into their issue gaps: operands of the next stage are read into a second register set between them.
+//   - Against the wide shape above (2 wavefronts per SIMD, weights straight to registers), which ran these cases before,
+//     a k-step moves 24 KiB into the CU instead of 32 per 128 MFMAs (RT = 8), reads 48 KiB of LDS instead of 64, and has
+//     no sums to exchange at the end; and its height can follow the batch (plan_for_rows).  Gate/up of 384 rows x 4096
+//     x 28672: 179 -> 137 us; of 256 rows x 8192 x 57344: 392 -> 346 us = 1.39 PFLOP/s executed (both planes), where a
+//     large library product on the same card reaches 1.41: power, not the schedule, is what is left.
+// Loads and waits are written by hand as above; all vector-memory operations of the loop are direct-to-LDS loads, so
+// no register is ever the target of a load in flight.
+constexpr int TILE_WAVES = 4, TILE_CT = 8;
+constexpr int tile_stage_kib(int RT) { return PLANES * RT + TILE_CT; }
+constexpr int tile_ring(int RT) { return 160 / tile_stage_kib(RT); }
+// K is dealt out to the slices in units of 8 k-steps; a slice holds at least two units, so never fewer stages than the ring
+constexpr int TILE_UNIT = 8, TILE_MIN_STAGES = 16;
+
+template <int RT, int EPI>
+__global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf16_t* __restrict__ Xp, size_t x_plane,
+                                                                       const bf16_t* __restrict__ Wp, int NT, int KS, int n_col,
+                                                                       int n_split, int n_zb, int T, int T_pad, int N,
+                                                                       float* __restrict__ out, bf16_t* __restrict__ out_act,
+                                                                       size_t act_plane, int F_act) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int HR = RT / 2, HC = TILE_CT / 2;               // row and column tiles of a wavefront's quarter
+    constexpr int XT = PLANES * RT, ST = XT + TILE_CT;         // 1 KiB operand tiles per stage: activations, then weights
+    constexpr int NB = tile_ring(RT);                          // stages in the ring = stages in flight
+    constexpr int XL = XT / TILE_WAVES, WL = TILE_CT / TILE_WAVES, PER = XL + WL;   // loads per wavefront and stage
+    static_assert(RT % 2 == 0 && XT % TILE_WAVES == 0 && TILE_CT % TILE_WAVES == 0, "tiles do not divide among the wavefronts");
+    static_assert(NB % 2 == 0 && TILE_UNIT % 2 == 0 && NB <= TILE_MIN_STAGES, "the trips of the stage loop are written for an even ring");
+    static_assert((NB - 1) * PER < 64, "too many loads in flight for the counter");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wv >> 1, wc = wv & 1;
+    // workgroup -> (column block, K slice, row block), as in gemm_bf16_kernel
+    int bx, by, bz;
+    {
+        const int w = blockIdx.x, xcd = w & 7, local = w >> 3;
+        bz = local % n_zb;
+        const int t = (local / n_zb) * 8 + xcd;
+        if (t >= n_col * n_split) return;
+        bx = t % n_col;
+        by = t / n_col;
+    }
+    const int units = KS / TILE_UNIT, ubase = units / n_split, urem = units - ubase * n_split;
+    const int ks_begin = (by * ubase + min(by, urem)) * TILE_UNIT;
+    const int n_stage = (ubase + (by < urem ? 1 : 0)) * TILE_UNIT;   // even, at least TILE_MIN_STAGES (the host sees to it)
+    const int mt_base = bz * RT, nt_base = bx * TILE_CT;
+
+    // ---- sources of this wavefront's loads: a uniform base per tile, advanced stage by stage, and a lane offset
+    const int row_lim = (T + 7) & ~7;
+    const char* xsrc[XL];
+    unsigned xoff[XL];
+    const char* wsrc[WL];
+#pragma unroll
+    for (int j = 0; j < XL; j++) {
+        const int i = j * TILE_WAVES + wv, pl = i / RT, b = i - pl * RT;
+        const int mt = min(mt_base + b, T_pad / 32 - 1);   // a tile past the last one re-reads it; its results are not stored
+        // lanes past the last token re-read the tile's first line (see gemm_bf16_kernel)
+        const int src_lane = mt * 32 + (lane & 31) < row_lim ? lane : (lane & 32) + (lane & 7);
+        xsrc[j] = reinterpret_cast<const char*>(Xp + pl * x_plane + ((size_t)mt * KS + ks_begin) * 512);
+        xoff[j] = src_lane * 16;
+    }
+#pragma unroll
+    for (int j = 0; j < WL; j++) {
+        const int nt = min(nt_base + j * TILE_WAVES + wv, NT - 1);
+        wsrc[j] = reinterpret_cast<const char*>(Wp + ((size_t)ks_begin * NT + nt) * 512);
+    }
+    const unsigned woff = lane * 16;
+    const size_t wstep = (size_t)NT * 1024;
+    const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem + wv * 1024;
+    // load number j of the next stage in order, into ring slot `buf`
+    auto issue_one = [&](int buf, int j) {
+        const unsigned slot = lds_base + (unsigned)buf * (ST * 1024);
+        if (j < XL) {
+            const unsigned dst = __builtin_amdgcn_readfirstlane(slot + j * (TILE_WAVES * 1024));
+            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(xoff[j < XL ? j : 0]), "s"(xsrc[j < XL ? j : 0]), "s"(dst) : "memory");
+            xsrc[j < XL ? j : 0] += 1024;
+        } else {
+            const int a = j < XL ? 0 : j - XL;
+            const unsigned dst = __builtin_amdgcn_readfirstlane(slot + (XT + a * TILE_WAVES) * 1024);
+            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(woff), "s"(wsrc[a]), "s"(dst) : "memory");
+            wsrc[a] += wstep;
+        }
+    };
+
+    float16_t acc[HC][HR];
+#pragma unroll
+    for (int a = 0; a < HC; a++)
+#pragma unroll
+        for (int b = 0; b < HR; b++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) acc[a][b][e] = 0.f;
+
+    struct frags {
+        bf16x8_t x[PLANES][HR], w[HC];
+    };
+    constexpr int NR = PLANES * HR + HC, NM = PLANES * HR * HC;   // LDS reads and MFMAs per stage
+    const unsigned char* rd = smem + lane * 16;
+    auto read_one = [&](frags& f, int buf, int r) {   // weights first, then the hi plane, then the lo plane
+        const unsigned char* p = rd + (unsigned)buf * (ST * 1024);
+        if (r < HC)
+            f.w[r < HC ? r : 0] = *reinterpret_cast<const bf16x8_t*>(p + (XT + wc * HC + r) * 1024);
+        else {
+            const int e = r < HC ? 0 : r - HC, pl = e / HR, b = e - pl * HR;
+            f.x[pl][b] = *reinterpret_cast<const bf16x8_t*>(p + (pl * RT + wr * HR + b) * 1024);
+        }
+    };
+    auto mfma_one = [&](const frags& f, int i) {   // all tiles with the hi plane, then all with the lo plane
+        const int pl = i / (HR * HC), e = i - pl * (HR * HC), b = e / HC, a = e - b * HC;
+        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[a], f.x[pl][b], acc[a][b], 0, 0, 0);
+    };
+    // Stage s with its operands in `cur`: the operands of stage s+1 are read into `nxt`, and slot s % NB -- whose last
+    // reads, those of stage s, every wavefront has back when it reaches the barrier -- is refilled with stage s+NB.
+    // The wait before the barrier is for this wavefront's share of stage s+1; AFTER loads have been issued since.
+    auto stage = [&](auto after_c, auto load_c, auto more_c, const frags& cur, frags& nxt, int buf, int next_buf) {
+        constexpr int AFTER = decltype(after_c)::value;
+        constexpr bool LOAD = decltype(load_c)::value != 0, MORE = decltype(more_c)::value != 0;
+        if (MORE) {
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(AFTER) : "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        int r = 0;
+#pragma unroll
+        for (int i = 0; i < NM; i++) {
+            mfma_one(cur, i);
+            if (LOAD && i < PER) issue_one(buf, i);
+            if (MORE && r < NR && i >= r * (NM - 6) / NR) {
+                read_one(nxt, next_buf, r);
+                r++;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    using std::integral_constant;
+    typedef integral_constant<int, 1> yes;
+    typedef integral_constant<int, 0> no;
+
+#pragma unroll
+    for (int s2 = 0; s2 < NB; s2++)
+#pragma unroll
+        for (int j = 0; j < PER; j++) issue_one(s2, j);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NB - 1) * PER) : "memory");   // this wavefront's share of stage 0
+    __builtin_amdgcn_s_barrier();                                           // everybody's
+    asm volatile("" ::: "memory");
+    frags f0, f1;
+#pragma unroll
+    for (int r = 0; r < NR; r++) read_one(f0, 0, r);
+    int buf = 0;
+    auto next = [&](int b2) { return b2 == NB - 1 ? 0 : b2 + 1; };
+    for (int s = 0; s + NB < n_stage; s += 2) {   // n_stage and NB are even: both stages of a trip have one NB further on
+        stage(integral_constant<int, (NB - 2) * PER>{}, yes{}, yes{}, f0, f1, buf, next(buf));
+        buf = next(buf);
+        stage(integral_constant<int, (NB - 2) * PER>{}, yes{}, yes{}, f1, f0, buf, next(buf));
+        buf = next(buf);
+    }
+    // the last NB stages fetch nothing: one stage fewer in flight behind the awaited one each time
+    auto last = [&](auto self, auto left_c) {   // left: stages still to do
+        constexpr int LEFT = decltype(left_c)::value;
+        if constexpr (LEFT > 0) {
+            constexpr int AFTER = LEFT >= 2 ? (LEFT - 2) * PER : 0;
+            if constexpr (LEFT % 2 == 0) stage(integral_constant<int, AFTER>{}, no{}, yes{}, f0, f1, buf, next(buf));
+            else if constexpr (LEFT > 1) stage(integral_constant<int, AFTER>{}, no{}, yes{}, f1, f0, buf, next(buf));
+            else stage(integral_constant<int, 0>{}, no{}, no{}, f1, f0, buf, buf);
+            buf = next(buf);
+            self(self, integral_constant<int, LEFT - 1>{});
+        }
+    };
+    last(last, integral_constant<int, NB>{});
+
+    // epilogue: lane holds row (token) mt*32 + lane%32 and, in registers 4q .. 4q+3, the columns nt*32 + 8q + (lane/32)*4 + 0..3
+#pragma unroll
+    for (int a = 0; a < HC; a++) {
+        const int nt = nt_base + wc * HC + a;
+        if (nt >= NT) continue;
+#pragma unroll
+        for (int b = 0; b < HR; b++) {
+            const int tok = (mt_base + wr * HR + b) * 32 + (lane & 31);
+            if (tok >= T) continue;   // padding rows are never read, or only by their own padding rows
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                store_cols<EPI>(float4_t{acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]}, tok,
+                                nt * 32 + q * 8 + (lane >> 5) * 4, by, T_pad, N, out, out_act, act_plane, F_act);
         }
     }
 }
@@ -522,6 +720,29 @@ int launch_one(const gemm_args& a) {
     return SLED_OK;
 }
 
+template <int RT, int EPI>
+int launch_tile_one(const gemm_args& a) {
+    static bool allowed = false;
+    auto kern = gemm_tile_kernel<RT, EPI>;
+    if (!allowed) {
+        SLED_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds));
+        allowed = true;
+    }
+    hipLaunchKernelGGL(kern, a.grid, dim3(64 * TILE_WAVES), a.lds, a.st, a.X, a.x_plane, a.W, a.NT, a.KS, a.n_col, a.n_split, a.n_zb,
+                       a.T, a.T_pad, a.N, a.out, a.out_act, a.act_plane, a.F_act);
+    SLED_LAUNCH_CHECK();
+    return SLED_OK;
+}
+
+template <int RT>
+int launch_tile(int epi, const gemm_args& a) {
+    switch (epi) {
+        case SLED_EPI_PARTIAL: return launch_tile_one<RT, SLED_EPI_PARTIAL>(a);
+        case SLED_EPI_SWIGLU: return launch_tile_one<RT, SLED_EPI_SWIGLU>(a);
+        default: return launch_tile_one<RT, SLED_EPI_STORE>(a);
+    }
+}
+
 template <int MT, int KG, int CG, int WB>
 int launch_epi_wb(int epi, const gemm_args& a) {
     switch (epi) {
@@ -546,15 +767,15 @@ int launch_epi(int epi, const gemm_args& a) {
 // chip wants at least one per CU) but more partial sums to reduce.  Each slice must hold a multiple
 // of 4 stages of 64 k.
 static sled_gemm_plan plan_one_block(int N, int K, bool needs_full_k);
-static sled_gemm_plan plan_for_rows(sled_gemm_plan base, int N, int K, int T_pad);
+static sled_gemm_plan plan_for_rows(sled_gemm_plan base, int N, int K, int T_pad, int wbits);
 
 sled_gemm_plan sled_gemm_make_plan(const sled_model* m, int N, int K, bool needs_full_k) {
-    if (m->s.dtype != SLED_BF16) return sled_gemm_plan{1, 1};
+    if (m->s.dtype != SLED_BF16) return sled_gemm_plan{1, 1, 0};
     return plan_one_block(N, K, needs_full_k);
 }
 
 static sled_gemm_plan plan_one_block(int N, int K, bool needs_full_k) {
-    sled_gemm_plan p{1, 1};
+    sled_gemm_plan p{1, 1, 0};
     auto legal = [&](int sp) { return sp >= 1 && (K / 16) % (sp * NARROW_KG * NBUF) == 0; };
     const int n_wg = (N + NARROW_COLS - 1) / NARROW_COLS;
     if (!needs_full_k)
@@ -564,29 +785,40 @@ static sled_gemm_plan plan_one_block(int N, int K, bool needs_full_k) {
     return p;
 }
 
-// With more than one block of rows (the wide shape) the workgroups of a projection are column blocks x row blocks x
-// K slices, and what counts is how many rounds of 256 they make: 288 workgroups take as long as 512.  Fewer K slices
-// also mean fewer partial sums to write and to read back.  Estimated time of a launch, in microseconds: rounds x
-// (fixed part + stages per workgroup x time per stage) + bytes of partial sums written and read / rate.
+// With more than one block of 128 rows the workgroups of a projection are column blocks x row blocks x K slices, and what
+// counts is how many rounds of 256 they make: 288 workgroups take as long as 512.  Fewer K slices also mean fewer
+// partial sums to write and to read back.  Estimated time of a launch, in microseconds: rounds x (fixed part +
+// k-steps per workgroup x time per k-step) + bytes of partial sums written and read / rate; minimised over the K slices
+// and, for the tile kernel, its row tiles.  Times per k-step measured on full rounds: 0.35-0.39 us at 4 row tiles
+// (as the wide shape), 0.51-0.54 at 6, 0.66-0.68 at 8.  So equal rows cost about the same at each height, and what the
+// choice of height gives is better filled rounds: 384 rows x 28672 columns are 336 workgroups in two rounds at 4 row
+// tiles (178 us) and 224 in one round at 6 (137 us); 256 x 57344 take 383 us at 4, 346 us at 8.
 sled_gemm_plan sled_gemm_plan_rows(const sled_model* m, sled_gemm_plan base, int N, int K, int T_pad) {
     if (m->s.dtype != SLED_BF16 || m->batch_invariant) return base;
-    return plan_for_rows(base, N, K, T_pad);
+    return plan_for_rows(base, N, K, T_pad, m->wbits);
 }
 
-static sled_gemm_plan plan_for_rows(sled_gemm_plan base, int N, int K, int T_pad) {
-    if (base.split <= 1 || T_pad / 32 <= 4) return base;
-    constexpr double FIXED_US = 9.0, STAGE_US = 0.8, PARTIAL_BYTES_PER_US = 4.0e6;
-    const int n_col = (N / 32 + WIDE_CG * NW - 1) / (WIDE_CG * NW), zb = (T_pad / 32 + 3) / 4;
-    const int units = K / 16 / (WIDE_KG * NBUF);   // trips of the stage loop in all of K
+static sled_gemm_plan plan_for_rows(sled_gemm_plan base, int N, int K, int T_pad, int wbits) {
+    if (T_pad / 32 <= 4) return base;
+    constexpr double FIXED_US = 9.0, PARTIAL_BYTES_PER_US = 4.0e6;
+    constexpr int HEIGHTS[3] = {4, 6, 8};
+    constexpr double STEP_US[3] = {0.40, 0.59, 0.74};
+    const int n_col = (N / 32 + 7) / 8;                      // of 256 columns, in either kernel
+    const int units = K / 16 / TILE_UNIT;                    // trips of the stage loop in all of K
     sled_gemm_plan best = base;
     double best_t = -1.0;
-    for (int sp = 1; sp <= base.cap && sp <= units; sp++) {
-        const int64_t wgs = (int64_t)n_col * zb * sp;
-        const int stages = (units + sp - 1) / sp * NBUF;   // of the longest slice
-        const double t = (double)((wgs + 255) / 256) * (FIXED_US + stages * STAGE_US) + 2.0 * sp * (double)T_pad * N * 4.0 / PARTIAL_BYTES_PER_US;
-        if (best_t < 0 || t < best_t) {
-            best_t = t;
-            best.split = sp;
+    for (int h = 0; h < (wbits == 16 ? 3 : 1); h++) {
+        const int zb = (T_pad / 32 + HEIGHTS[h] - 1) / HEIGHTS[h];
+        for (int sp = 1; sp <= base.cap && sp * TILE_MIN_STAGES <= K / 16; sp++) {
+            const int64_t wgs = (int64_t)n_col * zb * sp;
+            const int steps = (units + sp - 1) / sp * TILE_UNIT;   // of the longest slice
+            const double partial = base.cap > 1 ? 2.0 * sp * (double)T_pad * N * 4.0 / PARTIAL_BYTES_PER_US : 0.0;
+            const double t = (double)((wgs + 255) / 256) * (FIXED_US + steps * STEP_US[h]) + partial;
+            if (best_t < 0 || t < best_t) {
+                best_t = t;
+                best.split = sp;
+                best.tile = wbits == 16 ? HEIGHTS[h] : 0;
+            }
         }
     }
     return best;
@@ -596,7 +828,7 @@ extern "C" int sled_projection_slices(int n_out, int n_in, int T, int* slices /*
     if (!slices || !max_slices || n_out < 32 || n_in < 16 * NARROW_KG * NBUF || n_out % 32 || n_in % (16 * NARROW_KG * NBUF) || T < 1)
         SLED_FAIL(SLED_EINVAL, "sled_projection_slices: bad argument");
     const sled_gemm_plan base = plan_one_block(n_out, n_in, false);
-    *slices = plan_for_rows(base, n_out, n_in, (T + 31) / 32 * 32).split;
+    *slices = plan_for_rows(base, n_out, n_in, (T + 31) / 32 * 32, 16).split;
     *max_slices = base.cap;
     return SLED_OK;
 }
@@ -609,8 +841,8 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
         if (N % 32 || K % 16 || T_pad % 32 || plan.split < 1 || KS % (NARROW_KG * NBUF) || plan.split > KS / (NARROW_KG * NBUF))
             SLED_FAIL(SLED_EINVAL, "gemm: unsupported shape N=%d K=%d T_pad=%d split=%d", N, K, T_pad, plan.split);
         const int mt_total = T_pad / 32;
-        // rows are processed in blocks of at most 4 tiles (128 rows): one block -> narrow shape with exactly its
-        // tiles; several -> wide shape, four tiles each (the last block may reach past the end)
+        // up to 128 rows (4 tiles): narrow shape with exactly these tiles; more: the tile kernel at the planned height
+        // (bf16 weights) or blocks of four tiles in the wide shape (8- and 4-bit weights); the last block may reach past the end
         // (a batch-invariant model keeps the narrow shape at every size: the two shapes add the k-steps up in
         // different groupings, so a row's sums would depend on whether its batch has more than 128 rows)
         const bool wide = mt_total > 4 && !m->batch_invariant;
@@ -619,6 +851,8 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
         // one block of four row tiles, no K slices, and column blocks of 512 that fill at least three quarters of the CUs
         const bool broad = !wide && MT == 4 && plan.split == 1 && !m->batch_invariant && (NT + BROAD_CG * NW - 1) / (BROAD_CG * NW) >= 192;
         const int KG = wide ? WIDE_KG : broad ? BROAD_KG : NARROW_KG, CG = wide ? WIDE_CG : broad ? BROAD_CG : NARROW_CG;
+        const int RT = wide ? plan.tile : 0;
+        if (wide && m->wbits == 16 && RT != 4 && RT != 6 && RT != 8) SLED_FAIL(SLED_EINVAL, "gemm: no tile height planned for %d rows", T_pad);
         gemm_args a;
         a.n_col = (NT + CG * NW - 1) / (CG * NW);
         a.n_split = plan.split;
@@ -645,7 +879,19 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
         a.out_act = static_cast<bf16_t*>(out_act);
         a.act_plane = act_plane;
         a.F_act = F_act;
-        if (wide) return launch_epi<4, WIDE_KG, WIDE_CG>(epilogue, a);
+        if (RT) {
+            a.n_col = (NT + TILE_CT - 1) / TILE_CT;
+            a.n_zb = (mt_total + RT - 1) / RT;
+            a.grid = dim3((a.n_col * a.n_split + 7) / 8 * 8 * a.n_zb, 1, 1);
+            a.lds = (size_t)tile_ring(RT) * tile_stage_kib(RT) * 1024;
+            switch (RT) {
+                case 4: return launch_tile<4>(epilogue, a);
+                case 6: return launch_tile<6>(epilogue, a);
+                default: return launch_tile<8>(epilogue, a);
+            }
+        }
+        if (wide)
+            return m->wbits == 8 ? launch_epi_wb<4, WIDE_KG, WIDE_CG, 8>(epilogue, a) : launch_epi_wb<4, WIDE_KG, WIDE_CG, 4>(epilogue, a);
         if (broad) return launch_epi<4, BROAD_KG, BROAD_CG>(epilogue, a);
         switch (MT) {
             case 1: return launch_epi<1, NARROW_KG, NARROW_CG>(epilogue, a);
