@@ -1,9 +1,11 @@
 // Vocab-parallel acceptance (greedy match or speculative sampling, Eq. 1 of Sec. 3.1).
 //
-// Two kernels per call:
-//   accept_row_stats   one pass over all logits: per row (split over a few workgroups when the
-//                      batch is small) the maximum, its lowest index, and sum exp((z - max)/tau).
-//                      Pure HBM scan: four float4 loads in flight per thread, wavefront reductions.
+// Two kinds of kernel per call:
+//   accept_row_stats   per row of logits (split over a few workgroups when the batch is small) the maximum, its
+//                      lowest index, and sum exp((z - max)/tau).  Pure HBM scan: four float4 loads in flight per
+//                      thread, wavefront reductions.  A large batch is scanned in up to three launches that take the
+//                      requests' rows from the front, with the accept test of the rows so far (accept_over) between
+//                      them: where one of them ended the prefix nothing reads what is behind it.
 //   accept_finish      one workgroup per request.  Its first wavefront applies the accept test (or the
 //                      argmax comparison) to all of the request's rows at once, one row per lane, and
 //                      takes the first failure.  In sampling mode the workgroup then draws the request's
@@ -14,13 +16,10 @@
 //                      mass per tile follows from the sums of p and one pass over the pairs.
 #include "sled_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace {
-
-struct KPack {
-    uint8_t k[1024];
-};
 
 struct RowStat {
     double s;   // sum of exp((z - m) / tau) over the segment
@@ -39,117 +38,25 @@ __device__ inline void stat_merge(float& m, int& idx, double& s, float m2, int i
     }
 }
 
-template <bool SAMPLE>
-__global__ __launch_bounds__(256) void accept_row_stats(const float* __restrict__ logits, int V, int n_split, int seg,
-                                                        float inv_tau, RowStat* __restrict__ stats) {
-    const int row = blockIdx.x, split = blockIdx.y;
-    const int v0 = split * seg;
-    const int v1 = min(V, v0 + seg);
-    const float* z = logits + (size_t)row * V;
-    float m = -INFINITY;
-    int idx = 0x7fffffff;
-    double s = 0.0;
-
-    // a chunk of values in ascending index order: its maximum first, then one rescale of the running sum, then
-    // the chunk's terms (summed in float32, as accurate as the float32 exponentials themselves)
-    auto take = [&](const float* x, const int* vi, auto n_c) {
-        constexpr int n = decltype(n_c)::value;
-        float cm = x[0];
-        int ci = vi[0];
-#pragma unroll
-        for (int e = 1; e < n; e++)
-            if (x[e] > cm) {
-                cm = x[e];
-                ci = vi[e];
-            }
-        if (cm > m) {
-            if (SAMPLE) s *= (double)expf((m - cm) * inv_tau);  // m = -inf: s is still 0
-            m = cm;
-            idx = ci;
-        }
-        if (SAMPLE) {
-            float cs = 0.f;
-#pragma unroll
-            for (int e = 0; e < n; e++) cs += expf((x[e] - m) * inv_tau);  // padding is -inf: adds 0
-            s += (double)cs;
-        }
-    };
-
-    if ((V & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0) {
-        // seg is a multiple of 4 and rows are 16-byte aligned
-        const float4* z4 = reinterpret_cast<const float4*>(z);
-        const int e4 = v1 / 4;
-        for (int v = v0 / 4 + threadIdx.x; v < e4; v += 256 * 4) {
-            float4 q[4];
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-                const int vv = v + 256 * u;
-                q[u] = vv < e4 ? z4[vv] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-            }
-            float x[16];
-            int vi[16];
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-                x[4 * u] = q[u].x;
-                x[4 * u + 1] = q[u].y;
-                x[4 * u + 2] = q[u].z;
-                x[4 * u + 3] = q[u].w;
-#pragma unroll
-                for (int e = 0; e < 4; e++) vi[4 * u + e] = 4 * (v + 256 * u) + e;
-            }
-            take(x, vi, std::integral_constant<int, 16>{});
-        }
-    } else {
-        for (int v = v0 + threadIdx.x; v < v1; v += 256) {
-            const float x = z[v];
-            take(&x, &v, std::integral_constant<int, 1>{});
-        }
-    }
-    if (idx == 0x7fffffff) {  // this thread saw nothing
-        m = -INFINITY;
-        s = 0.0;
-    }
-    // wavefront reduction, then across the 4 wavefronts through LDS
-    for (int off = 32; off > 0; off >>= 1) {
-        const float m2 = __shfl_xor(m, off);
-        const int i2 = __shfl_xor(idx, off);
-        const double s2 = __shfl_xor(s, off);
-        stat_merge<SAMPLE>(m, idx, s, m2, i2, s2, inv_tau);
-    }
-    __shared__ float sm[4];
-    __shared__ int si[4];
-    __shared__ double ss[4];
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        sm[w] = m;
-        si[w] = idx;
-        ss[w] = s;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 1; i < 4; i++) stat_merge<SAMPLE>(m, idx, s, sm[i], si[i], ss[i], inv_tau);
-        RowStat r;
-        r.s = s;
-        r.m = m;
-        r.idx = idx;
-        stats[(size_t)row * n_split + split] = r;
-    }
-}
-
 // statistics of a whole row from those of its segments, merged in ascending order
 __device__ inline void row_stat(const RowStat* __restrict__ st, int n_split, float inv_tau, float& m, int& amax, double& S) {
     m = st[0].m;
     amax = st[0].idx;
     S = st[0].s;
-    for (int sp = 1; sp < n_split; sp++) {
-        const float m2 = st[sp].m;
-        if (m2 == -INFINITY) continue;
-        if (m2 > m) {  // strictly greater: equal maxima keep the lower index (earlier segment)
-            S = S * exp(((double)m - (double)m2) * (double)inv_tau) + st[sp].s;
-            m = m2;
-            amax = st[sp].idx;
-        } else {
-            S += st[sp].s * exp(((double)m2 - (double)m) * (double)inv_tau);
+    for (int sp0 = 1; sp0 < n_split; sp0 += 4) {   // four segments' statistics are requested together
+        RowStat r[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) r[u] = st[min(sp0 + u, n_split - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            if (sp0 + u >= n_split || r[u].m == -INFINITY) continue;
+            if (r[u].m > m) {  // strictly greater: equal maxima keep the lower index (earlier segment)
+                S = S * exp(((double)m - (double)r[u].m) * (double)inv_tau) + r[u].s;
+                m = r[u].m;
+                amax = r[u].idx;
+            } else {
+                S += r[u].s * exp(((double)r[u].m - (double)m) * (double)inv_tau);
+            }
         }
     }
 }
@@ -175,22 +82,250 @@ __device__ inline double q_background(const QSrc& q, int qrow, int V, int n_real
     return (double)q.rest[qrow] / (double)(V - n_real);
 }
 
-__device__ inline double q_of(const QSrc& q, int qrow, int V, int d) {
-    if (q.m == 0) return (double)q.dense[(size_t)qrow * V + d];
-    double v = 0.0;
-    bool found = false;
-    int n_real = 0;
-    for (int i = 0; i < q.m; i++) {
-        const int id = q.ids[(size_t)qrow * q.m + i];
-        const float pr = q.probs[(size_t)qrow * q.m + i];
-        if (!q_entry_real(id, pr, V)) continue;
-        n_real++;
-        if (id == d) {
-            v = (double)pr;
-            found = true;
+// Probability of token d (lane's own) in draft row qrow (lane's own), for the first n lanes; called by a whole wavefront.
+// Pairs: as many lanes per row as the n rows leave (8 for up to eight drafts) search its list together, so that the look-up
+// is a handful of independent loads instead of m dependent trips; of several equal ids the last one counts.
+__device__ inline double q_lookup(const QSrc& q, int qrow, int V, int d, bool want, int n, int lane) {
+    if (q.m == 0) return want ? (double)q.dense[(size_t)qrow * V + d] : 0.0;
+    int per = 64;
+    while (per > 1 && 64 / per < n) per >>= 1;   // lanes per row
+    const int r = lane / per, sub = lane & (per - 1);
+    const int d_r = __shfl(d, r), qrow_r = __shfl(qrow, r);
+    const bool want_r = __shfl((int)want, r) != 0 && r < n;
+    int best = -1, n_real = 0;
+    float v = 0.f;
+    if (want_r) {
+        const int32_t* ids = q.ids + (size_t)qrow_r * q.m;
+        const float* probs = q.probs + (size_t)qrow_r * q.m;
+#pragma unroll 4
+        for (int e = sub; e < q.m; e += per) {
+            const int id = ids[e];
+            const float pr = probs[e];
+            if (!q_entry_real(id, pr, V)) continue;
+            n_real++;
+            if (id == d_r) {
+                best = e;
+                v = pr;
+            }
         }
     }
-    return found ? v : q_background(q, qrow, V, n_real);
+    for (int off = 1; off < per; off <<= 1) {
+        n_real += __shfl_xor(n_real, off);
+        const int b2 = __shfl_xor(best, off);
+        const float v2 = __shfl_xor(v, off);
+        if (b2 > best) {
+            best = b2;
+            v = v2;
+        }
+    }
+    // back from the searching lanes (r * per) to the lane that asked
+    const int from = (lane * per) & 63;
+    best = __shfl(best, from);
+    v = __shfl(v, from);
+    n_real = __shfl(n_real, from);
+    if (!want) return 0.0;
+    return best >= 0 ? (double)v : q_background(q, qrow, V, n_real);
+}
+
+struct __align__(16) KPack {
+    uint8_t k[1024];
+};
+
+// rows before request i are its drafts and one more per request; every lane gets the drafts before it
+__device__ inline int drafts_before(const KPack& kp, int i, int lane) {
+    // lane l sums bytes 16 l .. 16 l + 15 below i: one load for all 1024
+    const uint4 w = *reinterpret_cast<const uint4*>(kp.k + 16 * lane);
+    const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+    int n = 0;
+#pragma unroll
+    for (int u = 0; u < 4; u++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) n += 16 * lane + 4 * u + e < i ? (int)((ws[u] >> (8 * e)) & 0xffu) : 0;
+    for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off);
+    return n;
+}
+
+struct Judged {
+    bool fail;    // the draft behind this lane's row is rejected ...
+    bool close;   // ... or kept by so little that the decision needs the normaliser in float64
+    float m;      // the row's maximum
+    double zd, lhs;
+};
+
+// The accept test of up to 64 drafts of one request at once: lane l judges draft j0+l+1 against row j0+l, for the rows
+// below jn (Eq. 1; in greedy mode equality with the row's argmax).
+__device__ inline Judged judge_rows(int mode, int row0, int d0, int j0, int jn, int V, int n_split, float inv_tau, double it,
+                                    const float* __restrict__ logits, const int32_t* __restrict__ tokens, const QSrc& draft_q,
+                                    const float* __restrict__ u_acc, const RowStat* __restrict__ stats, int lane) {
+    const int j = j0 + lane;
+    const bool on = j < jn;
+    Judged r{false, false, 0.f, 0.0, 0.0};
+    const int d = on ? tokens[row0 + j + 1] : -1;
+    const bool real = on && d >= 0 && d < V;
+    if (mode == SLED_GREEDY) {
+        if (on) {
+            int amax;
+            double S;
+            row_stat(stats + (size_t)(row0 + j) * n_split, n_split, inv_tau, r.m, amax, S);
+            r.fail = d != amax;
+        }
+        return r;
+    }
+    const float zf = real ? logits[(size_t)(row0 + j) * V + d] : 0.f;
+    const double qd = q_lookup(draft_q, d0 + j, V, d, real, min(64, jn - j0), lane);
+    if (real) {
+        int amax;
+        double S;
+        row_stat(stats + (size_t)(row0 + j) * n_split, n_split, inv_tau, r.m, amax, S);
+        r.zd = (double)zf;
+        const double pd = exp((r.zd - (double)r.m) * it) / S;
+        r.lhs = (double)u_acc[d0 + j] * qd;
+        r.fail = !(r.lhs <= pd);
+        // S carries the float32 round-off of the row scan (about 1e-7): a test this close is decided again
+        r.close = fabs(r.lhs - pd) <= 1e-4 * pd;
+    } else if (on) {
+        r.fail = true;  // a draft outside the vocabulary has no target probability: rejected where it stands
+    }
+    return r;
+}
+
+// e^a in float32 for a <= 0, -inf or NaN: a log2(e) as a rounded product and its remainder, the hardware exponential of the
+// first, the second to first order.  (The scan of 16 segments per row is bound by the exponentials' instructions.)
+__device__ inline float expf_nonpos(float a) {
+    a = a < -150.f ? -150.f : a;   // (not fmax: a NaN stays one)
+    const float h = a * 1.44269502f;
+    const float l = fmaf(a, 1.92596303e-8f, fmaf(a, 1.44269502f, -h));
+    const float e = __builtin_amdgcn_exp2f(h);
+    return fmaf(e, l * 0.693147182f, e);
+}
+
+// statistics of elements v0 .. v1-1 of a row, by the whole workgroup of 256
+template <bool SAMPLE>
+__device__ inline void scan_segment(const float* __restrict__ z, bool vec, int v0, int v1, float inv_tau, RowStat* __restrict__ dst) {
+    float m = -INFINITY;
+    int idx = 0x7fffffff;
+    double s = 0.0;
+
+    // a chunk of values in ascending index order: its maximum first, then one rescale of the running sum, then
+    // the chunk's terms (summed in float32, as accurate as the float32 exponentials themselves)
+    auto take = [&](const float* x, auto n_c, auto index_of) {
+        constexpr int n = decltype(n_c)::value;
+        float cm = x[0];
+        int ce = 0;
+#pragma unroll
+        for (int e = 1; e < n; e++) {
+            const bool gt = x[e] > cm;
+            cm = gt ? x[e] : cm;
+            ce = gt ? e : ce;
+        }
+        if (cm > m) {
+            if (SAMPLE) s *= (double)expf_nonpos((m - cm) * inv_tau);  // m = -inf: s is still 0
+            m = cm;
+            idx = index_of(ce);
+        }
+        if (SAMPLE) {
+            float cs = 0.f;
+#pragma unroll
+            for (int e = 0; e < n; e++) cs += expf_nonpos((x[e] - m) * inv_tau);  // padding is -inf: adds 0
+            s += (double)cs;
+        }
+    };
+
+    if (vec) {
+        // v0 is a multiple of 4 and rows are 16-byte aligned
+        const float4* z4 = reinterpret_cast<const float4*>(z);
+        const int e4 = v1 / 4;
+        for (int v = v0 / 4 + threadIdx.x; v < e4; v += 256 * 4) {
+            float4 q[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const int vv = v + 256 * u;
+                q[u] = vv < e4 ? z4[vv] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+            }
+            const float x[16] = {q[0].x, q[0].y, q[0].z, q[0].w, q[1].x, q[1].y, q[1].z, q[1].w,
+                                 q[2].x, q[2].y, q[2].z, q[2].w, q[3].x, q[3].y, q[3].z, q[3].w};
+            take(x, std::integral_constant<int, 16>{}, [&](int e) { return 4 * (v + 256 * (e >> 2)) + (e & 3); });
+        }
+    } else {
+        for (int v = v0 + threadIdx.x; v < v1; v += 256) {
+            const float x = z[v];
+            take(&x, std::integral_constant<int, 1>{}, [&](int) { return v; });
+        }
+    }
+    if (idx == 0x7fffffff) {  // this thread saw nothing
+        m = -INFINITY;
+        s = 0.0;
+    }
+    // over the wavefront, then across the 4 wavefronts through LDS: the maximum first, so that each sum is rescaled once
+    auto rescaled = [&](double s2, float m2, float top) { return m2 == -INFINITY ? 0.0 : m2 == top ? s2 : s2 * (double)expf_nonpos((m2 - top) * inv_tau); };
+    float top = m;
+    for (int off = 32; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
+    int first = m == top ? idx : 0x7fffffff;   // of equal maxima the lowest index
+    for (int off = 32; off > 0; off >>= 1) first = min(first, __shfl_xor(first, off));
+    if (SAMPLE) {
+        s = rescaled(s, m, top);
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    }
+    __shared__ float sm[4];
+    __shared__ int si[4];
+    __shared__ double ss[4];
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        sm[w] = top;
+        si[w] = first;
+        ss[w] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        RowStat r{0.0, fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3])), 0x7fffffff};
+        for (int i = 0; i < 4; i++) {
+            if (sm[i] == r.m) r.idx = min(r.idx, si[i]);
+            if (SAMPLE) r.s += rescaled(ss[i], sm[i], r.m);
+        }
+        *dst = r;
+    }
+}
+
+// Between two parts of the row scan: over[i] = 1 where one of request i's rows before jn, which the parts so far have scanned
+// (or left out behind a rejection that this test sees first), ends the prefix for certain.  A close test, which the finish
+// decides, ends nothing here.  One wavefront per request.
+__global__ __launch_bounds__(64) void accept_over(int mode, KPack kp, int jn, int V, int n_split, float inv_tau, float temperature,
+                                                  const float* __restrict__ logits, const int32_t* __restrict__ tokens, QSrc qsrc,
+                                                  const float* __restrict__ u_acc, const RowStat* __restrict__ stats, int32_t* __restrict__ over) {
+    const int i = blockIdx.x, lane = threadIdx.x;
+    const int d0 = drafts_before(kp, i, lane);
+    const Judged jd = judge_rows(mode, d0 + i, d0, 0, min(jn, (int)kp.k[i]), V, n_split, inv_tau, 1.0 / (double)temperature, logits, tokens,
+                                 qsrc, u_acc, stats, lane);
+    const unsigned long long certain = __ballot(jd.fail && !jd.close);
+    if (lane == 0) over[i] = certain != 0ull;
+}
+
+// rows j0 .. of every request: what one launch of the row scan takes when it works in parts
+struct RowPart {
+    int B, j0;
+    KPack kp;
+    const int32_t* over;   // accept_over's word on every request; not read for the part that starts at row 0
+};
+
+// blockIdx.x: the packed row; in parts request + B * (row of the request - j0).  (One workgroup for all of a request's rows of
+// a part would start fewer, but the few requests that are left do not fill the chip then: 93 us for rows 4 .. 8 of 256
+// requests.  Making the test in each workgroup instead of ahead of the launch: 59 us.)
+template <bool SAMPLE, bool PART>
+__global__ __launch_bounds__(256) void accept_row_stats(const float* __restrict__ logits, int V, int n_split, int seg,
+                                                        float inv_tau, std::conditional_t<PART, RowPart, int> part, RowStat* __restrict__ stats) {
+    const int split = blockIdx.y;
+    const int v0 = split * seg;
+    const int v1 = min(V, v0 + seg);
+    const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;   // (seg is a multiple of 4)
+    int row = blockIdx.x;
+    if constexpr (PART) {
+        // Workgroups go to the XCDs round robin, so with a batch of a multiple of eight all rows and segments of a request would
+        // meet on one of them, and of the later parts' few requests some XCDs get twice their share: turned by row and segment.
+        const int jj = row / part.B, i = (row - jj * part.B + jj + 3 * split) % part.B, j = part.j0 + jj;
+        if (j > part.kp.k[i] || (part.j0 > 0 && part.over[i])) return;
+        row = drafts_before(part.kp, i, threadIdx.x & 63) + i + j;
+    }
+    scan_segment<SAMPLE>(logits + (size_t)row * V, vec, v0, v1, inv_tau, stats + (size_t)row * n_split + split);
 }
 
 struct Decision {
@@ -201,54 +336,33 @@ struct Decision {
     int amax;    // and its argmax
 };
 
-// One wavefront decides one request: lane j judges draft j+1 against row j; the first failing lane ends the
-// accepted prefix (Eq. 1; in greedy mode the test is equality with the row's argmax).
+// One wavefront decides one request: the first failing lane of judge_rows ends the accepted prefix.
 __device__ inline Decision decide_request(int mode, int i, const KPack& kp, int V, int n_split, float inv_tau, double it,
                                           const float* __restrict__ logits, const int32_t* __restrict__ tokens,
                                           const QSrc& draft_q, const float* __restrict__ u_acc,
                                           const RowStat* __restrict__ stats, int lane) {
-    int row0 = 0;
-    for (int r = lane; r < i; r += 64) row0 += kp.k[r];
-    for (int off = 32; off > 0; off >>= 1) row0 += __shfl_xor(row0, off);
-    const int d0 = row0;   // drafts before this request
-    row0 += i;             // rows before it: one more per request
+    const int d0 = drafts_before(kp, i, lane);   // drafts before this request
+    const int row0 = d0 + i;                     // rows before it: one more per request
     const int k = kp.k[i];
     int a = k;
     for (int j0 = 0; j0 < k; j0 += 64) {
-        const int j = j0 + lane;
-        bool fail = false, close = false;
-        float m = 0.f;
-        double zd = 0.0, lhs = 0.0;
-        if (j < k) {
-            int amax;
-            double S;
-            row_stat(stats + (size_t)(row0 + j) * n_split, n_split, inv_tau, m, amax, S);
-            const int d = tokens[row0 + j + 1];
-            if (mode == SLED_GREEDY) {
-                fail = (d != amax);
-            } else if (d < 0 || d >= V) {
-                fail = true;  // a draft outside the vocabulary has no target probability: rejected where it stands
-            } else {
-                zd = (double)logits[(size_t)(row0 + j) * V + d];
-                const double pd = exp((zd - (double)m) * it) / S;
-                lhs = (double)u_acc[d0 + j] * q_of(draft_q, d0 + j, V, d);
-                fail = !(lhs <= pd);
-                // S carries the float32 round-off of the row scan (about 1e-7): a test this close is decided again below
-                close = fabs(lhs - pd) <= 1e-4 * pd;
-            }
-        }
+        const Judged jd = judge_rows(mode, row0, d0, j0, k, V, n_split, inv_tau, it, logits, tokens, draft_q, u_acc, stats, lane);
+        bool fail = jd.fail;
         // Rare: the two sides of Eq. 1 agree to four digits.  The whole wavefront then sums the row's normaliser in
-        // float64, in a fixed order (lane-strided partial sums, then a butterfly), and the lane decides again.
-        unsigned long long todo = __ballot(close);
+        // float64, in a fixed order (lane-strided partial sums, then a butterfly), and the lane decides again.  Rows
+        // behind the first certain rejection do not matter (and may not have been scanned).
+        const unsigned long long certain = __ballot(jd.fail && !jd.close);
+        unsigned long long todo = __ballot(jd.close);
+        if (certain) todo &= (certain & (0ull - certain)) - 1ull;
         while (todo) {
             const int src = __ffsll((long long)todo) - 1;
             todo &= todo - 1;
-            const float ms = __shfl(m, src);
+            const float ms = __shfl(jd.m, src);
             const float* z = logits + (size_t)(row0 + j0 + src) * V;
             double part = 0.0;
             for (int v = lane; v < V; v += 64) part += exp(((double)z[v] - (double)ms) * it);
             for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
-            if (lane == src) fail = !(lhs <= exp((zd - (double)m) * it) / part);
+            if (lane == src) fail = !(jd.lhs <= exp((jd.zd - (double)jd.m) * it) / part);
         }
         const unsigned long long mask = __ballot(fail);
         if (mask) {
@@ -269,22 +383,162 @@ constexpr int SLED_SPARSE_Q_MAX = 1024;  // entries per draft of a sparse draft 
 constexpr int WTILE = 1024;        // elements per wavefront tile: 16 consecutive ones per lane
 constexpr int MAX_WTILES = 2048;   // covers vocabularies up to 2 097 152
 
+// the row a request's token is drawn from, as the float64 sweeps see it
+struct RowView {
+    const float* z;
+    const float* q;    // dense draft distribution of the rejected draft, or nullptr
+    double m, it;
+    int V;
+    bool vec;          // rows of z and q are 16-byte aligned
+};
+
+// Sums over tiles t0, t0 + step, .. of exp((z - m)/tau) (proportional to p), or with `residual` of max(0, p - q), p = that *
+// inv_S (qconst >= 0: against the same q everywhere -- the background of a sparse q with remainder mass); by one wavefront,
+// into out[t].  Loads are whole KiB, and with AHEAD those of the next tile are under way while this one's exponentials are computed;
+// the order of the additions within a tile is fixed (16 values of a lane, then a butterfly).
+template <bool AHEAD>
+__device__ inline void sweep_tiles(const RowView& r, bool residual, double inv_S, double qconst, int t0, int t_end, int step,
+                                   double* out, int lane) {
+    const bool use_q = residual && qconst < 0.0 && r.q;
+    auto load = [&](const float* p, int t, float* x, float pad) {   // values 256 u + 4 lane + 0..3 of the tile (64 e + lane when unaligned)
+        if (r.vec) {
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const int v = t * WTILE + u * 256 + lane * 4;
+                float4 y = make_float4(pad, pad, pad, pad);
+                if (v < r.V) y = *reinterpret_cast<const float4*>(p + v);
+                x[4 * u] = y.x;
+                x[4 * u + 1] = y.y;
+                x[4 * u + 2] = y.z;
+                x[4 * u + 3] = y.w;
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                const int v = t * WTILE + e * 64 + lane;
+                x[e] = v < r.V ? p[v] : pad;
+            }
+        }
+    };
+    float zx[16], qx[16], zn[16], qn[16];
+    auto fetch = [&](int t) {
+#pragma unroll
+        for (int e = 0; e < 16; e++) qn[e] = 0.f;
+        load(r.z, t, zn, -INFINITY);
+        if (use_q) load(r.q, t, qn, 0.f);
+    };
+    if (AHEAD && t0 < t_end) fetch(t0);
+    for (int t = t0; t < t_end; t += step) {
+        if (!AHEAD) fetch(t);
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            zx[e] = zn[e];
+            qx[e] = qn[e];
+        }
+        if (AHEAD && t + step < t_end) fetch(t + step);
+        double acc = 0.0;
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            const double ev = exp(((double)zx[e] - r.m) * r.it);  // exp(-inf) = 0 beyond the row
+            if (residual) {
+                const double d = ev * inv_S - (qconst >= 0.0 ? qconst : (double)qx[e]);
+                acc += d > 0.0 ? d : 0.0;
+            } else {
+                acc += ev;
+            }
+        }
+        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+        if (lane == 0) out[t] = acc;
+    }
+}
+
+// Total of the tile sums by one wavefront (per lane a run of tiles in ascending order, then a scan over the lanes); `incl`,
+// `part`: the running sum behind this lane's run, and the run's own
+__device__ inline double tile_total(const double* tile_sum, int n_tiles, int lane, double& incl, double& part) {
+    const int per = (n_tiles + 63) / 64;
+    const int t0 = lane * per, t1 = min(n_tiles, t0 + per);
+    part = 0.0;
+    for (int t = t0; t < t1; t++) part += tile_sum[t];
+    incl = part;
+    for (int off = 1; off < 64; off <<= 1) {
+        const double o = __shfl_up(incl, off);
+        if (lane >= off) incl += o;
+    }
+    return __shfl(incl, 63);
+}
+
+// A batch too small to fill the chip with one workgroup per request: the sweeps run as launches of their own, gridDim.y
+// workgroups per request, and leave their tile sums in the workspace (per request n_tiles of p, then n_tiles of the residual)
+// for accept_finish.  SECOND: the residual's, which need the total of the first; same sums in the same order either way.
+template <bool SECOND>
+__global__ __launch_bounds__(512) void accept_sweep(KPack kp, int V, int n_split, float inv_tau, float temperature,
+                                                    const float* __restrict__ logits, const int32_t* __restrict__ tokens, QSrc qsrc,
+                                                    const float* __restrict__ u_acc, const RowStat* __restrict__ stats,
+                                                    Decision* __restrict__ decisions, double* __restrict__ tile_sums) {
+    __shared__ Decision sh_dc;
+    __shared__ double sh_S;
+    __shared__ int sh_real;
+    const int i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int n_tiles = (V + WTILE - 1) / WTILE;
+    double* sums = tile_sums + (size_t)i * 2 * n_tiles;
+    if (tid == 64) sh_real = 0;
+    const double it = 1.0 / (double)temperature;
+    if (wv == 0) {
+        if (SECOND) {
+            double incl, part;
+            const double S = tile_total(sums, n_tiles, lane, incl, part);
+            if (lane == 0) {
+                sh_S = S;
+                sh_dc = decisions[i];
+            }
+        } else {
+            const Decision dc = decide_request(SLED_SAMPLE, i, kp, V, n_split, inv_tau, it, logits, tokens, qsrc, u_acc, stats, lane);
+            if (lane == 0) {
+                sh_dc = dc;
+                if (blockIdx.y == 0) decisions[i] = dc;
+            }
+        }
+    }
+    __syncthreads();
+    const Decision dc = sh_dc;
+    const bool sparse = qsrc.m > 0;
+    double qconst = -1.0;
+    if (SECOND) {
+        if (dc.qrow < 0) return;   // drawn from p
+        if (sparse) {
+            int n = 0;
+            for (int e = tid; e < qsrc.m; e += blockDim.x)
+                n += q_entry_real(qsrc.ids[(size_t)dc.qrow * qsrc.m + e], qsrc.probs[(size_t)dc.qrow * qsrc.m + e], V);
+            if (n) atomicAdd(&sh_real, n);
+            __syncthreads();
+            qconst = q_background(qsrc, dc.qrow, V, sh_real);
+            if (!(qconst > 0.0)) return;   // accept_finish has the background from the sums of p
+        }
+    }
+    const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0 && (reinterpret_cast<uintptr_t>(qsrc.dense) & 15) == 0;
+    const RowView rv{logits + (size_t)dc.row * V, dc.qrow >= 0 && !sparse ? qsrc.dense + (size_t)dc.qrow * V : nullptr, (double)dc.m, it, V, vec};
+    sweep_tiles<true>(rv, SECOND, SECOND ? 1.0 / sh_S : 1.0, qconst, blockIdx.y * (blockDim.x >> 6) + wv, n_tiles, gridDim.y * (blockDim.x >> 6),
+                SECOND ? sums + n_tiles : sums, lane);
+}
+
 __global__ __launch_bounds__(1024) void accept_finish(int mode, KPack kp, int V, int n_split, float inv_tau, float temperature,
                                                       const float* __restrict__ logits, const int32_t* __restrict__ tokens,
                                                       QSrc qsrc, const float* __restrict__ u_acc,
                                                       const float* __restrict__ u_smp, const RowStat* __restrict__ stats,
-                                                      int32_t* __restrict__ accept_len, int32_t* __restrict__ out_token) {
+                                                      int32_t* __restrict__ accept_len, int32_t* __restrict__ out_token,
+                                                      const Decision* __restrict__ decisions, const double* __restrict__ tile_sums) {
     __shared__ double tile_sum[MAX_WTILES];
     __shared__ double sp_take[SLED_SPARSE_Q_MAX];   // sparse q: probability mass entry i removes from p
-    __shared__ int sp_tile[SLED_SPARSE_Q_MAX];      //           and the tile it falls in (-1: padding)
+    __shared__ __align__(16) int sp_tile[SLED_SPARSE_Q_MAX];   //           and the tile it falls in (-1: padding)
     __shared__ double q_tile[WTILE];                //           q over the tile that holds the draw
     __shared__ Decision sh_dc;
-    __shared__ int sh_tile, sh_real;
+    __shared__ int sh_tile;
     __shared__ double sh_base, sh_total;
     const int i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, n_wv = blockDim.x >> 6;
     if (wv == 0) {
         // float64 work divides by the temperature as given (a float32 number), exactly as a float64 reference does
-        const Decision dc = decide_request(mode, i, kp, V, n_split, inv_tau, 1.0 / (double)temperature, logits, tokens, qsrc, u_acc, stats, lane);
+        const Decision dc = decisions ? decisions[i]   // accept_sweep has decided
+                                      : decide_request(mode, i, kp, V, n_split, inv_tau, 1.0 / (double)temperature, logits, tokens, qsrc, u_acc, stats, lane);
         if (lane == 0) {
             sh_dc = dc;
             accept_len[i] = dc.a;
@@ -323,8 +577,7 @@ __global__ __launch_bounds__(1024) void accept_finish(int mode, KPack kp, int V,
     };
     // this lane's 16 weights of tile t: exp((z - m)/tau) (proportional to p), or max(0, p - q) with p = that / S
     // (with sparse q the residual is only ever needed inside the tile that holds the draw, whose q is in q_tile)
-    // (qconst >= 0: the residual against the same q everywhere -- the background of a sparse q with remainder mass)
-    auto weights = [&](int t, bool residual, double inv_S, double* w, double qconst = -1.0) {
+    auto weights = [&](int t, bool residual, double inv_S, double* w) {
         const int v = t * WTILE + lane * 16;
         float zx[16], qx[16];
         load16(z, v, zx, -INFINITY);
@@ -333,23 +586,21 @@ __global__ __launch_bounds__(1024) void accept_finish(int mode, KPack kp, int V,
         for (int e = 0; e < 16; e++) {
             const double ev = exp(((double)zx[e] - m) * it);  // exp(-inf) = 0 beyond the row
             if (residual) {
-                const double r = ev * inv_S - (qconst >= 0.0 ? qconst : sparse ? q_tile[lane * 16 + e] : (double)qx[e]);
+                const double r = ev * inv_S - (sparse ? q_tile[lane * 16 + e] : (double)qx[e]);
                 w[e] = r > 0.0 ? r : 0.0;
             } else {
                 w[e] = ev;
             }
         }
     };
-    // every wavefront sums whole tiles (lane order, then a butterfly): no workgroup barrier per tile
+    const RowView rv{z, q, m, it, V, vec};
+    // every wavefront sums whole tiles: no workgroup barrier per tile; or accept_sweep has summed them
     auto sweep = [&](bool residual, double inv_S, double qconst = -1.0) {
-        for (int t = wv; t < n_tiles; t += n_wv) {
-            double w[16];
-            weights(t, residual, inv_S, w, qconst);
-            double acc = 0.0;
-#pragma unroll
-            for (int e = 0; e < 16; e++) acc += w[e];
-            for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-            if (lane == 0) tile_sum[t] = acc;
+        if (tile_sums) {
+            const double* src = tile_sums + ((size_t)i * 2 + (residual ? 1 : 0)) * n_tiles;
+            for (int t = tid; t < n_tiles; t += blockDim.x) tile_sum[t] = src[t];
+        } else {
+            sweep_tiles<false>(rv, residual, inv_S, qconst, wv, n_tiles, n_wv, tile_sum, lane);
         }
         __syncthreads();
     };
@@ -359,14 +610,8 @@ __global__ __launch_bounds__(1024) void accept_finish(int mode, KPack kp, int V,
         if (wv == 0) {
             const int per = (n_tiles + 63) / 64;
             const int t0 = lane * per, t1 = min(n_tiles, t0 + per);
-            double part = 0.0;
-            for (int t = t0; t < t1; t++) part += tile_sum[t];
-            double incl = part;
-            for (int off = 1; off < 64; off <<= 1) {
-                const double o = __shfl_up(incl, off);
-                if (lane >= off) incl += o;
-            }
-            const double total = __shfl(incl, 63);
+            double incl, part;
+            const double total = tile_total(tile_sum, n_tiles, lane, incl, part);
             const double target = u * total;
             const unsigned long long mask = __ballot(incl > target && t1 > t0);
             // round-off can leave no lane past the target: then the last tile holds the crossing
@@ -409,16 +654,13 @@ __global__ __launch_bounds__(1024) void accept_finish(int mode, KPack kp, int V,
             // max(0, p - c) - max(0, p - q).
             const int32_t* ids = qsrc.ids + (size_t)dc.qrow * qsrc.m;
             const float* pr = qsrc.probs + (size_t)dc.qrow * qsrc.m;
-            if (tid == 0) {
-                int n_real = 0;
-                for (int e = 0; e < qsrc.m; e++) n_real += q_entry_real(ids[e], pr[e], V);
-                sh_real = n_real;
-            }
-            __syncthreads();
-            qbg = q_background(qsrc, dc.qrow, V, sh_real);
+            // (a workgroup has a thread for every entry a row can have)
+            const int n_real = __syncthreads_count(tid < qsrc.m && q_entry_real(ids[tid < qsrc.m ? tid : 0], pr[tid < qsrc.m ? tid : 0], V));
+            qbg = q_background(qsrc, dc.qrow, V, n_real);
             if (qbg > 0.0) {
                 sweep(true, 1.0 / S, qbg);
             }
+            if (tid >= qsrc.m && tid < ((qsrc.m + 3) & ~3)) sp_tile[tid] = -1;
             for (int e = tid; e < qsrc.m; e += blockDim.x) {
                 const int id = ids[e];
                 const double qv = (double)pr[e];
@@ -435,8 +677,13 @@ __global__ __launch_bounds__(1024) void accept_finish(int mode, KPack kp, int V,
             __syncthreads();
             for (int t = tid; t < n_tiles; t += blockDim.x) {
                 double r = qbg > 0.0 ? tile_sum[t] : tile_sum[t] * (1.0 / S);
-                for (int e = 0; e < qsrc.m; e++)   // in entry order: the result does not depend on the thread layout
-                    if (sp_tile[e] == t) r -= sp_take[e];
+                for (int e = 0; e < qsrc.m; e += 4) {   // in entry order: the result does not depend on the thread layout
+                    const int4 te = *reinterpret_cast<const int4*>(sp_tile + e);   // (the tail up to a multiple of 4 is padding)
+                    if (te.x == t) r -= sp_take[e];
+                    if (te.y == t) r -= sp_take[e + 1];
+                    if (te.z == t) r -= sp_take[e + 2];
+                    if (te.w == t) r -= sp_take[e + 3];
+                }
                 tile_sum[t] = r > 0.0 ? r : 0.0;
             }
             __syncthreads();
@@ -529,6 +776,13 @@ size_t sled_accept_ws_bytes(int B, int T, int n_split) {
     return (stats + 255) & ~(size_t)255;
 }
 
+// Behind the statistics: tile sums and decisions of the sweeps that run as launches of their own, and accept_over's word on every
+// request.  A workspace without that room is as good: the rows are then scanned in one launch and the finish sweeps itself.
+static size_t sweep_ws_bytes(int B, int vocab) {
+    return (size_t)B * (sizeof(Decision) + sizeof(int32_t) + 2 * (size_t)((vocab + WTILE - 1) / WTILE) * sizeof(double));
+}
+size_t sled_accept_ws_bytes_full(int B, int T, int vocab) { return sled_accept_ws_bytes(B, T, 16) + 256 + sweep_ws_bytes(B, vocab); }
+
 int sled_accept_pick_split(int T, int vocab) {
     // enough workgroups (rows x segments) for several rounds over the chip, so that the last round is short
     int n = (8192 + T - 1) / T;
@@ -541,26 +795,82 @@ int sled_accept_pick_split(int T, int vocab) {
 int sled_launch_accept(int mode, int B, int T, const int* k_host, int vocab, float temperature, const float* logits,
                        const int32_t* tokens, const float* draft_q, const int32_t* q_ids, const float* q_probs,
                        const float* q_rest, int q_m, const float* u_acc, const float* u_smp, int32_t* accept_len, int32_t* out_token, void* ws,
-                       hipStream_t st) {
+                       size_t ws_bytes, hipStream_t st) {
     if ((vocab + WTILE - 1) / WTILE > MAX_WTILES) SLED_FAIL(SLED_EINVAL, "accept: vocabulary %d too large", vocab);
     if (q_m < 0 || q_m > SLED_SPARSE_Q_MAX) SLED_FAIL(SLED_EINVAL, "accept: %d sparse entries per draft, at most %d", q_m, SLED_SPARSE_Q_MAX);
     KPack kp;
     for (int i = 0; i < B; i++) kp.k[i] = (uint8_t)k_host[i];
     QSrc qsrc{draft_q, q_ids, q_probs, q_m > 0 ? q_rest : nullptr, q_m};
-    const int n_split = sled_accept_pick_split(T, vocab);
+    const float inv_tau = 1.0f / temperature;
+    // The scan in parts.  A cut at row c saves the rows from c on of every request that ends before c and costs a launch
+    // and its drain, about 8 us: made where the rows behind it are at least 64 MB x c (the longer the prefix, the fewer
+    // requests still get there), unless so few requests have long drafts that most workgroups of a part would be empty.
+    // 256 requests x 8 drafts x 128256 tokens, 62 % accepted: 204 us in one launch, 115 + 10 in three.
+    auto rows_from = [&](int c) {
+        int64_t n = 0;
+        for (int i = 0; i < B; i++) n += std::max(0, k_host[i] + 1 - c);
+        return n;
+    };
+    int k_top = 0;
+    for (int i = 0; i < B; i++) k_top = std::max(k_top, k_host[i]);
+    const int n_tiles = (vocab + WTILE - 1) / WTILE;
+    const bool room = ws_bytes >= sled_accept_ws_bytes(B, T, sled_accept_pick_split(T, vocab)) + sweep_ws_bytes(B, vocab);
+    int cuts[4] = {0, 0, 0, 0}, n_part = 1;
+    for (int c = 2; room && c <= 8 && c <= k_top; c *= 2)
+        if (rows_from(c) * vocab * 4 >= (int64_t)64000000 * c && (int64_t)B * (k_top + 1 - c) <= 4 * rows_from(c)) cuts[n_part++] = c;
+    // Segments per row: about 2048 workgroups in the (first) launch.  More of them are shorter than their own start and
+    // reduction: 276 rows in 16 segments took 45 us for 141 MB, in 7 27 us.
+    const int64_t rows_first = n_part > 1 ? T - rows_from(cuts[1]) : T;
+    const int n_split = std::min(sled_accept_pick_split(T, vocab), (int)std::max<int64_t>(1, (2048 + rows_first / 2) / rows_first));
     int seg = (vocab + n_split - 1) / n_split;
     seg = (seg + 3) & ~3;
     RowStat* stats = reinterpret_cast<RowStat*>(ws);
-    const float inv_tau = 1.0f / temperature;
-    dim3 grid(T, n_split);
-    if (mode == SLED_SAMPLE)
-        hipLaunchKernelGGL(accept_row_stats<true>, grid, dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, stats);
-    else
-        hipLaunchKernelGGL(accept_row_stats<false>, grid, dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, stats);
-    SLED_LAUNCH_CHECK();
+    double* sums = reinterpret_cast<double*>(static_cast<char*>(ws) + sled_accept_ws_bytes(B, T, n_split));
+    Decision* decided = reinterpret_cast<Decision*>(sums + (size_t)B * 2 * n_tiles);
+    int32_t* over = reinterpret_cast<int32_t*>(decided + B);   // (these three only with room)
+    for (int part = 0; part < n_part && n_part > 1; part++) {
+        const int j0 = cuts[part], j1 = part + 1 < n_part ? cuts[part + 1] : k_top + 1;
+        const RowPart rp{B, j0, kp, over};
+        if (j0 > 0) {
+            hipLaunchKernelGGL(accept_over, dim3(B), dim3(64), 0, st, mode, kp, j0, vocab, n_split, inv_tau, temperature, logits, tokens, qsrc, u_acc,
+                               stats, over);
+            SLED_LAUNCH_CHECK();
+        }
+        const dim3 grid(B * (j1 - j0), n_split);
+        if (mode == SLED_SAMPLE)
+            hipLaunchKernelGGL((accept_row_stats<true, true>), grid, dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, rp, stats);
+        else
+            hipLaunchKernelGGL((accept_row_stats<false, true>), grid, dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, rp, stats);
+        SLED_LAUNCH_CHECK();
+    }
+    if (n_part == 1) {
+        const dim3 grid(T, n_split);
+        if (mode == SLED_SAMPLE)
+            hipLaunchKernelGGL((accept_row_stats<true, false>), grid, dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, 0, stats);
+        else
+            hipLaunchKernelGGL((accept_row_stats<false, false>), grid, dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, 0, stats);
+        SLED_LAUNCH_CHECK();
+    }
+    // The two float64 sweeps over a request's row are what the finish spends its time on: 93 us with one workgroup per request,
+    // be they 48 or 256.  Up to 128 requests, from 32 tiles (32768 tokens) on, they get launches of their own with two workgroups
+    // per CU: 48 requests 17 + 14 + 13 us.  Where every CU has a request anyway that does not pay: 256 requests
+    // 48 + 57 + 10 us in three launches, 93 in one.
+    Decision* decisions = nullptr;
+    double* tile_sums = nullptr;
+    if (mode == SLED_SAMPLE && room && n_tiles >= 32 && B <= 128) {
+        tile_sums = sums;
+        decisions = decided;
+        const dim3 grid(B, std::min((n_tiles + 7) / 8, std::max(2, 512 / B)));   // a workgroup has eight wavefronts, a tile each at a time
+        hipLaunchKernelGGL(accept_sweep<false>, grid, dim3(512), 0, st, kp, vocab, n_split, inv_tau, temperature, logits, tokens, qsrc, u_acc, stats,
+                           decisions, tile_sums);
+        SLED_LAUNCH_CHECK();
+        hipLaunchKernelGGL(accept_sweep<true>, grid, dim3(512), 0, st, kp, vocab, n_split, inv_tau, temperature, logits, tokens, qsrc, u_acc, stats,
+                           decisions, tile_sums);
+        SLED_LAUNCH_CHECK();
+    }
     // greedy needs only the deciding wavefront
     hipLaunchKernelGGL(accept_finish, dim3(B), dim3(mode == SLED_SAMPLE ? 1024 : 64), 0, st, mode, kp, vocab, n_split, inv_tau,
-                       temperature, logits, tokens, qsrc, u_acc, u_smp, stats, accept_len, out_token);
+                       temperature, logits, tokens, qsrc, u_acc, u_smp, stats, accept_len, out_token, decisions, tile_sums);
     SLED_LAUNCH_CHECK();
     return SLED_OK;
 }
@@ -614,9 +924,9 @@ extern "C" int sled_accept_static(int mode, int B, const int* k, int vocab, floa
     void* ws = nullptr;
     int rc = static_scratch(&ws);
     if (rc != SLED_OK) return rc;
-    // nothing in the array has to start at zero: the row scan writes every statistic the finish kernel reads
+    // nothing in the array has to start at zero: the row scan writes every statistic that decides anything
     return sled_launch_accept(mode, B, T, k, vocab, temperature, logits, tokens, draft_q, nullptr, nullptr, nullptr, 0, u_acc,
-                              u_smp, accept_len, out_token, ws, static_cast<hipStream_t>(stream));
+                              u_smp, accept_len, out_token, ws, SLED_STATIC_STATS * sizeof(RowStat), static_cast<hipStream_t>(stream));
 }
 
 int sled_launch_row_confidence(int T, int vocab, float temperature, const float* logits, float* conf, int32_t* top, void* ws,
@@ -626,7 +936,7 @@ int sled_launch_row_confidence(int T, int vocab, float temperature, const float*
     seg = (seg + 3) & ~3;
     RowStat* stats = reinterpret_cast<RowStat*>(ws);
     const float inv_tau = 1.0f / temperature;
-    hipLaunchKernelGGL(accept_row_stats<true>, dim3(T, n_split), dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, stats);
+    hipLaunchKernelGGL((accept_row_stats<true, false>), dim3(T, n_split), dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, 0, stats);
     SLED_LAUNCH_CHECK();
     hipLaunchKernelGGL(row_confidence_finish, dim3((T + 255) / 256), dim3(256), 0, st, stats, T, n_split, inv_tau, conf, top);
     SLED_LAUNCH_CHECK();

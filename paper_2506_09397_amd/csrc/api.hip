@@ -1103,7 +1103,7 @@ extern "C" int sled_prefill(sled_model* m, sled_kvpool* p, int req_id, int n_tok
 // ------------------------------------------------------------------------------------------ accept
 extern "C" size_t sled_accept_workspace_bytes(int B, int T, int vocab) {
     if (B < 1 || T < 1 || vocab < 2) return 0;
-    return sled_accept_ws_bytes(B, T, 16) + 256;
+    return sled_accept_ws_bytes_full(B, T, vocab);
 }
 
 namespace {
@@ -1144,7 +1144,7 @@ extern "C" int sled_accept(int mode, int B, const int* k, int vocab, float tempe
     if (mode == SLED_SAMPLE && (!u_smp || (nd > 0 && (!draft_q || !u_acc))))
         SLED_FAIL(SLED_EINVAL, "sled_accept: sampling needs draft_q, u_acc and u_smp");
     return sled_launch_accept(mode, B, T, k, vocab, temperature, logits, tokens, draft_q, nullptr, nullptr, nullptr, 0, u_acc,
-                              u_smp, accept_len, out_token, workspace, static_cast<hipStream_t>(stream));
+                              u_smp, accept_len, out_token, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int sled_accept_sparse(int B, const int* k, int vocab, float temperature, const float* logits, const int32_t* tokens,
@@ -1160,7 +1160,7 @@ extern "C" int sled_accept_sparse(int B, const int* k, int vocab, float temperat
     if (!u_smp || (nd > 0 && (!q_ids || !q_probs || !u_acc)))
         SLED_FAIL(SLED_EINVAL, "sled_accept_sparse: needs q_ids, q_probs, u_acc and u_smp");
     return sled_launch_accept(SLED_SAMPLE, B, T, k, vocab, temperature, logits, tokens, nullptr, q_ids, q_probs, q_rest, q_m, u_acc,
-                              u_smp, accept_len, out_token, workspace, static_cast<hipStream_t>(stream));
+                              u_smp, accept_len, out_token, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int sled_row_confidence(int T, int vocab, float temperature, const float* logits, float* conf, int32_t* top,

@@ -294,11 +294,12 @@ int sled_launch_attention(const sled_model* m, const sled_kvpool* p, const sled_
 int sled_launch_fill_i32(int32_t* p, int32_t v, size_t n, hipStream_t st);
 
 // accept.hip
-size_t sled_accept_ws_bytes(int B, int T, int n_split);
+size_t sled_accept_ws_bytes(int B, int T, int n_split);               // the least that is accepted
+size_t sled_accept_ws_bytes_full(int B, int T, int vocab);            // ... and what is used where it is there
 int sled_accept_pick_split(int T, int vocab);
 int sled_launch_row_confidence(int T, int vocab, float temperature, const float* logits, float* conf, int32_t* top, void* ws,
                                hipStream_t st);
 int sled_launch_accept(int mode, int B, int T, const int* k_host, int vocab, float temperature, const float* logits,
                        const int32_t* tokens, const float* draft_q, const int32_t* q_ids, const float* q_probs,
                        const float* q_rest, int q_m, const float* u_acc, const float* u_smp, int32_t* accept_len, int32_t* out_token, void* ws,
-                       hipStream_t st);
+                       size_t ws_bytes, hipStream_t st);
