@@ -557,12 +557,24 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(sled_step_meta meta, const
     for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
     const float inv = 1.0f / l;
     float* xp = X + (size_t)t * (Hq * D) + h * D;
+    // the D sums over the lanes by halving: each step a lane keeps half of its values and sends the other half (D exchanges
+    // instead of 6 D); lane l ends up with dims l * D/64 ..
 #pragma unroll
-    for (int d = 0; d < D; d++) {
-        float v = o[d] * f;
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-        if (lane == (d & 63)) xp[d] = v * inv;
+    for (int d = 0; d < D; d++) o[d] *= f;
+#pragma unroll
+    for (int s = 0; s < 6; s++) {
+        const int off = 32 >> s, half = (D / 2) >> s;
+        const bool up = (lane & off) != 0;
+#pragma unroll
+        for (int i = 0; i < half; i++) {
+            float a = o[i], b = o[i + half];
+            asm("" : "+v"(a), "+v"(b));   // values, not places: the choice below must not become a dynamic index
+            const float send = up ? a : b, keep = up ? b : a;
+            o[i] = keep + __shfl_xor(send, off);
+        }
     }
+#pragma unroll
+    for (int i = 0; i < D / 64; i++) xp[lane * (D / 64) + i] = o[i] * inv;
 }
 
 }  // namespace

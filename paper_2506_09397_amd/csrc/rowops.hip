@@ -382,14 +382,22 @@ __global__ __launch_bounds__(256) void kv_move_kernel(void* k_buf, void* v_buf, 
         bf16_t* kp = static_cast<bf16_t*>(k_pool) + page;
         bf16_t* vp = static_cast<bf16_t*>(v_pool) + page;
         // K: D is 128 (16 chunks per token and head); in page order chunk = (c / 4) * 64 + (c % 4) * 16 + slot
-#pragma unroll 4
-        for (int e = threadIdx.x; e < Hkv * 256; e += 256) {
-            const int g = e >> 8, c4 = (e >> 6) & 3, slot = (e >> 2) & 15, c = c4 * 4 + (e & 3);
-            if (slot < lo || slot >= hi) continue;
-            bf16_t* u = kb + (size_t)(slot - off) * row + g * 128 + c * 8;
-            bf16_t* q = kp + (size_t)g * 2048 + (c4 * 64 + (e & 3) * 16 + slot) * 8;
-            if (INGEST) st_chunk(q, ld_chunk(u, aligned), true);
-            else st_chunk(u, ld_chunk(q, true), aligned);
+        // (four chunks in flight per thread: a loop of single ones waits for each before it stores it)
+        for (int g0 = 0; g0 < Hkv; g0 += 4) {
+            const int e = threadIdx.x, c4 = (e >> 6) & 3, slot = (e >> 2) & 15, c = c4 * 4 + (e & 3);
+            if (slot < lo || slot >= hi) break;
+            bf16_t* u = kb + (size_t)(slot - off) * row + g0 * 128 + c * 8;
+            bf16_t* q = kp + (size_t)g0 * 2048 + (c4 * 64 + (e & 3) * 16 + slot) * 8;
+            chunk16 t[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                if (g0 + i < Hkv) t[i] = INGEST ? ld_chunk(u + i * 128, aligned) : ld_chunk(q + i * 2048, true);
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                if (g0 + i < Hkv) {
+                    if (INGEST) st_chunk(q + i * 2048, t[i], true);
+                    else st_chunk(u + i * 128, t[i], aligned);
+                }
         }
         // V: thread = (head, 4 slots s4, pair of 16-dim tiles, half of their 16 dims)
         for (int e = threadIdx.x; e < Hkv * 32; e += 256) {
@@ -443,16 +451,37 @@ __global__ __launch_bounds__(256) void kv_move_kernel(void* k_buf, void* v_buf, 
         float* vb = static_cast<float*>(v_buf) + (size_t)layer * n_tok * row;
         float* kp = static_cast<float*>(k_pool) + page;
         float* vp = static_cast<float*>(v_pool) + page;
-        const int n = hi - lo;
-        for (int e = threadIdx.x; e < n * (int)row; e += 256) {
-            const int s = lo + e / (int)row, w = e % (int)row, g = w / D, dd = w - g * D;
-            const size_t u = (size_t)(s - off) * row + w, q = g * head_elems + (size_t)s * D + dd;
-            if (INGEST) {
-                kp[q] = kb[u];
-                vp[q] = vb[u];
-            } else {
-                kb[u] = kp[q];
-                vb[u] = vp[q];
+        // four chunks of 4 values per thread and trip, all requested before the first is stored (heads are multiples of 64 values)
+        const int row4 = (int)row / 4, n4 = (hi - lo) * row4;
+        auto ld4 = [&](const float* p, bool al) { return al ? *reinterpret_cast<const float4*>(p) : make_float4(p[0], p[1], p[2], p[3]); };
+        auto st4 = [&](float* p, const float4& x, bool al) {
+            if (al) {
+                *reinterpret_cast<float4*>(p) = x;
+                return;
+            }
+            p[0] = x.x;
+            p[1] = x.y;
+            p[2] = x.z;
+            p[3] = x.w;
+        };
+        for (int e0 = threadIdx.x; e0 < n4; e0 += 4 * 256) {
+            float4 a[4][2];
+            size_t u[4], q[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const int e = e0 + i * 256;
+                if (e >= n4) continue;
+                const int s = lo + e / row4, w = (e % row4) * 4, g = w / D, dd = w - g * D;
+                u[i] = (size_t)(s - off) * row + w;
+                q[i] = g * head_elems + (size_t)s * D + dd;
+                a[i][0] = INGEST ? ld4(kb + u[i], aligned) : ld4(kp + q[i], true);
+                a[i][1] = INGEST ? ld4(vb + u[i], aligned) : ld4(vp + q[i], true);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                if (e0 + i * 256 >= n4) continue;
+                st4(INGEST ? kp + q[i] : kb + u[i], a[i][0], INGEST || aligned);
+                st4(INGEST ? vp + q[i] : vb + u[i], a[i][1], INGEST || aligned);
             }
         }
     }
