@@ -1,5 +1,9 @@
 // Projections of the verify step: out[T, N] = X[T, K] * W[N, K]^T over the packed rows of a batch.
 //
+// Two kernels share the work of bf16 models.  16-bit weights run in gemm_tile_kernel (both operands through LDS; described there)
+// at every number of rows; 8- and 4-bit weights, batch-invariant models, and the LM head at 97 to 128 rows run in
+// gemm_bf16_kernel, which the following describes.
+//
 // bf16 path (the one that matters): T is about 100-600 packed rows, so every weight byte is used
 // for only T multiply-adds and the kernel is a weight stream bounded by HBM.  It is still a dense
 // contraction, so the arithmetic goes through v_mfma_f32_32x32x16_bf16 (the 16x16 shapes run at
@@ -56,7 +60,7 @@ constexpr int AHEAD = DEPTH + 1;  // activation stages in flight beyond the one 
 constexpr int NXB = AHEAD + 1;    // LDS ring
 // Two workgroup shapes (KG k-groups = k-steps of 16 per stage, CG column groups of 64 columns):
 //   narrow  KG 4, CG 2: 128 columns, 64 k per stage.  Most workgroups per projection: the shape for one block of
-//           rows (up to 128), where the chip has to be filled by column blocks and K slices alone.
+//           rows (up to 128) of 8- and 4-bit weights, and for batch-invariant models at any size, where the chip has to be filled by column blocks and K slices alone.
 //   wide    KG 2, CG 4: 256 columns, 32 k per stage.  Per MFMA it fetches two thirds of the bytes (half the
 //           activations, the same weights): the shape for several row blocks of 8- and 4-bit weights, where the
 //           workgroups are many anyway and the L2 -> CU path, not HBM, is what the MFMAs wait for (bf16 weights: the
@@ -462,7 +466,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(const bf16_t* __r
 }
 
 // ------------------------------------------------------------------------------------------ tile kernel
-// bf16 weights, more than 128 rows: the contraction is bound by the matrix pipes, so the workgroup is shaped for them.
+// 16-bit weights.  With more than 128 rows the contraction is bound by the matrix pipes, so the workgroup is shaped for them.
 // Four wavefronts, ONE per SIMD (512 registers each), own a tile of RT x 32 rows by 256 columns as 2 x 2 quarters; a
 // quarter is RT/2 x 4 accumulator tiles.  Both operands go through a ring of LDS stages of one k-step (16 k), filled
 // by direct-to-LDS loads that keep as many stages in flight as the 160 KiB hold.  Per stage and wavefront (RT = 8):
@@ -473,30 +477,41 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(const bf16_t* __r
 //     no sums to exchange at the end; and its height can follow the batch (plan_for_rows).  Gate/up of 384 rows x 4096
 //     x 28672: 179 -> 137 us; of 256 rows x 8192 x 57344: 392 -> 346 us = 1.39 PFLOP/s executed (both planes), where a
 //     large library product on the same card reaches 1.41: power, not the schedule, is what is left.
+//   - One block of rows (up to 128) runs in a slim tile, RT x 32 rows by 128 columns with two k-steps per stage: as many
+//     workgroups as the narrow shape above and the same K slices, but no k-group sums to exchange at the end, a cost that a
+//     launch of 15 to 60 us feels.  101 rows: gate/up 59.8 -> 57.0, QKV 22.1 -> 19.4, O 16.9 -> 14.2 us, the 8B step 5.97 ->
+//     5.66 ms; one row: QKV 11.8 -> 11.0 us, the step 3.75 -> 3.68 ms.  With an odd number of row tiles the four
+//     wavefronts take a column tile each instead of quarters.
 // Loads and waits are written by hand as above; all vector-memory operations of the loop are direct-to-LDS loads, so
 // no register is ever the target of a load in flight.
 constexpr int TILE_WAVES = 4, TILE_CT = 8;
-constexpr int tile_stage_kib(int RT) { return PLANES * RT + TILE_CT; }
-constexpr int tile_ring(int RT) { return 160 / tile_stage_kib(RT); }
+constexpr int SLIM_CT = 4, SLIM_U = 2;   // one block of up to 128 rows: see below
+constexpr int tile_stage_kib(int RT, int CT, int U) { return (PLANES * RT + CT) * U; }
 // K is dealt out to the slices in units of 8 k-steps; a slice holds at least two units, so never fewer stages than the ring
 constexpr int TILE_UNIT = 8, TILE_MIN_STAGES = 16;
+// stages in the ring: what LDS holds, an even number, no more k-steps than the shortest slice has
+constexpr int tile_ring(int RT, int CT, int U) { return std::min(160 / tile_stage_kib(RT, CT, U) / 2 * 2, TILE_MIN_STAGES / U); }
+// wavefronts along the rows: quarters of 2 x 2 where the row tiles are even, else four column quarters of all rows
+constexpr int tile_wave_rows(int RT) { return RT % 2 == 0 ? 2 : 1; }
 
-template <int RT, int EPI>
+// RT, CT: row and column tiles of the workgroup; U: k-steps per stage
+template <int RT, int CT, int U, int EPI>
 __global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf16_t* __restrict__ Xp, size_t x_plane,
                                                                        const bf16_t* __restrict__ Wp, int NT, int KS, int n_col,
                                                                        int n_split, int n_zb, int T, int T_pad, int N,
                                                                        float* __restrict__ out, bf16_t* __restrict__ out_act,
                                                                        size_t act_plane, int F_act) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int HR = RT / 2, HC = TILE_CT / 2;               // row and column tiles of a wavefront's quarter
-    constexpr int XT = PLANES * RT, ST = XT + TILE_CT;         // 1 KiB operand tiles per stage: activations, then weights
-    constexpr int NB = tile_ring(RT);                          // stages in the ring = stages in flight
-    constexpr int XL = XT / TILE_WAVES, WL = TILE_CT / TILE_WAVES, PER = XL + WL;   // loads per wavefront and stage
-    static_assert(RT % 2 == 0 && XT % TILE_WAVES == 0 && TILE_CT % TILE_WAVES == 0, "tiles do not divide among the wavefronts");
-    static_assert(NB % 2 == 0 && TILE_UNIT % 2 == 0 && NB <= TILE_MIN_STAGES, "the trips of the stage loop are written for an even ring");
+    constexpr int WR = tile_wave_rows(RT), WC = TILE_WAVES / WR;   // wavefronts along rows and columns
+    constexpr int HR = RT / WR, HC = CT / WC;                  // row and column tiles of a wavefront's quarter
+    constexpr int XT = PLANES * RT * U, ST = XT + CT * U;      // 1 KiB operand tiles per stage: activations [k-step][plane][row tile], then weights [k-step][column tile]
+    constexpr int NB = tile_ring(RT, CT, U);                   // stages in the ring = stages in flight
+    constexpr int XL = XT / TILE_WAVES, WL = CT * U / TILE_WAVES, PER = XL + WL;   // loads per wavefront and stage
+    static_assert(RT % WR == 0 && CT % WC == 0 && XT % TILE_WAVES == 0 && CT * U % TILE_WAVES == 0, "tiles do not divide among the wavefronts");
+    static_assert(NB % 2 == 0 && TILE_UNIT % (2 * U) == 0 && NB * U <= TILE_MIN_STAGES, "the trips of the stage loop are written for an even ring");
     static_assert((NB - 1) * PER < 64, "too many loads in flight for the counter");
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wv >> 1, wc = wv & 1;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wv / WC, wc = wv % WC;
     // workgroup -> (column block, K slice, row block), as in gemm_bf16_kernel
     int bx, by, bz;
     {
@@ -509,8 +524,8 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf1
     }
     const int units = KS / TILE_UNIT, ubase = units / n_split, urem = units - ubase * n_split;
     const int ks_begin = (by * ubase + min(by, urem)) * TILE_UNIT;
-    const int n_stage = (ubase + (by < urem ? 1 : 0)) * TILE_UNIT;   // even, at least TILE_MIN_STAGES (the host sees to it)
-    const int mt_base = bz * RT, nt_base = bx * TILE_CT;
+    const int n_stage = (ubase + (by < urem ? 1 : 0)) * (TILE_UNIT / U);   // even, at least the ring's length (the host sees to it)
+    const int mt_base = bz * RT, nt_base = bx * CT;
 
     // ---- sources of this wavefront's loads: a uniform base per tile, advanced stage by stage, and a lane offset
     const int row_lim = (T + 7) & ~7;
@@ -519,20 +534,20 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf1
     const char* wsrc[WL];
 #pragma unroll
     for (int j = 0; j < XL; j++) {
-        const int i = j * TILE_WAVES + wv, pl = i / RT, b = i - pl * RT;
+        const int i = j * TILE_WAVES + wv, u = i / (PLANES * RT), pl = (i / RT) % PLANES, b = i % RT;
         const int mt = min(mt_base + b, T_pad / 32 - 1);   // a tile past the last one re-reads it; its results are not stored
         // lanes past the last token re-read the tile's first line (see gemm_bf16_kernel)
         const int src_lane = mt * 32 + (lane & 31) < row_lim ? lane : (lane & 32) + (lane & 7);
-        xsrc[j] = reinterpret_cast<const char*>(Xp + pl * x_plane + ((size_t)mt * KS + ks_begin) * 512);
+        xsrc[j] = reinterpret_cast<const char*>(Xp + pl * x_plane + ((size_t)mt * KS + ks_begin + u) * 512);
         xoff[j] = src_lane * 16;
     }
 #pragma unroll
     for (int j = 0; j < WL; j++) {
-        const int nt = min(nt_base + j * TILE_WAVES + wv, NT - 1);
-        wsrc[j] = reinterpret_cast<const char*>(Wp + ((size_t)ks_begin * NT + nt) * 512);
+        const int i = j * TILE_WAVES + wv, nt = min(nt_base + i % CT, NT - 1);
+        wsrc[j] = reinterpret_cast<const char*>(Wp + ((size_t)(ks_begin + i / CT) * NT + nt) * 512);
     }
     const unsigned woff = lane * 16;
-    const size_t wstep = (size_t)NT * 1024;
+    const size_t wstep = (size_t)NT * (1024 * U);
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem + wv * 1024;
     // load number j of the next stage in order, into ring slot `buf`
     auto issue_one = [&](int buf, int j) {
@@ -540,7 +555,7 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf1
         if (j < XL) {
             const unsigned dst = __builtin_amdgcn_readfirstlane(slot + j * (TILE_WAVES * 1024));
             asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(xoff[j < XL ? j : 0]), "s"(xsrc[j < XL ? j : 0]), "s"(dst) : "memory");
-            xsrc[j < XL ? j : 0] += 1024;
+            xsrc[j < XL ? j : 0] += 1024 * U;
         } else {
             const int a = j < XL ? 0 : j - XL;
             const unsigned dst = __builtin_amdgcn_readfirstlane(slot + (XT + a * TILE_WAVES) * 1024);
@@ -558,22 +573,24 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf1
             for (int e = 0; e < 16; e++) acc[a][b][e] = 0.f;
 
     struct frags {
-        bf16x8_t x[PLANES][HR], w[HC];
+        bf16x8_t x[U][PLANES][HR], w[U][HC];
     };
-    constexpr int NR = PLANES * HR + HC, NM = PLANES * HR * HC;   // LDS reads and MFMAs per stage
+    constexpr int RS = PLANES * HR + HC, MS = PLANES * HR * HC;   // LDS reads and MFMAs per k-step ...
+    constexpr int NR = RS * U, NM = MS * U;                       // ... and per stage
     const unsigned char* rd = smem + lane * 16;
-    auto read_one = [&](frags& f, int buf, int r) {   // weights first, then the hi plane, then the lo plane
+    auto read_one = [&](frags& f, int buf, int rr) {   // per k-step weights first, then the hi plane, then the lo plane
         const unsigned char* p = rd + (unsigned)buf * (ST * 1024);
+        const int u = rr / RS, r = rr - u * RS;
         if (r < HC)
-            f.w[r < HC ? r : 0] = *reinterpret_cast<const bf16x8_t*>(p + (XT + wc * HC + r) * 1024);
+            f.w[u][r < HC ? r : 0] = *reinterpret_cast<const bf16x8_t*>(p + (XT + u * CT + wc * HC + r) * 1024);
         else {
             const int e = r < HC ? 0 : r - HC, pl = e / HR, b = e - pl * HR;
-            f.x[pl][b] = *reinterpret_cast<const bf16x8_t*>(p + (pl * RT + wr * HR + b) * 1024);
+            f.x[u][pl][b] = *reinterpret_cast<const bf16x8_t*>(p + ((u * PLANES + pl) * RT + wr * HR + b) * 1024);
         }
     };
-    auto mfma_one = [&](const frags& f, int i) {   // all tiles with the hi plane, then all with the lo plane
-        const int pl = i / (HR * HC), e = i - pl * (HR * HC), b = e / HC, a = e - b * HC;
-        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[a], f.x[pl][b], acc[a][b], 0, 0, 0);
+    auto mfma_one = [&](const frags& f, int ii) {   // per k-step all tiles with the hi plane, then all with the lo plane
+        const int u = ii / MS, i = ii - u * MS, pl = i / (HR * HC), e = i - pl * (HR * HC), b = e / HC, a = e - b * HC;
+        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[u][a], f.x[u][pl][b], acc[a][b], 0, 0, 0);
     };
     // Stage s with its operands in `cur`: the operands of stage s+1 are read into `nxt`, and slot s % NB -- whose last
     // reads, those of stage s, every wavefront has back when it reaches the barrier -- is refilled with stage s+NB.
@@ -587,15 +604,15 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf1
             asm volatile("" ::: "memory");
         }
         __builtin_amdgcn_sched_barrier(0);
-        int r = 0;
+        constexpr int SPREAD = NM - 6 > NM / 2 ? NM - 6 : NM / 2;
+        static_assert(PER <= NM, "one load per slot");
 #pragma unroll
         for (int i = 0; i < NM; i++) {
             mfma_one(cur, i);
             if (LOAD && i < PER) issue_one(buf, i);
-            if (MORE && r < NR && i >= r * (NM - 6) / NR) {
-                read_one(nxt, next_buf, r);
-                r++;
-            }
+#pragma unroll
+            for (int q = 0; q < NR; q++)   // the reads are spread over the slots up to the last few
+                if (MORE && q * SPREAD / NR == i) read_one(nxt, next_buf, q);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -756,10 +773,10 @@ int launch_one(const gemm_args& a) {
     return SLED_OK;
 }
 
-template <int RT, int EPI>
+template <int RT, int CT, int U, int EPI>
 int launch_tile_one(const gemm_args& a) {
     static bool allowed = false;
-    auto kern = gemm_tile_kernel<RT, EPI>;
+    auto kern = gemm_tile_kernel<RT, CT, U, EPI>;
     if (!allowed) {
         SLED_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds));
         allowed = true;
@@ -770,12 +787,12 @@ int launch_tile_one(const gemm_args& a) {
     return SLED_OK;
 }
 
-template <int RT>
+template <int RT, int CT = TILE_CT, int U = 1>
 int launch_tile(int epi, const gemm_args& a) {
     switch (epi) {
-        case SLED_EPI_PARTIAL: return launch_tile_one<RT, SLED_EPI_PARTIAL>(a);
-        case SLED_EPI_SWIGLU: return launch_tile_one<RT, SLED_EPI_SWIGLU>(a);
-        default: return launch_tile_one<RT, SLED_EPI_STORE>(a);
+        case SLED_EPI_PARTIAL: return launch_tile_one<RT, CT, U, SLED_EPI_PARTIAL>(a);
+        case SLED_EPI_SWIGLU: return launch_tile_one<RT, CT, U, SLED_EPI_SWIGLU>(a);
+        default: return launch_tile_one<RT, CT, U, SLED_EPI_STORE>(a);
     }
 }
 
@@ -877,7 +894,7 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
         if (N % 32 || K % 16 || T_pad % 32 || plan.split < 1 || KS % (NARROW_KG * NBUF) || plan.split > KS / (NARROW_KG * NBUF))
             SLED_FAIL(SLED_EINVAL, "gemm: unsupported shape N=%d K=%d T_pad=%d split=%d", N, K, T_pad, plan.split);
         const int mt_total = T_pad / 32;
-        // up to 128 rows (4 tiles): narrow shape with exactly these tiles; more: the tile kernel at the planned height
+        // up to 128 rows (4 tiles): slim tile (16-bit weights) or narrow shape with exactly these tiles; more: the tile kernel at the planned height
         // (bf16 weights) or blocks of four tiles in the wide shape (8- and 4-bit weights); the last block may reach past the end
         // (a batch-invariant model keeps the narrow shape at every size: the two shapes add the k-steps up in
         // different groupings, so a row's sums would depend on whether its batch has more than 128 rows)
@@ -919,7 +936,7 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
             a.n_col = (NT + TILE_CT - 1) / TILE_CT;
             a.n_zb = (mt_total + RT - 1) / RT;
             a.grid = dim3((a.n_col * a.n_split + 7) / 8 * 8 * a.n_zb, 1, 1);
-            a.lds = (size_t)tile_ring(RT) * tile_stage_kib(RT) * 1024;
+            a.lds = (size_t)tile_ring(RT, TILE_CT, 1) * tile_stage_kib(RT, TILE_CT, 1) * 1024;
             switch (RT) {
                 case 4: return launch_tile<4>(epilogue, a);
                 case 6: return launch_tile<6>(epilogue, a);
@@ -928,6 +945,18 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
         }
         if (wide)
             return m->wbits == 8 ? launch_epi_wb<4, WIDE_KG, WIDE_CG, 8>(epilogue, a) : launch_epi_wb<4, WIDE_KG, WIDE_CG, 4>(epilogue, a);
+        // one block of rows, 16-bit weights: the slim tile kernel, wherever the slices are long enough for its ring
+        if (!wide && !broad && m->wbits == 16 && !m->batch_invariant && KS / TILE_UNIT >= plan.split * (TILE_MIN_STAGES / TILE_UNIT)) {
+            a.n_col = (NT + SLIM_CT - 1) / SLIM_CT;
+            a.grid = dim3((a.n_col * a.n_split + 7) / 8 * 8, 1, 1);
+            a.lds = (size_t)tile_ring(MT, SLIM_CT, SLIM_U) * tile_stage_kib(MT, SLIM_CT, SLIM_U) * 1024;
+            switch (MT) {
+                case 1: return launch_tile<1, SLIM_CT, SLIM_U>(epilogue, a);
+                case 2: return launch_tile<2, SLIM_CT, SLIM_U>(epilogue, a);
+                case 3: return launch_tile<3, SLIM_CT, SLIM_U>(epilogue, a);
+                default: return launch_tile<4, SLIM_CT, SLIM_U>(epilogue, a);
+            }
+        }
         if (broad) return launch_epi<4, BROAD_KG, BROAD_CG>(epilogue, a);
         switch (MT) {
             case 1: return launch_epi<1, NARROW_KG, NARROW_CG>(epilogue, a);

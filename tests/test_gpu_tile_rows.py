@@ -1,5 +1,5 @@
-"""Verification steps of more than 128 rows against the oracle, at the row counts where the projections' workgroups change
-height (4, 6 or 8 tiles of 32 rows), at whole and ragged last tiles, and with a vocabulary whose last column block is
+"""Verification steps against the oracle at the row counts where the projections' workgroups change height (1 to 4 tiles of
+32 rows in one block; 4, 6 or 8 beyond 128 rows), at whole and ragged last tiles, and with a vocabulary whose last column block is
 partial.  One layer of small width but wide FFN and vocabulary, so that all heights occur."""
 import numpy as np
 import pytest
@@ -17,8 +17,8 @@ pytestmark = pytest.mark.gpu
 TOL = 5e-3
 
 
-@pytest.mark.parametrize("T", [129, 160, 161, 192, 227, 256, 257, 367, 385, 500])
-def test_rows_beyond_one_block(T):
+@pytest.mark.parametrize("T", [1, 31, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 227, 256, 257, 367, 385, 500])
+def test_rows_at_the_edges_of_tiles_and_blocks(T):
     shape = synth.scaled_shape(synth.SHAPES["tiny_bf16"], n_layers=1, d_model=256, n_q_heads=2, n_kv_heads=1, d_ffn=14336, vocab=57376)
     k = [8] * (T // 9) + ([T % 9 - 1] if T % 9 else [])
     ctx = [1 + 7 * i % 40 for i in range(len(k))]
