@@ -23,10 +23,9 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 # L2 fetch + write-back bytes per projection launch: a STORED counter figure, not read in this run (FETCH_SIZE and
 # WRITE_SIZE of rocprofv3 need runs of their own; each is scaled by what the counter reads for a 1 GiB copy;
-# profiles/verify_step_llama8b_b16_hbm_traffic.txt gives the commands and the table).  Taken with gemm_bf16_kernel as
-# it stands in csrc/gemm.hip (retaken after every change to that file's kernel code, last after K slices became
-# uneven: 149.9 MB each time); to be reset to None whenever that kernel changes.
-MEASURED_TRAFFIC = {"llama8b_b16": 149.9e6}
+# profiles/verify_step_llama8b_b16_hbm_traffic.txt gives the commands and the table of the kernel that ran these
+# projections before: 149.9 MB).  None since 16-bit projections run in gemm_tile_kernel, whose traffic has not been taken.
+MEASURED_TRAFFIC = {}
 TRAFFIC_NOTE = "stored rocprofv3 FETCH_SIZE+WRITE_SIZE figure for gemm_bf16_kernel (profiles/verify_step_llama8b_b16_hbm_traffic.txt), not measured in this run"
 CPU_SAMPLE_REQUESTS, CPU_SAMPLE_LAYERS = 16, 24   # the oracle's bounded sample (about 10-20 s of CPU work)
 
@@ -163,7 +162,7 @@ def main():
     proj_launches = n[sled.PROF_PROJ] // psteps
     achieved = weight_bytes / (proj_ms * 1e-3) / 1e9
     roofline = {
-        "bound": "hbm", "kernel": "gemm_bf16_kernel (projection GEMMs, weight stream)",
+        "bound": "hbm", "kernel": "gemm_tile_kernel, gemm_bf16_kernel (projection GEMMs, weight stream)",
         "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
         "traffic": (traffic := None if (w8 or args.batch_invariant) else MEASURED_TRAFFIC.get(args.workload)),
         "traffic_source": TRAFFIC_NOTE if traffic is not None else None,

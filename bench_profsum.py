@@ -36,11 +36,11 @@ def stats(d: str) -> None:
             continue
         print(f"{short(r['Name']):70s} {int(r['Calls']):7d} {t / 1e6:10.3f} {float(r['AverageNs']) / 1e3:9.2f} "
               f"{int(r['MinNs']) / 1e3:9.2f} {int(r['MaxNs']) / 1e3:9.2f} {100.0 * t / total:6.2f}")
-        if "gemm_bf16_kernel" in r["Name"]:
+        if "gemm_bf16_kernel" in r["Name"] or "gemm_tile_kernel" in r["Name"]:
             gemm_calls += int(r["Calls"])
             gemm_ns += t
     if gemm_calls:
-        print(f"\nall gemm_bf16_kernel instances: {gemm_calls} launches, {gemm_ns / 1e6:.3f} ms, "
+        print(f"\nall gemm_bf16_kernel and gemm_tile_kernel instances: {gemm_calls} launches, {gemm_ns / 1e6:.3f} ms, "
               f"average {gemm_ns / gemm_calls / 1e3:.2f} us per launch")
 
 
