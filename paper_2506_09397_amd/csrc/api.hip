@@ -922,12 +922,10 @@ int run_forward(sled_model* m, sled_kvpool* p, const std::vector<step_entry>& en
     const sled_gemm_plan g_qkv = sled_gemm_plan_rows(m, sled_gemm_make_plan(m, m->n_qkv, d, false), m->n_qkv, d, T_pad),
                          g_o = sled_gemm_plan_rows(m, sled_gemm_make_plan(m, d, HD, false), d, HD, T_pad),
                          g_dn = sled_gemm_plan_rows(m, sled_gemm_make_plan(m, d, F, false), d, F, T_pad),
-                         g_lm = sled_gemm_plan_rows(m, sled_gemm_make_plan(m, s.vocab, d, true), s.vocab, d, logits_all ? T_pad : 32);
+                         g_lm = sled_gemm_make_plan(m, s.vocab, d, true);
     // gate/up applies SwiGLU in its epilogue when it runs unsplit; otherwise (and for fp32 models) a row
     // kernel reduces the K slices and applies it
-    sled_gemm_plan g_gu = sled_gemm_make_plan(m, 2 * F, d, false);
-    g_gu.cap = g_gu.split;   // its slices have no room beyond the model's plan
-    g_gu = sled_gemm_plan_rows(m, g_gu, 2 * F, d, T_pad);
+    const sled_gemm_plan g_gu = sled_gemm_make_plan(m, 2 * F, d, false);
     const bool gu_fused = bf && g_gu.split == 1;
     // The attention kernel takes the QKV projection's partial sums itself (sum over K slices, rotary, K/V write) when
     // every block is a request of its own at offset 0, i.e. in a verification step.  The blocks of a prompt slice read

@@ -474,7 +474,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(const bf16_t* __r
 // fits into their issue gaps: operands of the next stage are read into a second register set between them.
 //   - Against the wide shape above (2 wavefronts per SIMD, weights straight to registers), which ran these cases before,
 //     a k-step moves 24 KiB into the CU instead of 32 per 128 MFMAs (RT = 8), reads 48 KiB of LDS instead of 64, and has
-//     no sums to exchange at the end; and its height can follow the batch (plan_for_rows).  Gate/up of 384 rows x 4096
+//     no sums to exchange at the end; and its height can follow the batch (tile_height).  Gate/up of 384 rows x 4096
 //     x 28672: 179 -> 137 us; of 256 rows x 8192 x 57344: 392 -> 346 us = 1.39 PFLOP/s executed (both planes), where a
 //     large library product on the same card reaches 1.41: power, not the schedule, is what is left.
 //   - One block of rows (up to 128) runs in a slim tile, RT x 32 rows by 128 columns with two k-steps per stage: as many
@@ -820,15 +820,15 @@ int launch_epi(int epi, const gemm_args& a) {
 // chip wants at least one per CU) but more partial sums to reduce.  Each slice must hold a multiple
 // of 4 stages of 64 k.
 static sled_gemm_plan plan_one_block(int N, int K, bool needs_full_k);
-static sled_gemm_plan plan_for_rows(sled_gemm_plan base, int N, int K, int T_pad, int wbits);
+static sled_gemm_plan plan_for_rows(sled_gemm_plan base, int N, int K, int T_pad);
 
 sled_gemm_plan sled_gemm_make_plan(const sled_model* m, int N, int K, bool needs_full_k) {
-    if (m->s.dtype != SLED_BF16) return sled_gemm_plan{1, 1, 0};
+    if (m->s.dtype != SLED_BF16) return sled_gemm_plan{1, 1};
     return plan_one_block(N, K, needs_full_k);
 }
 
 static sled_gemm_plan plan_one_block(int N, int K, bool needs_full_k) {
-    sled_gemm_plan p{1, 1, 0};
+    sled_gemm_plan p{1, 1};
     auto legal = [&](int sp) { return sp >= 1 && (K / 16) % (sp * NARROW_KG * NBUF) == 0; };
     const int n_wg = (N + NARROW_COLS - 1) / NARROW_COLS;
     if (!needs_full_k)
@@ -841,37 +841,28 @@ static sled_gemm_plan plan_one_block(int N, int K, bool needs_full_k) {
 // With more than one block of 128 rows the workgroups of a projection are column blocks x row blocks x K slices, and what
 // counts is how many rounds of 256 they make: 288 workgroups take as long as 512.  Fewer K slices also mean fewer
 // partial sums to write and to read back.  Estimated time of a launch, in microseconds: rounds x (fixed part +
-// k-steps per workgroup x time per k-step) + bytes of partial sums written and read / rate; minimised over the K slices
-// and, for the tile kernel, its row tiles.  Times per k-step measured on full rounds: 0.35-0.39 us at 4 row tiles
-// (as the wide shape), 0.51-0.54 at 6, 0.66-0.68 at 8.  So equal rows cost about the same at each height, and what the
-// choice of height gives is better filled rounds: 384 rows x 28672 columns are 336 workgroups in two rounds at 4 row
-// tiles (178 us) and 224 in one round at 6 (137 us); 256 x 57344 take 383 us at 4, 346 us at 8.
+// stages of 32 k per workgroup x time per stage) + bytes of partial sums written and read / rate.  The slices are those of
+// blocks of 128 rows by 256 columns for weights of any width: how many there are is part of how a row's sums are rounded, and
+// the tile kernel takes them as they are, whatever its height.
 sled_gemm_plan sled_gemm_plan_rows(const sled_model* m, sled_gemm_plan base, int N, int K, int T_pad) {
     if (m->s.dtype != SLED_BF16 || m->batch_invariant) return base;
-    return plan_for_rows(base, N, K, T_pad, m->wbits);
+    return plan_for_rows(base, N, K, T_pad);
 }
 
-static sled_gemm_plan plan_for_rows(sled_gemm_plan base, int N, int K, int T_pad, int wbits) {
-    if (T_pad / 32 <= 4) return base;
-    constexpr double FIXED_US = 9.0, PARTIAL_BYTES_PER_US = 4.0e6;
-    constexpr int HEIGHTS[3] = {4, 6, 8};
-    constexpr double STEP_US[3] = {0.40, 0.59, 0.74};
-    const int n_col = (N / 32 + 7) / 8;                      // of 256 columns, in either kernel
-    const int units = K / 16 / TILE_UNIT;                    // trips of the stage loop in all of K
+static sled_gemm_plan plan_for_rows(sled_gemm_plan base, int N, int K, int T_pad) {
+    if (base.split <= 1 || T_pad / 32 <= 4) return base;
+    constexpr double FIXED_US = 9.0, STAGE_US = 0.8, PARTIAL_BYTES_PER_US = 4.0e6;
+    const int n_col = (N / 32 + WIDE_CG * NW - 1) / (WIDE_CG * NW), zb = (T_pad / 32 + 3) / 4;
+    const int units = K / 16 / (WIDE_KG * NBUF);   // trips of the stage loop in all of K
     sled_gemm_plan best = base;
     double best_t = -1.0;
-    for (int h = 0; h < (wbits == 16 ? 3 : 1); h++) {
-        const int zb = (T_pad / 32 + HEIGHTS[h] - 1) / HEIGHTS[h];
-        for (int sp = 1; sp <= base.cap && sp * TILE_MIN_STAGES <= K / 16; sp++) {
-            const int64_t wgs = (int64_t)n_col * zb * sp;
-            const int steps = (units + sp - 1) / sp * TILE_UNIT;   // of the longest slice
-            const double partial = base.cap > 1 ? 2.0 * sp * (double)T_pad * N * 4.0 / PARTIAL_BYTES_PER_US : 0.0;
-            const double t = (double)((wgs + 255) / 256) * (FIXED_US + steps * STEP_US[h]) + partial;
-            if (best_t < 0 || t < best_t) {
-                best_t = t;
-                best.split = sp;
-                best.tile = wbits == 16 ? HEIGHTS[h] : 0;
-            }
+    for (int sp = 1; sp <= base.cap && sp <= units; sp++) {
+        const int64_t wgs = (int64_t)n_col * zb * sp;
+        const int stages = (units + sp - 1) / sp * NBUF;   // of the longest slice
+        const double t = (double)((wgs + 255) / 256) * (FIXED_US + stages * STAGE_US) + 2.0 * sp * (double)T_pad * N * 4.0 / PARTIAL_BYTES_PER_US;
+        if (best_t < 0 || t < best_t) {
+            best_t = t;
+            best.split = sp;
         }
     }
     return best;
@@ -881,9 +872,32 @@ extern "C" int sled_projection_slices(int n_out, int n_in, int T, int* slices /*
     if (!slices || !max_slices || n_out < 32 || n_in < 16 * NARROW_KG * NBUF || n_out % 32 || n_in % (16 * NARROW_KG * NBUF) || T < 1)
         SLED_FAIL(SLED_EINVAL, "sled_projection_slices: bad argument");
     const sled_gemm_plan base = plan_one_block(n_out, n_in, false);
-    *slices = plan_for_rows(base, n_out, n_in, (T + 31) / 32 * 32, 16).split;
+    *slices = plan_for_rows(base, n_out, n_in, (T + 31) / 32 * 32).split;
     *max_slices = base.cap;
     return SLED_OK;
+}
+
+// Row tiles per workgroup of the tile kernel beyond 128 rows, by the same estimate (without the partial sums, which do not depend on
+// it).  Times per k-step measured on full rounds: 0.35-0.39 us at 4 row tiles (as the wide shape), 0.51-0.54 at 6, 0.66-0.68 at
+// 8.  So equal rows cost about the same at each height, and what the choice gives is better filled rounds: 384 rows x 28672
+// columns are 336 workgroups in two rounds at 4 row tiles (178 us) and 224 in one round at 6 (137 us); 256 x 57344 take 383 us
+// at 4, 346 us at 8.
+static int tile_height(int N, int K, int T_pad, int split) {
+    constexpr double FIXED_US = 9.0;
+    constexpr int HEIGHTS[3] = {4, 6, 8};
+    constexpr double STEP_US[3] = {0.40, 0.59, 0.74};
+    const int n_col = (N / 32 + TILE_CT - 1) / TILE_CT, steps = (K / 16 / TILE_UNIT + split - 1) / split * TILE_UNIT;   // of the longest slice
+    int best = 0;
+    double best_t = -1.0;
+    for (int h = 0; h < 3; h++) {
+        const int64_t wgs = (int64_t)n_col * ((T_pad / 32 + HEIGHTS[h] - 1) / HEIGHTS[h]) * split;
+        const double t = (double)((wgs + 255) / 256) * (FIXED_US + steps * STEP_US[h]);
+        if (best_t < 0 || t < best_t) {
+            best_t = t;
+            best = HEIGHTS[h];
+        }
+    }
+    return best;
 }
 
 int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const void* W, const void* scale, int T, int T_pad,
@@ -894,7 +908,7 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
         if (N % 32 || K % 16 || T_pad % 32 || plan.split < 1 || KS % (NARROW_KG * NBUF) || plan.split > KS / (NARROW_KG * NBUF))
             SLED_FAIL(SLED_EINVAL, "gemm: unsupported shape N=%d K=%d T_pad=%d split=%d", N, K, T_pad, plan.split);
         const int mt_total = T_pad / 32;
-        // up to 128 rows (4 tiles): slim tile (16-bit weights) or narrow shape with exactly these tiles; more: the tile kernel at the planned height
+        // up to 128 rows (4 tiles): slim tile (16-bit weights) or narrow shape with exactly these tiles; more: the tile kernel at the height that suits
         // (bf16 weights) or blocks of four tiles in the wide shape (8- and 4-bit weights); the last block may reach past the end
         // (a batch-invariant model keeps the narrow shape at every size: the two shapes add the k-steps up in
         // different groupings, so a row's sums would depend on whether its batch has more than 128 rows)
@@ -904,8 +918,7 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
         // one block of four row tiles, no K slices, and column blocks of 512 that fill at least three quarters of the CUs
         const bool broad = !wide && MT == 4 && plan.split == 1 && !m->batch_invariant && (NT + BROAD_CG * NW - 1) / (BROAD_CG * NW) >= 192;
         const int KG = wide ? WIDE_KG : broad ? BROAD_KG : NARROW_KG, CG = wide ? WIDE_CG : broad ? BROAD_CG : NARROW_CG;
-        const int RT = wide ? plan.tile : 0;
-        if (wide && m->wbits == 16 && RT != 4 && RT != 6 && RT != 8) SLED_FAIL(SLED_EINVAL, "gemm: no tile height planned for %d rows", T_pad);
+        const int RT = wide && m->wbits == 16 ? tile_height(N, K, T_pad, plan.split) : 0;
         gemm_args a;
         a.n_col = (NT + CG * NW - 1) / (CG * NW);
         a.n_split = plan.split;

@@ -273,7 +273,6 @@ enum { SLED_EPI_PARTIAL = 0, SLED_EPI_SWIGLU = 1, SLED_EPI_STORE = 2 };
 struct sled_gemm_plan {
     int split;   // K slices
     int cap;     // the most K slices a step may choose instead (sizes the partial-sum buffer)
-    int tile;    // row tiles of 32 per workgroup of the tile kernel (steps of more than 128 rows, bf16 weights), else 0
 };
 sled_gemm_plan sled_gemm_make_plan(const sled_model* m, int N, int K, bool needs_full_k);
 // the plan for a step of T_pad rows: never more K slices than `base` (which sizes the workspace), fewer where several

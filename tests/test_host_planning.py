@@ -96,6 +96,9 @@ def test_projection_slices_of_the_benchmark_model():
     assert sled.sled_projection_slices(nqkv, d, 372)[0] == 3
     assert sled.sled_projection_slices(d, d, 372)[0] == 5
     assert sled.sled_projection_slices(d, F, 372)[0] == 5
+    # one plan for weights of every width, whatever the height of a workgroup: partial sums count against rounds of blocks of 128 rows
+    assert [sled.sled_projection_slices(d, K, 700)[0] for K in (d, F)] == [2, 5]
+    assert [sled.sled_projection_slices(N, K, 129)[0] for N, K in ((nqkv, d), (d, d), (d, F))] == [5, 8, 8]
     for N, K in ((nqkv, d), (d, d), (d, F), (10240, 8192), (8192, 28672)):
         for T in (1, 33, 128, 129, 225, 372, 512, 1008, 2016, 4096):
             s, cap = sled.sled_projection_slices(N, K, T)
