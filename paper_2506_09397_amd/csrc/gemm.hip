@@ -468,19 +468,24 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(const bf16_t* __r
 // ------------------------------------------------------------------------------------------ tile kernel
 // 16-bit weights.  With more than 128 rows the contraction is bound by the matrix pipes, so the workgroup is shaped for them.
 // Four wavefronts, ONE per SIMD (512 registers each), own a tile of RT x 32 rows by 256 columns as 2 x 2 quarters; a
-// quarter is RT/2 x 4 accumulator tiles.  Both operands go through a ring of LDS stages of one k-step (16 k), filled
-// by direct-to-LDS loads that keep as many stages in flight as the 160 KiB hold.  Per stage and wavefront (RT = 8):
-// 32 MFMAs (1024 clocks of the matrix pipe), 12 ds_read_b128, 6 loads and one barrier, so everything but the MFMAs
+// quarter is RT/2 x 4 result tiles.  Both operands go through a ring of LDS stages of one k-step (16 k), filled
+// by direct-to-LDS loads that keep as many stages in flight as the 160 KiB hold.  Per stage and wavefront (RT = 6):
+// 24 MFMAs (768 clocks of the matrix pipe), 10 ds_read_b128, 5 loads and one barrier, so everything but the MFMAs
 // fits into their issue gaps: operands of the next stage are read into a second register set between them.
+//   - The k-steps of a slice go to 2 U sums in turn (U k-steps per stage: two sums beyond 128 rows, four in the slim tile),
+//     which are added in ascending order at the end: the very sums that the k-groups of the wide and the narrow shape keep, so
+//     a sum's rounding grows with a half or a quarter of the slice and a result does not depend on which kernel made it.
+//     Two sums are what limits the height: 24 result tiles x 16 registers at RT = 6.  (220 rows x 8192 x 57344 took 387 us with
+//     one sum at RT = 8, 408 with two at RT = 4, and 418 in the wide shape; but one sum has about 1.4 times the round-off.)
 //   - Against the wide shape above (2 wavefronts per SIMD, weights straight to registers), which ran these cases before,
-//     a k-step moves 24 KiB into the CU instead of 32 per 128 MFMAs (RT = 8), reads 48 KiB of LDS instead of 64, and has
-//     no sums to exchange at the end; and its height can follow the batch (tile_height).  Gate/up of 384 rows x 4096
-//     x 28672: 179 -> 137 us; of 256 rows x 8192 x 57344: 392 -> 346 us = 1.39 PFLOP/s executed (both planes), where a
-//     large library product on the same card reaches 1.41: power, not the schedule, is what is left.
+//     a k-step moves 20 KiB into the CU instead of 24 per 96 MFMAs (RT = 6), reads 40 KiB of LDS instead of 48, and has
+//     no sums to exchange at the end; and its height can follow the batch (tile_height).  Gate/up of 372 rows x 4096
+//     x 28672: 185 -> 138 us; of 700 rows: 290 -> 270 us = 1.22 PFLOP/s executed (both planes), where a large library
+//     product on the same card reaches 1.41.
 //   - One block of rows (up to 128) runs in a slim tile, RT x 32 rows by 128 columns with two k-steps per stage: as many
 //     workgroups as the narrow shape above and the same K slices, but no k-group sums to exchange at the end, a cost that a
-//     launch of 15 to 60 us feels.  101 rows: gate/up 59.8 -> 57.0, QKV 22.1 -> 19.4, O 16.9 -> 14.2 us, the 8B step 5.97 ->
-//     5.66 ms; one row: QKV 11.8 -> 11.0 us, the step 3.75 -> 3.68 ms.  With an odd number of row tiles the four
+//     launch of 15 to 60 us feels.  101 rows: gate/up 62.5 -> 61.3, QKV 22.7 -> 20.1 us; 8 layers and the head of the 8B
+//     shape 1.54-1.62 -> 1.45-1.55 ms from box to box, at 20 rows 1.08 -> 1.05, at one 1.03 -> 1.02.  With an odd number of row tiles the four
 //     wavefronts take a column tile each instead of quarters.
 // Loads and waits are written by hand as above; all vector-memory operations of the loop are direct-to-LDS loads, so
 // no register is ever the target of a load in flight.
@@ -506,6 +511,7 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf1
     constexpr int HR = RT / WR, HC = CT / WC;                  // row and column tiles of a wavefront's quarter
     constexpr int XT = PLANES * RT * U, ST = XT + CT * U;      // 1 KiB operand tiles per stage: activations [k-step][plane][row tile], then weights [k-step][column tile]
     constexpr int NB = tile_ring(RT, CT, U);                   // stages in the ring = stages in flight
+    constexpr int G = 2 * U;                                   // sums: k-step number s of the slice goes to number s % G
     constexpr int XL = XT / TILE_WAVES, WL = CT * U / TILE_WAVES, PER = XL + WL;   // loads per wavefront and stage
     static_assert(RT % WR == 0 && CT % WC == 0 && XT % TILE_WAVES == 0 && CT * U % TILE_WAVES == 0, "tiles do not divide among the wavefronts");
     static_assert(NB % 2 == 0 && TILE_UNIT % (2 * U) == 0 && NB * U <= TILE_MIN_STAGES, "the trips of the stage loop are written for an even ring");
@@ -564,13 +570,13 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf1
         }
     };
 
-    float16_t acc[HC][HR];
-#pragma unroll
-    for (int a = 0; a < HC; a++)
-#pragma unroll
-        for (int b = 0; b < HR; b++)
-#pragma unroll
-            for (int e = 0; e < 16; e++) acc[a][b][e] = 0.f;
+    // The compiler gives all results of its MFMAs one kind of register, of which there are 256: 16 tiles.  Where there are more, the MFMAs
+    // are written here with the first 16 tiles in accumulation registers and the rest in ordinary ones, tied to their places.  The
+    // compiler does not know what such an instruction needs: nothing but another MFMA may touch a tile between the zeros below and
+    // the wait behind the last stage (compiled code is checked for it).
+    constexpr bool MORE_THAN_16 = G * HC * HR > 16;
+    auto in_agpr = [](int g, int a, int b) { return g * HC * HR + a * HR + b < 16; };
+    float16_t acc[G][HC][HR];
 
     struct frags {
         bf16x8_t x[U][PLANES][HR], w[U][HC];
@@ -588,15 +594,34 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf1
             f.x[u][pl][b] = *reinterpret_cast<const bf16x8_t*>(p + ((u * PLANES + pl) * RT + wr * HR + b) * 1024);
         }
     };
-    auto mfma_one = [&](const frags& f, int ii) {   // per k-step all tiles with the hi plane, then all with the lo plane
-        const int u = ii / MS, i = ii - u * MS, pl = i / (HR * HC), e = i - pl * (HR * HC), b = e / HC, a = e - b * HC;
-        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[u][a], f.x[u][pl][b], acc[a][b], 0, 0, 0);
+    auto mfma_one = [&](const frags& f, int odd, int ii) {   // per k-step all tiles with the hi plane, then all with the lo plane
+        const int u = ii / MS, i = ii - u * MS, pl = i / (HR * HC), e = i - pl * (HR * HC), b = e / HC, a = e - b * HC, g = odd * U + u;
+        float16_t& c = acc[g][a][b];
+        if (!MORE_THAN_16)
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[u][a], f.x[u][pl][b], c, 0, 0, 0);
+        else if (in_agpr(g, a, b))
+            asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(f.w[u][a]), "v"(f.x[u][pl][b]));
+        else
+            asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(f.w[u][a]), "v"(f.x[u][pl][b]));
+    };
+    auto pin_sums = [&]() {
+#pragma unroll
+        for (int g = 0; g < G; g++)
+#pragma unroll
+            for (int a = 0; a < HC; a++)
+#pragma unroll
+                for (int b = 0; b < HR; b++) {
+                    if (in_agpr(g, a, b))
+                        asm volatile("" : "+a"(acc[g][a][b]));
+                    else
+                        asm volatile("" : "+v"(acc[g][a][b]));
+                }
     };
     // Stage s with its operands in `cur`: the operands of stage s+1 are read into `nxt`, and slot s % NB -- whose last
     // reads, those of stage s, every wavefront has back when it reaches the barrier -- is refilled with stage s+NB.
-    // The wait before the barrier is for this wavefront's share of stage s+1; AFTER loads have been issued since.
-    auto stage = [&](auto after_c, auto load_c, auto more_c, const frags& cur, frags& nxt, int buf, int next_buf) {
-        constexpr int AFTER = decltype(after_c)::value;
+    // The wait before the barrier is for this wavefront's share of stage s+1; AFTER loads have been issued since.  ODD: s is odd.
+    auto stage = [&](auto odd_c, auto after_c, auto load_c, auto more_c, const frags& cur, frags& nxt, int buf, int next_buf) {
+        constexpr int ODD = decltype(odd_c)::value, AFTER = decltype(after_c)::value;
         constexpr bool LOAD = decltype(load_c)::value != 0, MORE = decltype(more_c)::value != 0;
         if (MORE) {
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(AFTER) : "memory");
@@ -608,7 +633,7 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf1
         static_assert(PER <= NM, "one load per slot");
 #pragma unroll
         for (int i = 0; i < NM; i++) {
-            mfma_one(cur, i);
+            mfma_one(cur, ODD, i);
             if (LOAD && i < PER) issue_one(buf, i);
 #pragma unroll
             for (int q = 0; q < NR; q++)   // the reads are spread over the slots up to the last few
@@ -624,6 +649,16 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf1
     for (int s2 = 0; s2 < NB; s2++)
 #pragma unroll
         for (int j = 0; j < PER; j++) issue_one(s2, j);
+    // zeros while the first loads are under way
+#pragma unroll
+    for (int g = 0; g < G; g++)
+#pragma unroll
+        for (int a = 0; a < HC; a++)
+#pragma unroll
+            for (int b = 0; b < HR; b++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) acc[g][a][b][e] = 0.f;
+    pin_sums();
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NB - 1) * PER) : "memory");   // this wavefront's share of stage 0
     __builtin_amdgcn_s_barrier();                                           // everybody's
     asm volatile("" ::: "memory");
@@ -632,25 +667,38 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf1
     for (int r = 0; r < NR; r++) read_one(f0, 0, r);
     int buf = 0;
     auto next = [&](int b2) { return b2 == NB - 1 ? 0 : b2 + 1; };
-    for (int s = 0; s + NB < n_stage; s += 2) {   // n_stage and NB are even: both stages of a trip have one NB further on
-        stage(integral_constant<int, (NB - 2) * PER>{}, yes{}, yes{}, f0, f1, buf, next(buf));
+    auto trip = [&]() {   // n_stage and NB are even: both stages of a trip have one NB further on
+        stage(no{}, integral_constant<int, (NB - 2) * PER>{}, yes{}, yes{}, f0, f1, buf, next(buf));
         buf = next(buf);
-        stage(integral_constant<int, (NB - 2) * PER>{}, yes{}, yes{}, f1, f0, buf, next(buf));
+        stage(yes{}, integral_constant<int, (NB - 2) * PER>{}, yes{}, yes{}, f1, f0, buf, next(buf));
         buf = next(buf);
+    };
+    int s = 0;
+    if constexpr (NB * U < TILE_MIN_STAGES) {   // there is a trip in every slice: as a do loop it leaves the sums where they are
+        do {
+            trip();
+            s += 2;
+        } while (s + NB < n_stage);
+    } else {
+        for (; s + NB < n_stage; s += 2) trip();
     }
     // the last NB stages fetch nothing: one stage fewer in flight behind the awaited one each time
     auto last = [&](auto self, auto left_c) {   // left: stages still to do
         constexpr int LEFT = decltype(left_c)::value;
         if constexpr (LEFT > 0) {
             constexpr int AFTER = LEFT >= 2 ? (LEFT - 2) * PER : 0;
-            if constexpr (LEFT % 2 == 0) stage(integral_constant<int, AFTER>{}, no{}, yes{}, f0, f1, buf, next(buf));
-            else if constexpr (LEFT > 1) stage(integral_constant<int, AFTER>{}, no{}, yes{}, f1, f0, buf, next(buf));
-            else stage(integral_constant<int, 0>{}, no{}, no{}, f1, f0, buf, buf);
+            if constexpr (LEFT % 2 == 0) stage(no{}, integral_constant<int, AFTER>{}, no{}, yes{}, f0, f1, buf, next(buf));
+            else if constexpr (LEFT > 1) stage(yes{}, integral_constant<int, AFTER>{}, no{}, yes{}, f1, f0, buf, next(buf));
+            else stage(yes{}, integral_constant<int, 0>{}, no{}, no{}, f1, f0, buf, buf);
             buf = next(buf);
             self(self, integral_constant<int, LEFT - 1>{});
         }
     };
     last(last, integral_constant<int, NB>{});
+    if (MORE_THAN_16) {
+        asm volatile("s_nop 15\n\ts_nop 7");   // the last MFMA's result (11 wait states for one of eight passes; twice that)
+        pin_sums();
+    }
 
     // epilogue: lane holds row (token) mt*32 + lane%32 and, in registers 4q .. 4q+3, the columns nt*32 + 8q + (lane/32)*4 + 0..3
 #pragma unroll
@@ -662,9 +710,13 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf1
             const int tok = (mt_base + wr * HR + b) * 32 + (lane & 31);
             if (tok >= T) continue;   // padding rows are never read, or only by their own padding rows
 #pragma unroll
-            for (int q = 0; q < 4; q++)
-                store_cols<EPI>(float4_t{acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]}, tok,
-                                nt * 32 + q * 8 + (lane >> 5) * 4, by, T_pad, N, out, out_act, act_plane, F_act);
+            for (int q = 0; q < 4; q++) {
+                auto quad = [&](int g) { return float4_t{acc[g][a][b][4 * q], acc[g][a][b][4 * q + 1], acc[g][a][b][4 * q + 2], acc[g][a][b][4 * q + 3]}; };
+                float4_t v = quad(0);
+#pragma unroll
+                for (int g = 1; g < G; g++) v += quad(g);
+                store_cols<EPI>(v, tok, nt * 32 + q * 8 + (lane >> 5) * 4, by, T_pad, N, out, out_act, act_plane, F_act);
+            }
         }
     }
 }
@@ -877,27 +929,19 @@ extern "C" int sled_projection_slices(int n_out, int n_in, int T, int* slices /*
     return SLED_OK;
 }
 
-// Row tiles per workgroup of the tile kernel beyond 128 rows, by the same estimate (without the partial sums, which do not depend on
-// it).  Times per k-step measured on full rounds: 0.35-0.39 us at 4 row tiles (as the wide shape), 0.51-0.54 at 6, 0.66-0.68 at
-// 8.  So equal rows cost about the same at each height, and what the choice gives is better filled rounds: 384 rows x 28672
-// columns are 336 workgroups in two rounds at 4 row tiles (178 us) and 224 in one round at 6 (137 us); 256 x 57344 take 383 us
-// at 4, 346 us at 8.
+// Row tiles per workgroup of the tile kernel beyond 128 rows, 4 or 6, by the same estimate (without the partial sums, which do not
+// depend on it).  Times per k-step on full rounds: 0.35-0.39 us at 4 row tiles (as the wide shape), 0.51-0.54 at 6.  So equal
+// rows cost about the same at either height, and what the choice gives is better filled rounds: 372 rows x 4096 x 28672 are 336
+// workgroups in two rounds at 4 row tiles (187 us) and 224 in one round at 6 (142 us); 220 x 8192 x 57344 are 448 in two
+// rounds at either (415 and 556 us).
 static int tile_height(int N, int K, int T_pad, int split) {
-    constexpr double FIXED_US = 9.0;
-    constexpr int HEIGHTS[3] = {4, 6, 8};
-    constexpr double STEP_US[3] = {0.40, 0.59, 0.74};
+    constexpr double FIXED_US = 9.0, STEP4_US = 0.40, STEP6_US = 0.59;
     const int n_col = (N / 32 + TILE_CT - 1) / TILE_CT, steps = (K / 16 / TILE_UNIT + split - 1) / split * TILE_UNIT;   // of the longest slice
-    int best = 0;
-    double best_t = -1.0;
-    for (int h = 0; h < 3; h++) {
-        const int64_t wgs = (int64_t)n_col * ((T_pad / 32 + HEIGHTS[h] - 1) / HEIGHTS[h]) * split;
-        const double t = (double)((wgs + 255) / 256) * (FIXED_US + steps * STEP_US[h]);
-        if (best_t < 0 || t < best_t) {
-            best_t = t;
-            best = HEIGHTS[h];
-        }
-    }
-    return best;
+    auto us = [&](int h, double step_us) {
+        const int64_t wgs = (int64_t)n_col * ((T_pad / 32 + h - 1) / h) * split;
+        return (double)((wgs + 255) / 256) * (FIXED_US + steps * step_us);
+    };
+    return us(6, STEP6_US) < us(4, STEP4_US) ? 6 : 4;
 }
 
 int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const void* W, const void* scale, int T, int T_pad,
@@ -950,11 +994,7 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
             a.n_zb = (mt_total + RT - 1) / RT;
             a.grid = dim3((a.n_col * a.n_split + 7) / 8 * 8 * a.n_zb, 1, 1);
             a.lds = (size_t)tile_ring(RT, TILE_CT, 1) * tile_stage_kib(RT, TILE_CT, 1) * 1024;
-            switch (RT) {
-                case 4: return launch_tile<4>(epilogue, a);
-                case 6: return launch_tile<6>(epilogue, a);
-                default: return launch_tile<8>(epilogue, a);
-            }
+            return RT == 6 ? launch_tile<6>(epilogue, a) : launch_tile<4>(epilogue, a);
         }
         if (wide)
             return m->wbits == 8 ? launch_epi_wb<4, WIDE_KG, WIDE_CG, 8>(epilogue, a) : launch_epi_wb<4, WIDE_KG, WIDE_CG, 4>(epilogue, a);

@@ -105,6 +105,86 @@ def test_no_instruction_touches_a_register_with_a_load_in_flight():
     assert not bad, "\n".join(bad[:20])
 
 
+# ------------------------------------------------------------------------------------------------ the kernel's own MFMAs
+def _any_regs(tok):
+    m = re.fullmatch(r"([av])(?:\[(\d+):(\d+)\]|(\d+))", tok)
+    lo, hi = (m.group(2), m.group(3)) if m.group(2) else (m.group(4), m.group(4))
+    return {(m.group(1), i) for i in range(int(lo), int(hi) + 1)}
+
+
+def scan_own_mfmas(text, kernel_filter="gemm_tile_kernel", after=18, before=2):
+    """MFMAs that the source writes out itself (csrc/gemm.hip: where the sums need more registers than the compiler gives its own)
+    get no wait states from the compiler.  In program order: no other instruction may name an MFMA's result within `after`
+    wait states (an MFMA of up to sixteen passes; ours has eight), and none may have written one of its operands with the vector unit
+    within `before`.  Returns (kernels with such MFMAs, such MFMAs, violations)."""
+    violations, kernels, n_own = [], set(), 0
+    name, in_asm, results, writes = None, False, [], []
+    for ln, line in enumerate(text.split("\n"), 1):
+        m = re.match(r"^(_Z\S+):", line)
+        if m:
+            name, results, writes = (m.group(1) if kernel_filter in m.group(1) else None), [], []
+            continue
+        t = line.strip()
+        if t.startswith(";;#ASM"):
+            in_asm = t.startswith(";;#ASMSTART")
+            continue
+        if name is None or not t or t[0] in ";.":
+            continue
+        op = t.split()[0]
+        args = [a.strip() for a in t[len(op):].split(";")[0].split(",")]
+        named = [set().union(*(_any_regs(r) for r in re.findall(r"\b[av](?:\[\d+:\d+\]|\d+)", a))) for a in args]
+        everything = set().union(*named)
+        states = int(args[0]) + 1 if op == "s_nop" else 1
+        if op.startswith("v_mfma"):
+            if in_asm:
+                kernels.add(name)
+                n_own += 1
+                for regs, age in writes:
+                    if regs & everything and age < before:
+                        violations.append(f"line {ln}: `{t}` reads what the vector unit wrote {age} wait states before")
+        else:
+            for regs, age in results:
+                if regs & everything:
+                    violations.append(f"line {ln}: `{t}` names the result of an MFMA {age} wait states after it")
+        results = [(r, a + states) for r, a in results if a + states < after]
+        writes = [(r, a + states) for r, a in writes if a + states < before]
+        if op.startswith("v_mfma"):
+            if in_asm:
+                results.append((named[0], 0))
+        elif op.startswith("v_"):
+            writes.append((named[0], 0))
+    return kernels, n_own, violations
+
+
+def test_own_mfma_scan_finds_planted_mistakes():
+    mfma = "\t;;#ASMSTART\n\tv_mfma_f32_32x32x16_bf16 v[16:31], v[2:5], v[6:9], v[16:31]\n\t;;#ASMEND\n"
+    good = "_Z16gemm_tile_kernelv:\n\tv_mov_b32_e32 v16, 0\n\ts_nop 1\n" + mfma + mfma + "\ts_nop 15\n\ts_nop 7\n\tv_add_f32_e32 v0, v16, v17\n\ts_endpgm\n"
+    kernels, n, bad = scan_own_mfmas(good)
+    assert (len(kernels), n, bad) == (1, 2, [])
+    assert scan_own_mfmas(good.replace("\ts_nop 15\n", ""))[2]                                   # the result is read too early
+    assert scan_own_mfmas(good.replace("\ts_nop 1\n", ""))[2]                                    # an operand was just written
+    assert scan_own_mfmas(good.replace(mfma + mfma, mfma + "\tv_accvgpr_write_b32 a0, v20\n" + mfma))[2]   # a copy between the two
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_nothing_touches_the_sums_of_the_kernels_own_mfmas():
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, "gemm.s")
+        flags = [f for f in B.FLAGS if f != "-fPIC"]
+        cmd = ["hipcc", *flags, "--cuda-device-only", "-S", os.path.join(B.CSRC, "gemm.hip"), "-o", out]
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr[-2000:]
+        text = open(out).read()
+    kernels, n_own, bad = scan_own_mfmas(text)
+    assert len(kernels) == 3 and n_own >= 3 * 48, (kernels, n_own)     # the tile of six row tiles, in each epilogue
+    assert not bad, "\n".join(bad[:20])
+    # and no spills: accesses to scratch memory would count in the hand-written waits, too
+    scratch = dict(re.findall(r"\.amdhsa_kernel (\S*gemm_tile_kernel\S*)\n(?:\s+\.amdhsa_.*\n)*?\s+\.amdhsa_private_segment_fixed_size (\d+)", text))
+    spilled = [k for k, n in scratch.items() if int(n)]
+    assert len(scratch) >= 9, len(scratch)
+    assert not spilled, spilled
+
+
 # ------------------------------------------------------------------------------------------------ attention
 VMEM = ("global_load", "global_store", "global_atomic", "buffer_", "scratch_", "flat_")
 
