@@ -1,7 +1,7 @@
 // Projections of the verify step: out[T, N] = X[T, K] * W[N, K]^T over the packed rows of a batch.
 //
-// Two kernels share the work of bf16 models.  16-bit weights run in gemm_tile_kernel (both operands through LDS; described there)
-// at every number of rows; 8- and 4-bit weights, batch-invariant models, and the LM head at 97 to 128 rows run in
+// Two kernels share the work of bf16 models.  16-bit weights run in gemm_tile_kernel (both operands through LDS; described there);
+// 8- and 4-bit weights, batch-invariant models, 65 to 96 rows (three row tiles), and the LM head at 97 to 128 rows run in
 // gemm_bf16_kernel, which the following describes.
 //
 // bf16 path (the one that matters): T is about 100-600 packed rows, so every weight byte is used
@@ -60,7 +60,7 @@ constexpr int AHEAD = DEPTH + 1;  // activation stages in flight beyond the one 
 constexpr int NXB = AHEAD + 1;    // LDS ring
 // Two workgroup shapes (KG k-groups = k-steps of 16 per stage, CG column groups of 64 columns):
 //   narrow  KG 4, CG 2: 128 columns, 64 k per stage.  Most workgroups per projection: the shape for one block of
-//           rows (up to 128) of 8- and 4-bit weights, and for batch-invariant models at any size, where the chip has to be filled by column blocks and K slices alone.
+//           rows (up to 128) of 8- and 4-bit weights, for three row tiles of any weights, and for batch-invariant models at any size, where the chip has to be filled by column blocks and K slices alone.
 //   wide    KG 2, CG 4: 256 columns, 32 k per stage.  Per MFMA it fetches two thirds of the bytes (half the
 //           activations, the same weights): the shape for several row blocks of 8- and 4-bit weights, where the
 //           workgroups are many anyway and the L2 -> CU path, not HBM, is what the MFMAs wait for (bf16 weights: the
@@ -485,8 +485,12 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(const bf16_t* __r
 //   - One block of rows (up to 128) runs in a slim tile, RT x 32 rows by 128 columns with two k-steps per stage: as many
 //     workgroups as the narrow shape above and the same K slices, but no k-group sums to exchange at the end, a cost that a
 //     launch of 15 to 60 us feels.  101 rows: gate/up 62.5 -> 61.3, QKV 22.7 -> 20.1 us; 8 layers and the head of the 8B
-//     shape 1.54-1.62 -> 1.45-1.55 ms from box to box, at 20 rows 1.08 -> 1.05, at one 1.03 -> 1.02.  With an odd number of row tiles the four
-//     wavefronts take a column tile each instead of quarters.
+//     shape 1.54-1.62 -> 1.45-1.55 ms from box to box, at 20 rows 1.08 -> 1.05, at one 1.03 -> 1.02.  With one row tile the four
+//     wavefronts take a column tile each instead of quarters.  Three row tiles do not run here: they divide into column quarters
+//     only, which read 28 KiB of LDS per k-step for 24 MFMAs (four tiles 24 for 32), and whether that is ahead of the narrow
+//     shape depends on the box: 8 layers and the head at 84 rows 1.36 against 1.42 ms on one, 1.49 against 1.47 on another,
+//     a prompt of 66 tokens 1.28 against 1.32 and 1.39 against 1.35.  (Dealt out as 2 + 1 row tiles it is the narrow shape's
+//     time on both.)
 // Loads and waits are written by hand as above; all vector-memory operations of the loop are direct-to-LDS loads, so
 // no register is ever the target of a load in flight.
 constexpr int TILE_WAVES = 4, TILE_CT = 8;
@@ -496,7 +500,7 @@ constexpr int tile_stage_kib(int RT, int CT, int U) { return (PLANES * RT + CT) 
 constexpr int TILE_UNIT = 8, TILE_MIN_STAGES = 16;
 // stages in the ring: what LDS holds, an even number, no more k-steps than the shortest slice has
 constexpr int tile_ring(int RT, int CT, int U) { return std::min(160 / tile_stage_kib(RT, CT, U) / 2 * 2, TILE_MIN_STAGES / U); }
-// wavefronts along the rows: quarters of 2 x 2 where the row tiles are even, else four column quarters of all rows
+// wavefronts along the rows: quarters of 2 x 2 where the row tiles are even, four column quarters of one
 constexpr int tile_wave_rows(int RT) { return RT % 2 == 0 ? 2 : 1; }
 
 // RT, CT: row and column tiles of the workgroup; U: k-steps per stage
@@ -952,7 +956,7 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
         if (N % 32 || K % 16 || T_pad % 32 || plan.split < 1 || KS % (NARROW_KG * NBUF) || plan.split > KS / (NARROW_KG * NBUF))
             SLED_FAIL(SLED_EINVAL, "gemm: unsupported shape N=%d K=%d T_pad=%d split=%d", N, K, T_pad, plan.split);
         const int mt_total = T_pad / 32;
-        // up to 128 rows (4 tiles): slim tile (16-bit weights) or narrow shape with exactly these tiles; more: the tile kernel at the height that suits
+        // up to 128 rows (4 tiles): slim tile (16-bit weights, not three tiles) or narrow shape with exactly these tiles; more: the tile kernel at the height that suits
         // (bf16 weights) or blocks of four tiles in the wide shape (8- and 4-bit weights); the last block may reach past the end
         // (a batch-invariant model keeps the narrow shape at every size: the two shapes add the k-steps up in
         // different groupings, so a row's sums would depend on whether its batch has more than 128 rows)
@@ -998,15 +1002,14 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
         }
         if (wide)
             return m->wbits == 8 ? launch_epi_wb<4, WIDE_KG, WIDE_CG, 8>(epilogue, a) : launch_epi_wb<4, WIDE_KG, WIDE_CG, 4>(epilogue, a);
-        // one block of rows, 16-bit weights: the slim tile kernel, wherever the slices are long enough for its ring
-        if (!wide && !broad && m->wbits == 16 && !m->batch_invariant && KS / TILE_UNIT >= plan.split * (TILE_MIN_STAGES / TILE_UNIT)) {
+        // one block of rows, 16-bit weights: the slim tile kernel (three row tiles: the narrow shape), wherever the slices are long enough for its ring
+        if (!wide && !broad && MT != 3 && m->wbits == 16 && !m->batch_invariant && KS / TILE_UNIT >= plan.split * (TILE_MIN_STAGES / TILE_UNIT)) {
             a.n_col = (NT + SLIM_CT - 1) / SLIM_CT;
             a.grid = dim3((a.n_col * a.n_split + 7) / 8 * 8, 1, 1);
             a.lds = (size_t)tile_ring(MT, SLIM_CT, SLIM_U) * tile_stage_kib(MT, SLIM_CT, SLIM_U) * 1024;
             switch (MT) {
                 case 1: return launch_tile<1, SLIM_CT, SLIM_U>(epilogue, a);
                 case 2: return launch_tile<2, SLIM_CT, SLIM_U>(epilogue, a);
-                case 3: return launch_tile<3, SLIM_CT, SLIM_U>(epilogue, a);
                 default: return launch_tile<4, SLIM_CT, SLIM_U>(epilogue, a);
             }
         }
