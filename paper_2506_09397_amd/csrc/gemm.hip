@@ -498,6 +498,7 @@ constexpr int SLIM_CT = 4, SLIM_U = 2;   // one block of up to 128 rows: see bel
 constexpr int tile_stage_kib(int RT, int CT, int U) { return (PLANES * RT + CT) * U; }
 // K is dealt out to the slices in units of 8 k-steps; a slice holds at least two units, so never fewer stages than the ring
 constexpr int TILE_UNIT = 8, TILE_MIN_STAGES = 16;
+static_assert(NARROW_KG * NBUF >= TILE_MIN_STAGES, "sled_launch_gemm has at most K / (16 NARROW_KG NBUF) slices");
 // stages in the ring: what LDS holds, an even number, no more k-steps than the shortest slice has
 constexpr int tile_ring(int RT, int CT, int U) { return std::min(160 / tile_stage_kib(RT, CT, U) / 2 * 2, TILE_MIN_STAGES / U); }
 // wavefronts along the rows: quarters of 2 x 2 where the row tiles are even, four column quarters of one
@@ -740,7 +741,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     const int n0 = (blockIdx.x * 4 + wv) * F32_NC, t0 = blockIdx.y * F32_T;
     const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
     float4 xr[4], wr[F32_NC];
-    auto fetch = [&](int k0) {   // K is a multiple of 4 (rows of float4)
+    auto fetch = [&](int k0) {   // rows of float4: every K of an fp32 model is a multiple of 8
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             const int t = t0 + i * 4 + wv, k = k0 + lane * 4;
@@ -953,7 +954,7 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
                      int F_act, hipStream_t st) {
     if (m->s.dtype == SLED_BF16) {
         const int NT = N / 32, KS = K / 16;
-        if (N % 32 || K % 16 || T_pad % 32 || plan.split < 1 || KS % (NARROW_KG * NBUF) || plan.split > KS / (NARROW_KG * NBUF))
+        if (N % 32 || K % 16 || T_pad % 32 || plan.split < 1 || KS % (NARROW_KG * NBUF) || plan.split > KS / (NARROW_KG * NBUF))   // a slice is never shorter than a trip of the narrow shape and than the tile kernel's ring
             SLED_FAIL(SLED_EINVAL, "gemm: unsupported shape N=%d K=%d T_pad=%d split=%d", N, K, T_pad, plan.split);
         const int mt_total = T_pad / 32;
         // up to 128 rows (4 tiles): slim tile (16-bit weights, not three tiles) or narrow shape with exactly these tiles; more: the tile kernel at the height that suits
@@ -1002,8 +1003,8 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
         }
         if (wide)
             return m->wbits == 8 ? launch_epi_wb<4, WIDE_KG, WIDE_CG, 8>(epilogue, a) : launch_epi_wb<4, WIDE_KG, WIDE_CG, 4>(epilogue, a);
-        // one block of rows, 16-bit weights: the slim tile kernel (three row tiles: the narrow shape), wherever the slices are long enough for its ring
-        if (!wide && !broad && MT != 3 && m->wbits == 16 && !m->batch_invariant && KS / TILE_UNIT >= plan.split * (TILE_MIN_STAGES / TILE_UNIT)) {
+        // one block of rows, 16-bit weights: the slim tile kernel (three row tiles: the narrow shape)
+        if (!wide && !broad && MT != 3 && m->wbits == 16 && !m->batch_invariant) {
             a.n_col = (NT + SLIM_CT - 1) / SLIM_CT;
             a.grid = dim3((a.n_col * a.n_split + 7) / 8 * 8, 1, 1);
             a.lds = (size_t)tile_ring(MT, SLIM_CT, SLIM_U) * tile_stage_kib(MT, SLIM_CT, SLIM_U) * 1024;
@@ -1022,7 +1023,6 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
         }
     }
     // fp32: no split, plain store (partial buffer with one slice has the same layout)
-    if (K % 4) SLED_FAIL(SLED_EINVAL, "gemm: fp32 rows of %d values, not a multiple of 4", K);
     dim3 grid((N + 4 * F32_NC - 1) / (4 * F32_NC), (T + F32_T - 1) / F32_T);
     hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, st, static_cast<const float*>(X),
                        static_cast<const float*>(W), T, N, K, out_f32);
