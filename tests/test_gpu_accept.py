@@ -314,6 +314,24 @@ def test_row_confidence_matches_oracle(T, vocab, temperature, std):
     assert torch.equal(conf, conf2)
 
 
+def test_row_confidence_uses_float32_exponentials_of_full_accuracy():
+    """Rows of one 0 and n equal values a in [-5, 0): the probability is 1 / (1 + n e^a), every term alike, so that the rounding of the
+    one exponential does not average out.  Against the same expression on torch's float32 exponential, which is the device's expf:
+    what is left is the rounding of the result (2^-24) and of three float32 additions of one thread's sum of 1 to 4, in a
+    total of at least 7.9 (3 x 2^-23 / 7.9)."""
+    T, V = 4096, 1024
+    a = (-5.0 * (torch.arange(T, dtype=torch.float64) + 0.37) / T).float().cuda()
+    logits = a[:, None].repeat(1, V)
+    logits[:, 0] = 0.0
+    conf = torch.empty(T, dtype=torch.float32, device="cuda")
+    ws = sled.workspace(sled.sled_accept_workspace_bytes(1, T, V))
+    sled.sled_row_confidence(V, 1.0, logits, conf, None, ws)
+    for name, e in (("float64", torch.exp(a.double())), ("float32", torch.exp(a).double())):
+        err = (conf.double() * (1.0 + (V - 1) * e) - 1.0).abs()
+        print(f"{name} exponentials: max {err.max().item():.3e}, rms {err.pow(2).mean().sqrt().item():.3e}")
+    assert err.max().item() < 2.0 ** -24 + 3 * 2.0 ** -23 / 7.9
+
+
 def test_row_confidence_argument_errors():
     logits = torch.zeros(4, 256, device="cuda")
     conf = torch.empty(4, device="cuda")
