@@ -783,12 +783,12 @@ size_t sled_accept_ws_bytes(int B, int T, int n_split) {
     return (stats + 255) & ~(size_t)255;
 }
 
-// Behind the statistics: tile sums and decisions of the sweeps that run as launches of their own, and accept_over's word on every
-// request.  A workspace without that room is as good: the rows are then scanned in one launch and the finish sweeps itself.
-static size_t sweep_ws_bytes(int B, int vocab) {
-    return (size_t)B * (sizeof(Decision) + sizeof(int32_t) + 2 * (size_t)((vocab + WTILE - 1) / WTILE) * sizeof(double));
-}
-size_t sled_accept_ws_bytes_full(int B, int T, int vocab) { return sled_accept_ws_bytes(B, T, 16) + 256 + sweep_ws_bytes(B, vocab); }
+// Behind the statistics: accept_over's word on every request, then tile sums and decisions of the sweeps that run as launches of
+// their own.  Each of the two is used where the workspace has room for it.  A workspace without is as good: the rows are then
+// scanned in one launch, and the finish sweeps itself.
+static size_t over_ws_bytes(int B) { return ((size_t)B * sizeof(int32_t) + 255) & ~(size_t)255; }
+static size_t sweep_ws_bytes(int B, int vocab) { return (size_t)B * (sizeof(Decision) + 2 * (size_t)((vocab + WTILE - 1) / WTILE) * sizeof(double)); }
+size_t sled_accept_ws_bytes_full(int B, int T, int vocab) { return sled_accept_ws_bytes(B, T, 16) + over_ws_bytes(B) + sweep_ws_bytes(B, vocab); }
 
 int sled_accept_pick_split(int T, int vocab) {
     // enough workgroups (rows x segments) for several rounds over the chip, so that the last round is short
@@ -821,20 +821,26 @@ int sled_launch_accept(int mode, int B, int T, const int* k_host, int vocab, flo
     int k_top = 0;
     for (int i = 0; i < B; i++) k_top = std::max(k_top, k_host[i]);
     const int n_tiles = (vocab + WTILE - 1) / WTILE;
-    const bool room = ws_bytes >= sled_accept_ws_bytes(B, T, sled_accept_pick_split(T, vocab)) + sweep_ws_bytes(B, vocab);
     int cuts[4] = {0, 0, 0, 0}, n_part = 1;
-    for (int c = 2; room && c <= 8 && c <= k_top; c *= 2)
+    for (int c = 2; c <= 8 && c <= k_top; c *= 2)
         if (rows_from(c) * vocab * 4 >= (int64_t)64000000 * c && (int64_t)B * (k_top + 1 - c) <= 4 * rows_from(c)) cuts[n_part++] = c;
     // Segments per row: about 2048 workgroups in the (first) launch.  More of them are shorter than their own start and
     // reduction: 276 rows in 16 segments took 45 us for 141 MB, in 7 27 us.
-    const int64_t rows_first = n_part > 1 ? T - rows_from(cuts[1]) : T;
-    const int n_split = std::min(sled_accept_pick_split(T, vocab), (int)std::max<int64_t>(1, (2048 + rows_first / 2) / rows_first));
+    auto segments = [&]() {
+        const int64_t rows_first = n_part > 1 ? T - rows_from(cuts[1]) : T;
+        return std::min(sled_accept_pick_split(T, vocab), (int)std::max<int64_t>(1, (2048 + rows_first / 2) / rows_first));
+    };
+    int n_split = segments();
+    if (n_part > 1 && ws_bytes < sled_accept_ws_bytes(B, T, n_split) + over_ws_bytes(B)) {
+        n_part = 1;
+        n_split = segments();
+    }
     int seg = (vocab + n_split - 1) / n_split;
     seg = (seg + 3) & ~3;
     RowStat* stats = reinterpret_cast<RowStat*>(ws);
-    double* sums = reinterpret_cast<double*>(static_cast<char*>(ws) + sled_accept_ws_bytes(B, T, n_split));
-    Decision* decided = reinterpret_cast<Decision*>(sums + (size_t)B * 2 * n_tiles);
-    int32_t* over = reinterpret_cast<int32_t*>(decided + B);   // (these three only with room)
+    const size_t over_at = sled_accept_ws_bytes(B, T, n_split), sums_at = over_at + over_ws_bytes(B);
+    int32_t* over = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + over_at);   // there when the scan comes in parts
+    const bool sweep_room = ws_bytes >= sums_at + sweep_ws_bytes(B, vocab);
     for (int part = 0; part < n_part && n_part > 1; part++) {
         const int j0 = cuts[part], j1 = part + 1 < n_part ? cuts[part + 1] : k_top + 1;
         const RowPart rp{B, j0, kp, over};
@@ -864,9 +870,9 @@ int sled_launch_accept(int mode, int B, int T, const int* k_host, int vocab, flo
     // 48 + 57 + 10 us in three launches, 93 in one.
     Decision* decisions = nullptr;
     double* tile_sums = nullptr;
-    if (mode == SLED_SAMPLE && room && n_tiles >= 32 && B <= 128) {
-        tile_sums = sums;
-        decisions = decided;
+    if (mode == SLED_SAMPLE && sweep_room && n_tiles >= 32 && B <= 128) {
+        tile_sums = reinterpret_cast<double*>(static_cast<char*>(ws) + sums_at);
+        decisions = reinterpret_cast<Decision*>(tile_sums + (size_t)B * 2 * n_tiles);
         const dim3 grid(B, std::min((n_tiles + 7) / 8, std::max(2, 512 / B)));   // a workgroup has eight wavefronts, a tile each at a time
         hipLaunchKernelGGL(accept_sweep<false>, grid, dim3(512), 0, st, kp, vocab, n_split, inv_tau, temperature, logits, tokens, qsrc, u_acc, stats,
                            decisions, tile_sums);

@@ -9,10 +9,11 @@ from paper_2506_09397_amd import sled, synth
 pytestmark = pytest.mark.gpu
 
 
-def _run(mode, k, vocab, logits, tokens, q, u_acc, u_smp, pairs):
+def _run(mode, k, vocab, logits, tokens, q, u_acc, u_smp, pairs, ws=None):
     a = torch.zeros(len(k), dtype=torch.int32, device="cuda")
     t = torch.zeros_like(a)
-    ws = sled.workspace(sled.sled_accept_workspace_bytes(len(k), sum(k) + len(k), vocab))
+    if ws is None:
+        ws = sled.workspace(sled.sled_accept_workspace_bytes(len(k), sum(k) + len(k), vocab))
     ws.fill_(0xFF)   # statistics that nobody wrote read as NaN
     if pairs:
         ids, probs, rest = q
@@ -54,3 +55,40 @@ def test_parts_match_small_batches(mode, vocab, B, k_max, pairs):
         a2, t2 = _run(m, k[i:e], vocab, c.logits[r].contiguous(), tokens[r].contiguous(), qq, c.u_acc[d].contiguous(), c.u_smp[i:e].contiguous(), pairs)
         assert a[i:e].tolist() == a2.tolist() and t[i:e].tolist() == t2.tolist(), f"requests {i}..{e - 1}"
     assert 0 < a.sum() < sum(k)
+
+
+def _stat_bytes(T, vocab, segments=None):
+    """the row statistics' share of a workspace: 16 bytes for each of a row's segments, whole 256 bytes"""
+    n = min(16, -(-8192 // T))
+    while n > 1 and vocab // n < 2048:
+        n -= 1
+    return (T * (segments or n) * 16 + 255) // 256 * 256
+
+
+def _unwritten(ws):
+    """16-byte records that nobody wrote, before the last one that somebody did"""
+    r = (ws[:ws.numel() // 16 * 16].view(-1, 16) != 0xFF).any(dim=1).cpu().numpy()
+    return int((~r[:np.flatnonzero(r)[-1]]).sum())
+
+
+# the least workspace that is accepted has room for the statistics alone; one of 16 segments a row, the size for every call before the
+# sweeps had launches of their own, has room for the word on every request that the scan in parts needs, but not for the sweeps
+@pytest.mark.parametrize("mode,B", [("greedy", 200), ("sample", 200), ("sample", 120)])
+def test_smaller_workspaces_and_the_static_one(mode, B):
+    vocab, k = 128256, [8] * B
+    T, m = 9 * B, sled.GREEDY if mode == "greedy" else sled.SAMPLE
+    c = synth.accept_case(k, vocab, 0.5, seed=B + 1, device="cuda")
+    args = (m, k, vocab, c.logits, c.tokens, c.q, c.u_acc, c.u_smp, 0)
+    want = [x.tolist() for x in _run(*args)]
+    for size in ("least", "earlier"):
+        ws = sled.workspace(_stat_bytes(T, vocab) if size == "least" else _stat_bytes(T, vocab, 16) + 256)
+        assert [x.tolist() for x in _run(*args, ws=ws)] == want, size
+        if size == "earlier":
+            assert _unwritten(ws) > T // 4          # rows behind a rejection were left out
+    with pytest.raises(sled.SledError):
+        _run(*args, ws=sled.workspace(_stat_bytes(T, vocab))[:-256])
+    a = torch.zeros(B, dtype=torch.int32, device="cuda")
+    t = torch.zeros_like(a)
+    q, ua, us = (c.q, c.u_acc, c.u_smp) if m == sled.SAMPLE else (None, None, None)
+    sled.sled_accept_static(m, k, vocab, 1.0, c.logits, c.tokens, q, ua, us, a, t)
+    assert [a.tolist(), t.tolist()] == want
