@@ -1,11 +1,14 @@
 // Vocab-parallel acceptance (greedy match or speculative sampling, Eq. 1 of Sec. 3.1).
 //
-// Two kinds of kernel per call:
+// Four kinds of kernel, the second and third for large and for small batches only:
 //   accept_row_stats   per row of logits (split over a few workgroups when the batch is small) the maximum, its
 //                      lowest index, and sum exp((z - max)/tau).  Pure HBM scan: four float4 loads in flight per
-//                      thread, wavefront reductions.  A large batch is scanned in up to three launches that take the
-//                      requests' rows from the front, with the accept test of the rows so far (accept_over) between
-//                      them: where one of them ended the prefix nothing reads what is behind it.
+//                      thread, wavefront reductions.
+//   accept_over        a large batch is scanned in up to four launches that take the requests' rows from the front; between
+//                      them this one makes the accept test of the rows so far: where one of them ended the prefix
+//                      nothing reads what is behind it.
+//   accept_sweep       a batch too small to fill the chip with one workgroup per request has its float64 sums over the
+//                      drawn row made here, in two launches, instead of in accept_finish.
 //   accept_finish      one workgroup per request.  Its first wavefront applies the accept test (or the
 //                      argmax comparison) to all of the request's rows at once, one row per lane, and
 //                      takes the first failure.  In sampling mode the workgroup then draws the request's

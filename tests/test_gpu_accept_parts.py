@@ -92,3 +92,29 @@ def test_smaller_workspaces_and_the_static_one(mode, B):
     q, ua, us = (c.q, c.u_acc, c.u_smp) if m == sled.SAMPLE else (None, None, None)
     sled.sled_accept_static(m, k, vocab, 1.0, c.logits, c.tokens, q, ua, us, a, t)
     assert [a.tolist(), t.tolist()] == want
+
+
+def test_all_three_cuts():
+    """Cuts at rows 2, 4 and 8 (about 1400 rows behind the last one): the later tests read rows that earlier cuts left out."""
+    vocab, B = 128256, 110
+    rng = np.random.default_rng(7)
+    k = rng.integers(16, 25, size=B).tolist()
+    T = sum(k) + B
+    g = torch.Generator(device="cuda").manual_seed(7)
+    logits = torch.randn(T, vocab, generator=g, device="cuda")
+    tokens = torch.randint(0, vocab, (T,), generator=g, device="cuda", dtype=torch.int32)
+    hit = torch.from_numpy(rng.random(T - 1) < 0.85).cuda()       # a third of the requests get past row 8
+    best = logits.argmax(dim=1)
+    tokens[1:] = torch.where(hit, best[:-1].to(torch.int32), tokens[1:])
+    ws = sled.workspace(sled.sled_accept_workspace_bytes(B, T, vocab))
+    a, t = _run(sled.GREEDY, k, vocab, logits, tokens, None, None, None, 0, ws=ws)
+    assert _unwritten(ws) > T // 4
+    tk, bt, row, want = tokens.cpu().numpy(), best.cpu().numpy(), 0, []
+    for n in k:
+        j = 0
+        while j < n and tk[row + j + 1] == bt[row + j]:
+            j += 1
+        want.append((j, int(bt[row + j])))
+        row += n + 1
+    assert list(zip(a.tolist(), t.tolist())) == want
+    assert sum(x > 8 for x, _ in want) > 10 and sum(x < 2 for x, _ in want) > 10
