@@ -868,12 +868,14 @@ int sled_launch_accept(int mode, int B, int T, const int* k_host, int vocab, flo
         SLED_LAUNCH_CHECK();
     }
     // The two float64 sweeps over a request's row are what the finish spends its time on: 93 us with one workgroup per request,
-    // be they 48 or 256.  Up to 128 requests, from 32 tiles (32768 tokens) on, they get launches of their own with two workgroups
-    // per CU: 48 requests 17 + 14 + 13 us.  Where every CU has a request anyway that does not pay: 256 requests
-    // 48 + 57 + 10 us in three launches, 93 in one.
+    // be they 48 or 256.  From 32 tiles (32768 tokens) on, they get launches of their own with two workgroups per CU: 48
+    // requests 17 + 14 + 13 us.  Where most CUs have a request anyway that does not pay: whole calls of B requests x 8 drafts x
+    // 128256 tokens, sweeps of their own / in the finish, dense q: 96 112 / 136 us, 128 132 / 150, 160 162 / 170, 192 193 / 182,
+    // 256 221 / 209, 384 313 / 322; sparse: 160 201 / 206, 192 230 / 217, 256 261 / 248, 384 387 / 400.
+    constexpr int SWEEP_MAX_B = 160;
     Decision* decisions = nullptr;
     double* tile_sums = nullptr;
-    if (mode == SLED_SAMPLE && sweep_room && n_tiles >= 32 && B <= 128) {
+    if (mode == SLED_SAMPLE && sweep_room && n_tiles >= 32 && B <= SWEEP_MAX_B) {
         tile_sums = reinterpret_cast<double*>(static_cast<char*>(ws) + sums_at);
         decisions = reinterpret_cast<Decision*>(tile_sums + (size_t)B * 2 * n_tiles);
         const dim3 grid(B, std::min((n_tiles + 7) / 8, std::max(2, 512 / B)));   // a workgroup has eight wavefronts, a tile each at a time
