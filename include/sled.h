@@ -216,10 +216,14 @@ SLED_API size_t sled_verify_workspace_bytes(const sled_model* m, int B_max, int 
  * sled_projection_slices: the number of K slices (partial sums that a row kernel or the attention prologue adds up)
  * a projection of n_out outputs over n_in inputs runs with in a step of T packed rows of a bf16 model (weights in 16, 8
  * or 4 bits alike; in batch-invariant mode every step runs with the slices of T = 1), and the most it may ever use (which
- * sizes the workspace).  n_out a multiple of 32, n_in of 256. */
+ * sizes the workspace).  n_out a multiple of 32, n_in of 256.
+ *
+ * sled_projection_rows: the rows one workgroup of that projection covers with 16-bit weights (not in batch-invariant mode):
+ * all of them, in whole tiles of 32, up to 128 rows; 128 or 192 beyond. */
 SLED_API int sled_attention_partition(int n_kv_heads, int B, const int* n_pages /*host*/, int* pages_per_item /*host out*/,
                              int* n_items /*host out*/);
 SLED_API int sled_projection_slices(int n_out, int n_in, int T, int* slices /*host out*/, int* max_slices /*host out*/);
+SLED_API int sled_projection_rows(int n_out, int n_in, int T, int* rows /*host out*/);
 
 /* One batched verification forward.
  *   req_ids[B], k[B]   host; 0 <= k[i] <= k_max (k[i] = 0 is a plain decode step); a request

@@ -949,6 +949,16 @@ static int tile_height(int N, int K, int T_pad, int split) {
     return us(6, STEP6_US) < us(4, STEP4_US) ? 6 : 4;
 }
 
+extern "C" int sled_projection_rows(int n_out, int n_in, int T, int* rows /*host out*/) {
+    int slices, cap;
+    if (!rows) SLED_FAIL(SLED_EINVAL, "sled_projection_rows: null argument");
+    const int rc = sled_projection_slices(n_out, n_in, T, &slices, &cap);
+    if (rc != SLED_OK) return rc;
+    const int T_pad = (T + 31) / 32 * 32;
+    *rows = T_pad <= 128 ? T_pad : 32 * tile_height(n_out, n_in, T_pad, slices);
+    return SLED_OK;
+}
+
 int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const void* W, const void* scale, int T, int T_pad,
                      int N, int K, int epilogue, sled_gemm_plan plan, float* out_f32, void* out_act, size_t act_plane,
                      int F_act, hipStream_t st) {

@@ -32,7 +32,7 @@ EXPORTS = [
     "sled_model_set_weight_bits",
     "sled_kvpool_create", "sled_kvpool_open", "sled_kvpool_close", "sled_kvpool_lengths", "sled_kvpool_destroy",
     "sled_kv_append", "sled_kv_read", "sled_verify_workspace_bytes", "sled_verify_batch", "sled_prefill",
-    "sled_attention_partition", "sled_projection_slices",
+    "sled_attention_partition", "sled_projection_slices", "sled_projection_rows",
     "sled_accept_workspace_bytes", "sled_accept", "sled_accept_static", "sled_accept_sparse", "sled_row_confidence", "sled_profile_enable", "sled_profile_read",
     "sled_strerror", "sled_last_error",
 ]
@@ -78,6 +78,7 @@ def lib() -> C.CDLL:
     L.sled_verify_workspace_bytes.argtypes = [vp, C.c_int, C.c_int, C.c_int64]
     L.sled_attention_partition.argtypes = [C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]
     L.sled_projection_slices.argtypes = [C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]
+    L.sled_projection_rows.argtypes = [C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]
     L.sled_verify_workspace_bytes.restype = C.c_size_t
     L.sled_verify_batch.argtypes = [vp, vp, C.c_int, ip, ip, vp, vp, vp, C.c_size_t, vp]
     L.sled_prefill.argtypes = [vp, vp, C.c_int, C.c_int, vp, vp, vp, C.c_size_t, vp]
@@ -198,6 +199,13 @@ def sled_projection_slices(n_out: int, n_in: int, T: int):
     a, b = C.c_int(0), C.c_int(0)
     _check(lib().sled_projection_slices(n_out, n_in, T, C.byref(a), C.byref(b)))
     return a.value, b.value
+
+
+def sled_projection_rows(n_out: int, n_in: int, T: int) -> int:
+    """Rows one workgroup of a projection n_in -> n_out covers in a step of T rows, 16-bit weights."""
+    a = C.c_int(0)
+    _check(lib().sled_projection_rows(n_out, n_in, T, C.byref(a)))
+    return a.value
 
 
 def sled_verify_batch(model: int, pool: int, req_ids: Sequence[int], k: Sequence[int], tokens: torch.Tensor,

@@ -11,6 +11,21 @@ from paper_2506_09397_amd import sled, synth
 
 CUS = 256
 
+# Steps of one layer of the large shapes that test_gpu_tile_rows.py runs, and what they are there for: per projection the K slices
+# (unequal ones marked) and the rows of a workgroup.  Between them the projections in slices have both heights, equal and unequal.
+LARGE_LAYER_CASES = [
+    ("llama8b", 545, {"qkv": (2, False, 128), "o": (3, True, 128), "gu": (1, False, 192), "dn": (3, True, 128)}),
+    ("llama8b", 700, {"qkv": (3, True, 128), "o": (2, False, 128), "gu": (1, False, 192), "dn": (5, True, 128)}),
+    ("llama8b", 1300, {"qkv": (2, False, 192), "o": (1, False, 128), "gu": (1, False, 128), "dn": (4, False, 192)}),
+    ("llama70b", 1030, {"qkv": (2, False, 192), "o": (2, False, 192), "gu": (1, False, 128), "dn": (5, True, 192)}),
+]
+
+
+def _projections(shape):
+    s = synth.SHAPES[shape]
+    heads = s.n_q_heads * s.head_dim
+    return {"qkv": (heads + 2 * s.n_kv_heads * s.head_dim, s.d_model), "o": (s.d_model, heads), "gu": (2 * s.d_ffn, s.d_model), "dn": (s.d_model, s.d_ffn)}
+
 
 def _items(n_pages, tgt, H):
     """sizes of the work items of one launch, in launch order (longest requests first, even split per request)"""
@@ -107,3 +122,21 @@ def test_projection_slices_of_the_benchmark_model():
                 assert s == sled.sled_projection_slices(N, K, 1)[0]
     with pytest.raises(Exception):
         sled.sled_projection_slices(100, 4096, 10)
+
+
+@pytest.mark.parametrize("shape,T,want", LARGE_LAYER_CASES)
+def test_the_large_layer_cases_have_the_slices_and_heights_they_are_there_for(shape, T, want):
+    got = {}
+    for name, (N, K) in _projections(shape).items():
+        s = sled.sled_projection_slices(N, K, T)[0]
+        got[name] = (s, (K // 128) % s != 0, sled.sled_projection_rows(N, K, T))      # K is dealt out in units of 128
+    assert got == want
+
+
+def test_rows_of_a_workgroup():
+    d, F = 4096, 14336
+    assert [sled.sled_projection_rows(d, d, T) for T in (1, 32, 33, 96, 97, 128)] == [32, 32, 64, 96, 128, 128]
+    # 112 column blocks: 336 workgroups in two rounds at 128 rows, 224 in one at 192; four blocks of 128 fill two rounds as well
+    assert [sled.sled_projection_rows(2 * F, d, T) for T in (129, 256, 257, 372, 384, 500)] == [128, 128, 192, 192, 192, 128]
+    with pytest.raises(Exception):
+        sled.sled_projection_rows(100, 4096, 10)
