@@ -485,7 +485,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(const bf16_t* __r
 //   - One block of rows (up to 128) runs in a slim tile, RT x 32 rows by 128 columns with two k-steps per stage: as many
 //     workgroups as the narrow shape above and the same K slices, but no k-group sums to exchange at the end, a cost that a
 //     launch of 15 to 60 us feels.  101 rows: gate/up 62.5 -> 61.3, QKV 22.7 -> 20.1 us; 8 layers and the head of the 8B
-//     shape 1.54-1.62 -> 1.45-1.55 ms from box to box, at 20 rows 1.08 -> 1.05, at one 1.03 -> 1.02.  With one row tile the four
+//     shape 1.54-1.62 -> 1.45-1.55 ms from box to box, at 20 rows 1.08 -> 1.05, at one 1.03 -> 1.01.  With one row tile the four
 //     wavefronts take a column tile each instead of quarters.  Three row tiles do not run here: they divide into column quarters
 //     only, which read 28 KiB of LDS per k-step for 24 MFMAs (four tiles 24 for 32), and whether that is ahead of the narrow
 //     shape depends on the box: 8 layers and the head at 84 rows 1.36 against 1.42 ms on one, 1.49 against 1.47 on another,
@@ -503,10 +503,14 @@ static_assert(NARROW_KG * NBUF >= TILE_MIN_STAGES, "sled_launch_gemm has at most
 constexpr int tile_ring(int RT, int CT, int U) { return std::min(160 / tile_stage_kib(RT, CT, U) / 2 * 2, TILE_MIN_STAGES / U); }
 // wavefronts along the rows: quarters of 2 x 2 where the row tiles are even, four column quarters of one
 constexpr int tile_wave_rows(int RT) { return RT % 2 == 0 ? 2 : 1; }
+// a wavefront's sums, in tiles of 16 registers.  Up to eight of them (one or two row tiles) fit into the 256 registers of a launch bound
+// of two wavefronts per SIMD, for which the compiler keeps MFMA results in ordinary registers: they are added up as they are,
+// where accumulation registers are read into ordinary ones first.  8 layers and the head at one row 1.026 -> 1.013 ms.
+constexpr int tile_sums(int RT, int CT, int U) { return 2 * U * RT * CT / TILE_WAVES; }
 
 // RT, CT: row and column tiles of the workgroup; U: k-steps per stage
 template <int RT, int CT, int U, int EPI>
-__global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf16_t* __restrict__ Xp, size_t x_plane,
+__global__ __launch_bounds__(64 * TILE_WAVES, tile_sums(RT, CT, U) <= 8 ? 2 : 1) void gemm_tile_kernel(const bf16_t* __restrict__ Xp, size_t x_plane,
                                                                        const bf16_t* __restrict__ Wp, int NT, int KS, int n_col,
                                                                        int n_split, int n_zb, int T, int T_pad, int N,
                                                                        float* __restrict__ out, bf16_t* __restrict__ out_act,
@@ -580,7 +584,8 @@ __global__ __launch_bounds__(64 * TILE_WAVES, 1) void gemm_tile_kernel(const bf1
     // compiler does not know what such an instruction needs: nothing but another MFMA may touch a tile between the zeros below and
     // the wait behind the last stage (compiled code is checked for it).
     constexpr bool MORE_THAN_16 = G * HC * HR > 16;
-    auto in_agpr = [](int g, int a, int b) { return g * HC * HR + a * HR + b < 16; };
+    constexpr int IN_AGPR = tile_sums(RT, CT, U) <= 8 ? 0 : 16;
+    auto in_agpr = [](int g, int a, int b) { return g * HC * HR + a * HR + b < IN_AGPR; };
     float16_t acc[G][HC][HR];
 
     struct frags {
