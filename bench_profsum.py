@@ -72,7 +72,7 @@ def traffic(dfetch: str, dwrite: str) -> None:
     print(f"{'kernel':70s} {'grid':>10s} {'n':>5s} {'fetch MB':>10s} {'write MB':>10s}   (per dispatch, scaled)")
     for key in sorted(fe, key=lambda k: -sum(fe[k])):
         n, g = key
-        if n.startswith("at::") or "rocclr" in n or n.startswith("pack_rows") or n.startswith("kv_ingest"):
+        if n.startswith("at::") or "rocclr" in n or n.startswith("pack_rows") or n.startswith("kv_move"):
             continue  # set-up work of the benchmark script (weight generation, loading, context upload)
         f_mb = sum(fe[key]) / len(fe[key]) * sf * 1024 / 1e6
         w_mb = (sum(wr[key]) / len(wr[key]) * sw * 1024 / 1e6) if key in wr else float("nan")
@@ -92,7 +92,7 @@ def mfma(d: str) -> None:
         dur[(short(r["Kernel_Name"]), grid)].append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
     print(f"{'kernel':40s} {'grid':>9s} {'n':>5s} {'avg us':>9s} {'MFMA busy':>10s} {'clock GHz':>10s}")
     for key in sorted(busy, key=lambda k: -sum(busy[k])):
-        if "gemm_bf16" not in key[0] or key not in act or key not in dur:
+        if ("gemm_bf16" not in key[0] and "gemm_tile" not in key[0]) or key not in act or key not in dur:
             continue
         b, a, t = sum(busy[key]) / len(busy[key]), sum(act[key]) / len(act[key]), sum(dur[key]) / len(dur[key])
         print(f"{key[0]:40s} {key[1]:9d} {len(busy[key]):5d} {t:9.1f} {b / (a / 8 * 1024):10.3f} {a / 8 / (t * 1e3):10.2f}")
