@@ -485,10 +485,10 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(const bf16_t* __r
 //   - One block of rows (up to 128) runs in a slim tile, RT x 32 rows by 128 columns with two k-steps per stage: as many
 //     workgroups as the narrow shape above and the same K slices, but no k-group sums to exchange at the end, a cost that a
 //     launch of 15 to 60 us feels.  101 rows: gate/up 62.5 -> 61.3, QKV 22.7 -> 20.1 us; 8 layers and the head of the 8B
-//     shape 1.54-1.62 -> 1.45-1.55 ms from box to box, at 20 rows 1.08 -> 1.05, at one 1.03 -> 1.01.  With one row tile the four
+//     shape 1.54-1.62 -> 1.45-1.55 ms from card to card, at 20 rows 1.08 -> 1.05, at one 1.03 -> 1.01.  With one row tile the four
 //     wavefronts take a column tile each instead of quarters.  Three row tiles do not run here: they divide into column quarters
 //     only, which read 28 KiB of LDS per k-step for 24 MFMAs (four tiles 24 for 32), and whether that is ahead of the narrow
-//     shape depends on the box: 8 layers and the head at 84 rows 1.36 against 1.42 ms on one, 1.49 against 1.47 on another,
+//     shape depends on the card: 8 layers and the head at 84 rows 1.36 against 1.42 ms on one, 1.49 against 1.47 on another,
 //     a prompt of 66 tokens 1.28 against 1.32 and 1.39 against 1.35.  (Dealt out as 2 + 1 row tiles it is the narrow shape's
 //     time on both.)
 // Loads and waits are written by hand as above; all vector-memory operations of the loop are direct-to-LDS loads, so
