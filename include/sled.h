@@ -288,7 +288,7 @@ SLED_API int sled_accept(int mode, int B, const int* k /*host*/, int vocab, floa
 
 /* sled_accept for callers that cannot allocate device memory -- code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc: same arguments and results as sled_accept without the workspace.  The row
- * statistics (and, where they leave room, four bytes per request for a large batch's scan in parts) go to a fixed 256 KiB array of
+ * statistics (and, where they leave room, what a large batch's scan in parts and a small batch's draw keep) go to a fixed 256 KiB array of
  * device memory inside the library (one copy per GPU, held until the process ends); the call allocates nothing and frees nothing.  Limit: T <= 16384 packed rows (the array holds 16384 row-segment
  * statistics, and T rows are scanned in at most ceil(8192 / T) segments each); beyond it the call fails with
  * SLED_EINVAL and sled_accept is the one to use.  All calls
