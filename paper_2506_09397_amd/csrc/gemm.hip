@@ -1,8 +1,9 @@
 // Projections of the verify step: out[T, N] = X[T, K] * W[N, K]^T over the packed rows of a batch.
 //
-// Two kernels share the work of bf16 models.  16-bit weights run in gemm_tile_kernel (both operands through LDS; described there);
-// 8- and 4-bit weights, batch-invariant models, 65 to 96 rows (three row tiles), and the LM head at 97 to 128 rows run in
-// gemm_bf16_kernel, which the following describes.
+// Three kernels share the work of bf16 models.  Up to 32 rows (and 4-bit weights up to 64 where K is long) run in gemm_kwave_kernel (both
+// operands straight to registers, the k-steps dealt out to the wavefronts); 16-bit weights beyond that in gemm_tile_kernel (both
+// operands through LDS); both are described there.  8- and 4-bit weights, batch-invariant models, 65 to 96 rows (three row tiles), and
+// the LM head at 97 to 128 rows run in gemm_bf16_kernel, which the following describes.
 //
 // bf16 path (the one that matters): T is about 100-600 packed rows, so every weight byte is used
 // for only T multiply-adds and the kernel is a weight stream bounded by HBM.  It is still a dense
@@ -482,11 +483,10 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(const bf16_t* __r
 //     no sums to exchange at the end; and its height can follow the batch (tile_height).  Gate/up of 372 rows x 4096
 //     x 28672: 185 -> 138 us; of 700 rows: 290 -> 270 us = 1.22 PFLOP/s executed (both planes), where a large library
 //     product on the same card reaches 1.41.
-//   - One block of rows (up to 128) runs in a slim tile, RT x 32 rows by 128 columns with two k-steps per stage: as many
+//   - One block of 33 to 128 rows runs in a slim tile, RT x 32 rows by 128 columns with two k-steps per stage: as many
 //     workgroups as the narrow shape above and the same K slices, but no k-group sums to exchange at the end, a cost that a
 //     launch of 15 to 60 us feels.  101 rows: gate/up 62.5 -> 61.3, QKV 22.7 -> 20.1 us; 8 layers and the head of the 8B
-//     shape 1.54-1.62 -> 1.45-1.55 ms from card to card, at 20 rows 1.08 -> 1.05, at one 1.03 -> 1.01.  With one row tile the four
-//     wavefronts take a column tile each instead of quarters.  Three row tiles do not run here: they divide into column quarters
+//     shape 1.54-1.62 -> 1.45-1.55 ms from card to card.  Three row tiles do not run here: they divide into column quarters
 //     only, which read 28 KiB of LDS per k-step for 24 MFMAs (four tiles 24 for 32), and whether that is ahead of the narrow
 //     shape depends on the card: 8 layers and the head at 84 rows 1.36 against 1.42 ms on one, 1.49 against 1.47 on another,
 //     a prompt of 66 tokens 1.28 against 1.32 and 1.39 against 1.35.  (Dealt out as 2 + 1 row tiles it is the narrow shape's
@@ -494,18 +494,16 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(const bf16_t* __r
 // Loads and waits are written by hand as above; all vector-memory operations of the loop are direct-to-LDS loads, so
 // no register is ever the target of a load in flight.
 constexpr int TILE_WAVES = 4, TILE_CT = 8;
-constexpr int SLIM_CT = 4, SLIM_U = 2;   // one block of up to 128 rows: see below
+constexpr int SLIM_CT = 4, SLIM_U = 2;
 constexpr int tile_stage_kib(int RT, int CT, int U) { return (PLANES * RT + CT) * U; }
 // K is dealt out to the slices in units of 8 k-steps; a slice holds at least two units, so never fewer stages than the ring
 constexpr int TILE_UNIT = 8, TILE_MIN_STAGES = 16;
 static_assert(NARROW_KG * NBUF >= TILE_MIN_STAGES, "sled_launch_gemm has at most K / (16 NARROW_KG NBUF) slices");
 // stages in the ring: what LDS holds, an even number, no more k-steps than the shortest slice has
 constexpr int tile_ring(int RT, int CT, int U) { return std::min(160 / tile_stage_kib(RT, CT, U) / 2 * 2, TILE_MIN_STAGES / U); }
-// wavefronts along the rows: quarters of 2 x 2 where the row tiles are even, four column quarters of one
-constexpr int tile_wave_rows(int RT) { return RT % 2 == 0 ? 2 : 1; }
-// a wavefront's sums, in tiles of 16 registers.  Up to eight of them (one or two row tiles) fit into the 256 registers of a launch bound
+// a wavefront's sums, in tiles of 16 registers.  Up to eight of them (two row tiles of the slim tile) fit into the 256 registers of a launch bound
 // of two wavefronts per SIMD, for which the compiler keeps MFMA results in ordinary registers: they are added up as they are,
-// where accumulation registers are read into ordinary ones first.  8 layers and the head at one row 1.026 -> 1.013 ms.
+// where accumulation registers are read into ordinary ones first.
 constexpr int tile_sums(int RT, int CT, int U) { return 2 * U * RT * CT / TILE_WAVES; }
 
 // RT, CT: row and column tiles of the workgroup; U: k-steps per stage
@@ -516,7 +514,7 @@ __global__ __launch_bounds__(64 * TILE_WAVES, tile_sums(RT, CT, U) <= 8 ? 2 : 1)
                                                                        float* __restrict__ out, bf16_t* __restrict__ out_act,
                                                                        size_t act_plane, int F_act) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int WR = tile_wave_rows(RT), WC = TILE_WAVES / WR;   // wavefronts along rows and columns
+    constexpr int WR = 2, WC = TILE_WAVES / WR;                // wavefronts along rows and columns
     constexpr int HR = RT / WR, HC = CT / WC;                  // row and column tiles of a wavefront's quarter
     constexpr int XT = PLANES * RT * U, ST = XT + CT * U;      // 1 KiB operand tiles per stage: activations [k-step][plane][row tile], then weights [k-step][column tile]
     constexpr int NB = tile_ring(RT, CT, U);                   // stages in the ring = stages in flight
@@ -731,6 +729,218 @@ __global__ __launch_bounds__(64 * TILE_WAVES, tile_sums(RT, CT, U) <= 8 ? 2 : 1)
     }
 }
 
+// ------------------------------------------------------------------------------------------ k-wave kernel
+// Up to 32 rows: few rows need few MFMAs, so what counts is that the weight stream never pauses and that a launch's fixed part is
+// short.  A workgroup of four wavefronts, one per SIMD, owns RT x 32 rows by 128 columns; the k-steps of its slice are dealt
+// out to the wavefronts in turn, and each multiplies its k-steps with all columns and all rows.  So no operand is needed by two
+// wavefronts: everything goes from memory to registers, SETS k-steps ahead, with no LDS, no barrier and no wait for another
+// wavefront in the loop, and the compiler counts the loads by itself.  The price is that the four sums of a result meet in LDS at
+// the end (64 KiB per row tile; writing them is what LDS is slowest at, 78 bytes per clock measured, 250 for reading).
+//   - Sum g of a result is that of the k-steps g, g + 4, ...; the four are added in ascending order: the sums of the narrow shape and of the
+//     slim tile, so a result does not depend on which kernel made it.
+//   - Measured inside the workgroups at one row, gate/up of 4096 x 28672: 1.4 us until the first loads are out, 29.4 us for the
+//     loop (8.0 TB/s while it runs), 1.6 us for the sums and SwiGLU, and 4.8 us for dispatch, the slowest workgroup and the end.
+//     Launch times, one row of 16-bit weights, slim tile of one row tile (which this replaced) against this: QKV 11.0 -> 11.2, O 9.6 -> 9.3,
+//     gate/up 38.9 -> 37.5, down 21.6 -> 21.1 us; 25 rows of 8-bit weights, narrow shape against this: 10.4 -> 10.0, 8.3 -> 7.5,
+//     27.5 -> 26.3, 16.9 -> 15.7; of 4-bit weights: 9.5 -> 8.9, 7.1 -> 6.9, 25.0 -> 21.0, 13.3 -> 13.0.
+//   - Four sets of operands in flight saturate the stream; eight delay a short slice's first k-step behind 28 others (QKV 11.2 -> 11.7,
+//     O 9.3 -> 10.0 us).  4-bit weights are the exception where a slice is long: the widening of a k-step's weights between the MFMAs
+//     of the step before asks for them a step earlier, and there are few bytes to a step (gate/up at 25 rows 22.2 -> 21.0, at 58 rows 34.2 -> 31.1).
+//   - More rows: at two row tiles 16- and 8-bit weights are no faster than in the kernels they have (gate/up 47.5 -> 49.0 and 35.8 -> 38.4), 4-bit
+//     weights are where the slice is long (35.2 -> 31.1; QKV 14.3 -> 14.0, O 10.2 -> 10.4, down 19.6 -> 19.0 are left alone).
+//     Three row tiles lose everywhere (54.4 -> 57.3), four do not fit into the registers.
+constexpr int KW_CT = 4, KW_WAVES = 4;
+constexpr int KW_MIN_STEPS = 16;     // k-steps of a slice come in multiples of this
+constexpr int KW_DEEP_STEPS = 256;   // 4-bit slices from here on are long: the 8B shape's gate/up and LM head have 256, its down projection 112
+constexpr int kw_lds(int RT) { return KW_WAVES * KW_CT * RT * 4096; }
+
+// SETS: k-steps whose operands are in registers or on their way
+template <int RT, int WB, int SETS>
+__global__ __launch_bounds__(64 * KW_WAVES, 1) void gemm_kwave_kernel(const bf16_t* __restrict__ Xp, size_t x_plane,
+                                                                      const unsigned char* __restrict__ Wp, const void* __restrict__ scale_v,
+                                                                      int NT, int KS, int n_col, int n_split, int T, int T_pad, int N,
+                                                                      float* __restrict__ out, bf16_t* __restrict__ out_act,
+                                                                      size_t act_plane, int F_act, int epi) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int TB = 64 * WB;                        // bytes of a 32 x 16 weight tile
+    constexpr int WL = WB == 16 ? 4 : 2;               // weight loads per k-step: a tile, or a pair of tiles
+    constexpr int WR = WB == 4 ? 2 : 4;                // ... and their registers
+    const int tid = threadIdx.x, lane = tid & 63, g = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int by = blockIdx.x / n_col, bx = blockIdx.x - by * n_col;
+    const int len = KS / n_split;                      // k-steps of a slice: a multiple of KW_MIN_STEPS (the host sees to it)
+    const int ks0 = by * len + g, n = len / KW_WAVES;  // this wavefront's: ks0, ks0 + 4, ...
+    const int nt_base = bx * KW_CT;
+
+    const size_t rowb = (size_t)NT * TB;               // bytes of a k-step of the whole matrix
+    const char* wsrc = reinterpret_cast<const char*>(Wp) + (size_t)ks0 * rowb;
+    const char* ssrc = WB == 4 ? static_cast<const char*>(scale_v) + (size_t)(ks0 >> 1) * (NT / 2) * 64 : nullptr;
+    unsigned woff[WL], soff[WL];
+#pragma unroll
+    for (int i = 0; i < WL; i++) {   // column tiles past the last one re-read it; their results are not stored
+        if (WB == 16)
+            woff[i] = min(nt_base + i, NT - 1) * 1024 + lane * 16;
+        else {
+            const int pair = min(nt_base / 2 + i, NT / 2 - 1);
+            woff[i] = pair * (2 * TB) + lane * (TB / 32);
+            soff[i] = pair * 64 + (lane & 31) * 2;
+        }
+    }
+    const int row_lim = (T + 7) & ~7;
+    const char* xsrc[2];
+    unsigned xoff[RT];
+#pragma unroll
+    for (int pl = 0; pl < 2; pl++) xsrc[pl] = reinterpret_cast<const char*>(Xp + pl * x_plane + (size_t)ks0 * 512);
+#pragma unroll
+    for (int b = 0; b < RT; b++) {
+        // lanes past the last token re-read the tile's first line (see gemm_bf16_kernel)
+        const int src_lane = b * 32 + (lane & 31) < row_lim ? lane : (lane & 32) + (lane & 7);
+        xoff[b] = (unsigned)b * KS * 1024 + src_lane * 16;
+    }
+    typedef __attribute__((__vector_size__(WR * sizeof(unsigned)))) unsigned wreg_t;
+    struct operands {
+        bf16x8_t x[2][RT];
+        wreg_t w[WL];
+        uint32_t sc[WB == 4 ? WL : 1];
+    } set[SETS];
+    auto load_x = [&](operands& o, int pl, int b, int s) {
+        o.x[pl][b] = *reinterpret_cast<const bf16x8_t*>(xsrc[pl] + (size_t)s * (KW_WAVES * 1024) + xoff[b]);
+    };
+    auto load_w = [&](operands& o, int i, int s) {
+        o.w[i] = __builtin_nontemporal_load(reinterpret_cast<const wreg_t*>(wsrc + (size_t)s * KW_WAVES * rowb + woff[i]));
+        if (WB == 4) o.sc[i] = *reinterpret_cast<const uint16_t*>(ssrc + (size_t)s * (KW_WAVES / 2) * (NT / 2) * 64 + soff[i]);
+    };
+
+    float16_t acc[KW_CT][RT];
+#pragma unroll
+    for (int a = 0; a < KW_CT; a++)
+#pragma unroll
+        for (int b = 0; b < RT; b++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) acc[a][b][e] = 0.f;
+    auto widened = [&](const operands& o, int a) {
+        const wreg_t& w = o.w[WB == 16 ? a : a / 2];
+        if constexpr (WB == 16)
+            return __builtin_bit_cast(bf16x8_t, w);
+        else if constexpr (WB == 8)
+            return a & 1 ? cvt_w8(w[2], w[3]) : cvt_w8(w[0], w[1]);
+        else
+            return cvt_w4(w[a & 1], __uint_as_float(((o.sc[a / 2] >> (8 * (a & 1))) & 0xffu) << 23));
+    };
+    // One k-step with the operands in `o`: the loads of the step four further on go into the registers as they fall free, and the
+    // next step's weights (in `nx`) are widened between the MFMAs.
+    bf16x8_t wb[2][KW_CT];
+    auto compute = [&](operands& o, const operands& nx, auto par_c, bool more, bool widen, int s_next) {
+        constexpr int PAR = decltype(par_c)::value;
+#pragma unroll
+        for (int pl = 0; pl < 2; pl++)
+#pragma unroll
+            for (int b = 0; b < RT; b++) {
+                constexpr int GROUPS = 2 * RT, PER = (KW_CT + GROUPS - 1) / GROUPS;
+                const int grp = pl * RT + b;
+#pragma unroll
+                for (int a = 0; a < KW_CT; a++) {
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(WB == 16 ? widened(o, a) : wb[PAR][a], o.x[pl][b], acc[a][b], 0, 0, 0);
+                    if (WB != 16 && widen && a < PER && grp * PER + a < KW_CT) {
+                        wb[PAR ^ 1][grp * PER + a] = widened(nx, grp * PER + a);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+                if (more) load_x(o, pl, b, s_next);
+                if (WB != 16 && more && grp == 0) {
+#pragma unroll
+                    for (int i = 0; i < WL; i++) load_w(o, i, s_next);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        if (WB == 16 && more) {
+#pragma unroll
+            for (int i = 0; i < WL; i++) load_w(o, i, s_next);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    using std::integral_constant;
+    // four k-steps with the operands in sets BASE .. BASE + 3; those of SETS steps further on are requested if `more`
+    auto trip = [&](auto base_c, bool more, int s) {
+        constexpr int B0 = decltype(base_c)::value;
+#pragma unroll
+        for (int j = 0; j < 4; j += 2) {
+            compute(set[B0 + j], set[(B0 + j + 1) % SETS], integral_constant<int, 0>{}, more, true, s + j + SETS);
+            compute(set[B0 + j + 1], set[(B0 + j + 2) % SETS], integral_constant<int, 1>{}, more, true, s + j + 1 + SETS);
+        }
+    };
+    auto request = [&](auto base_c, int s) {
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            operands& o = set[decltype(base_c)::value + j];
+#pragma unroll
+            for (int i = 0; i < WL; i++) load_w(o, i, s + j);
+#pragma unroll
+            for (int pl = 0; pl < 2; pl++)
+#pragma unroll
+                for (int b = 0; b < RT; b++) load_x(o, pl, b, s + j);
+        }
+    };
+    typedef integral_constant<int, 0> low;
+    typedef integral_constant<int, SETS - 4> high;
+    static_assert(SETS == 4 || SETS == 8, "the trips are written for one or two halves of four sets");
+    request(low{}, 0);
+    if (SETS == 8 && n > 4) request(high{}, 4);
+    if (WB != 16) {
+#pragma unroll
+        for (int a = 0; a < KW_CT; a++) wb[0][a] = widened(set[0], a);
+    }
+    int s = 0;
+    if constexpr (SETS == 4) {
+        for (; s + 4 < n; s += 4) trip(low{}, true, s);
+        trip(low{}, false, s);
+    } else {
+        for (; s + 12 < n; s += 8) {
+            trip(low{}, true, s);
+            trip(high{}, true, s + 4);
+        }
+        // 4, 8 or 12 steps are left
+        const bool third = s + 8 < n;
+        trip(low{}, third, s);
+        if (s + 4 < n) trip(high{}, false, s);
+        if (third) trip(low{}, false, s);
+    }
+
+    // The wavefronts' sums meet in LDS: wavefront g adds up column tile g, in ascending order
+    float4_t* red = reinterpret_cast<float4_t*>(smem) + lane;
+    const int nt = nt_base + g;
+    float4_t sc[4];
+    if (WB == 8 && nt < NT) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) sc[q] = *reinterpret_cast<const float4_t*>(static_cast<const float*>(scale_v) + nt * 32 + q * 8 + (lane >> 5) * 4);
+    }
+#pragma unroll
+    for (int a = 0; a < KW_CT; a++)
+#pragma unroll
+        for (int b = 0; b < RT; b++)
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                red[(((a * KW_WAVES + g) * RT + b) * 4 + q) * 64] = float4_t{acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]};
+    __syncthreads();
+    if (nt >= NT) return;
+#pragma unroll
+    for (int b = 0; b < RT; b++) {
+        const int tok = b * 32 + (lane & 31);
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            float4_t v = red[((g * KW_WAVES * RT + b) * 4 + q) * 64];
+#pragma unroll
+            for (int src = 1; src < KW_WAVES; src++) v += red[(((g * KW_WAVES + src) * RT + b) * 4 + q) * 64];
+            if (WB == 8) v *= sc[q];
+            const int n0 = nt * 32 + q * 8 + (lane >> 5) * 4;
+            if (tok >= T) continue;   // padding rows are never read
+            if (epi == SLED_EPI_SWIGLU)
+                store_cols<SLED_EPI_SWIGLU>(v, tok, n0, by, T_pad, N, out, out_act, act_plane, F_act);
+            else   // finished values are slice 0 of one
+                store_cols<SLED_EPI_PARTIAL>(v, tok, n0, by, T_pad, N, out, out_act, act_plane, F_act);
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------------ fp32
 // out[t][n] = sum_k X[t][k] W[n][k].  fp32 models are small, so a launch is a chain of memory round trips, not a stream: the
 // work is cut fine and the chain kept short.  Workgroup = 16 tokens x 8 columns; the lanes of a wavefront lie along k (256 of it
@@ -845,6 +1055,21 @@ int launch_tile_one(const gemm_args& a) {
     }
     hipLaunchKernelGGL(kern, a.grid, dim3(64 * TILE_WAVES), a.lds, a.st, a.X, a.x_plane, a.W, a.NT, a.KS, a.n_col, a.n_split, a.n_zb,
                        a.T, a.T_pad, a.N, a.out, a.out_act, a.act_plane, a.F_act);
+    SLED_LAUNCH_CHECK();
+    return SLED_OK;
+}
+
+template <int RT, int WB, int SETS>
+int launch_kwave(int epi, const gemm_args& a) {
+    static bool allowed = false;
+    auto kern = gemm_kwave_kernel<RT, WB, SETS>;
+    if (!allowed) {
+        SLED_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kw_lds(RT)));
+        allowed = true;
+    }
+    hipLaunchKernelGGL(kern, dim3(a.n_col * a.n_split), dim3(64 * KW_WAVES), kw_lds(RT), a.st, a.X, a.x_plane,
+                       reinterpret_cast<const unsigned char*>(a.W), a.scale, a.NT, a.KS, a.n_col, a.n_split, a.T, a.T_pad, a.N, a.out,
+                       a.out_act, a.act_plane, a.F_act, epi);
     SLED_LAUNCH_CHECK();
     return SLED_OK;
 }
@@ -972,7 +1197,7 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
         if (N % 32 || K % 16 || T_pad % 32 || plan.split < 1 || KS % (NARROW_KG * NBUF) || plan.split > KS / (NARROW_KG * NBUF))   // a slice is never shorter than a trip of the narrow shape and than the tile kernel's ring
             SLED_FAIL(SLED_EINVAL, "gemm: unsupported shape N=%d K=%d T_pad=%d split=%d", N, K, T_pad, plan.split);
         const int mt_total = T_pad / 32;
-        // up to 128 rows (4 tiles): slim tile (16-bit weights, not three tiles) or narrow shape with exactly these tiles; more: the tile kernel at the height that suits
+        // up to 128 rows (4 tiles): k-wave kernel (one tile), slim tile (16-bit weights, two or four tiles) or narrow shape with exactly these tiles; more: the tile kernel at the height that suits
         // (bf16 weights) or blocks of four tiles in the wide shape (8- and 4-bit weights); the last block may reach past the end
         // (a batch-invariant model keeps the narrow shape at every size: the two shapes add the k-steps up in
         // different groupings, so a row's sums would depend on whether its batch has more than 128 rows)
@@ -1018,13 +1243,27 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
         }
         if (wide)
             return m->wbits == 8 ? launch_epi_wb<4, WIDE_KG, WIDE_CG, 8>(epilogue, a) : launch_epi_wb<4, WIDE_KG, WIDE_CG, 4>(epilogue, a);
-        // one block of rows, 16-bit weights: the slim tile kernel (three row tiles: the narrow shape)
+        // up to 32 rows, and 4-bit weights up to 64 in long slices: the k-wave kernel (whose results do not depend on the choice either,
+        // so batch-invariant models take it too)
+        const int slice = KS / plan.split;   // whole and equal for every plan of one block of rows
+        if (mt_total <= 2 && KS % plan.split == 0 && slice % KW_MIN_STEPS == 0) {
+            const bool deep = m->wbits == 4 && slice >= KW_DEEP_STEPS;
+            a.n_col = (NT + KW_CT - 1) / KW_CT;
+            if (mt_total == 1) {
+                switch (m->wbits) {
+                    case 8: return launch_kwave<1, 8, 4>(epilogue, a);
+                    case 4: return deep ? launch_kwave<1, 4, 8>(epilogue, a) : launch_kwave<1, 4, 4>(epilogue, a);
+                    default: return launch_kwave<1, 16, 4>(epilogue, a);
+                }
+            }
+            if (deep) return launch_kwave<2, 4, 8>(epilogue, a);
+        }
+        // one block of 33 or more rows, 16-bit weights: the slim tile kernel (three row tiles: the narrow shape)
         if (!wide && !broad && MT != 3 && m->wbits == 16 && !m->batch_invariant) {
             a.n_col = (NT + SLIM_CT - 1) / SLIM_CT;
             a.grid = dim3((a.n_col * a.n_split + 7) / 8 * 8, 1, 1);
             a.lds = (size_t)tile_ring(MT, SLIM_CT, SLIM_U) * tile_stage_kib(MT, SLIM_CT, SLIM_U) * 1024;
             switch (MT) {
-                case 1: return launch_tile<1, SLIM_CT, SLIM_U>(epilogue, a);
                 case 2: return launch_tile<2, SLIM_CT, SLIM_U>(epilogue, a);
                 default: return launch_tile<4, SLIM_CT, SLIM_U>(epilogue, a);
             }
