@@ -897,6 +897,7 @@ int run_forward(sled_model* m, sled_kvpool* p, const std::vector<step_entry>& en
     meta.B = B;
     meta.T = T;
     meta.n_work = n_work;
+    meta.n_pages = total_pages;
 
     char* ws = static_cast<char*>(workspace);
     float* h = reinterpret_cast<float*>(ws + wp.h);

@@ -34,6 +34,8 @@
 // fp32 kernel (fp32 models): one wavefront per (row, query head), lanes over keys.
 #include "sled_internal.h"
 
+#include <type_traits>
+
 namespace {
 
 constexpr float NEG_BIG = -1.0e30f;
@@ -56,7 +58,7 @@ __global__ __launch_bounds__(64 * (QT + 1) * attn_groups(QT)) void attn_bf16_ker
     const int32_t* __restrict__ kvslot, const int32_t* __restrict__ plan, bf16_t* k_pool, bf16_t* v_pool, int64_t n_pages,
     int layer, int Hq, int Hkv,
     float scale_log2, float* __restrict__ part_o, float* __restrict__ part_ml, int32_t* __restrict__ arrive,
-    bf16_t* __restrict__ X, size_t x_plane) {
+    bf16_t* __restrict__ X, size_t x_plane, bool stream) {
     constexpr int D = 128, NPG = attn_groups(QT), RING = ATTN_RING;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ int sh_last;
@@ -250,12 +252,19 @@ __global__ __launch_bounds__(64 * (QT + 1) * attn_groups(QT)) void attn_bf16_ker
         const size_t base = (((size_t)layer * n_pages + phys) * Hkv + g) * (16 * D);
         const bf16_t* kg = k_pool + base + lane * 8;
         const bf16_t* vg = v_pool + base + lane * 8;
+        auto run = [&](auto stream_c) {
 #pragma unroll
-        for (int c = 0; c < 8; c++) {
-            const bf16_t* gp = (c < 4 ? kg : vg) + (c & 3) * 512;
-            const unsigned dst = __builtin_amdgcn_readfirstlane(ring_lds + (unsigned)(slot * 8192 + c * 1024));
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gp), "s"(dst) : "memory");
-        }
+            for (int c = 0; c < 8; c++) {
+                const bf16_t* gp = (c < 4 ? kg : vg) + (c & 3) * 512;
+                const unsigned dst = __builtin_amdgcn_readfirstlane(ring_lds + (unsigned)(slot * 8192 + c * 1024));
+                if (decltype(stream_c)::value)
+                    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(gp), "s"(dst) : "memory");
+                else
+                    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gp), "s"(dst) : "memory");
+            }
+        };
+        if (stream) run(std::true_type{});
+        else run(std::false_type{});
     };
     auto process = [&](int slot, int pg) {
         bf16x8_t kf[4];
@@ -596,6 +605,12 @@ int sled_launch_attention(const sled_model* m, const sled_kvpool* p, const sled_
         const size_t lds = sled_attn_lds_bytes(QT);
         dim3 grid(meta.n_work), blk(64 * (QT + 1) * attn_groups(QT));
         const bool fused = qkv_partial != nullptr;
+        // From about 64 MiB of K and V a launch on they are loaded past the caches' replacement order (nt): a layer of 512 MB (64 requests
+        // of 128 to 8192 tokens) takes 94.4 instead of 105 us and leaves the following row kernel 11.8 instead of 13.6, one of 88 MB
+        // 32.0 instead of 33.0; below, it gains nothing (47 MB: 26.3 either way, and the projection behind it 11.3 instead of 10.1) or loses what
+        // Infinity Cache would keep from step to step (one request of 1000 tokens, 131 MB in all layers: 15.9 instead of 15.2).
+        // (Blocks of a prompt read each other's pages, from L2 for the most part.)
+        const bool stream = fused && meta.n_pages * (2ll * s.n_kv_heads * 16 * s.head_dim * 2) >= (64ll << 20);
 #define SLED_ATTN_LAUNCH(N, F)                                                                                       \
     {                                                                                                                \
         static bool allowed = false;                                                                                 \
@@ -608,7 +623,7 @@ int sled_launch_attention(const sled_model* m, const sled_kvpool* p, const sled_
                            q_plane, qkv_partial, n_split, T_pad, reinterpret_cast<const float2*>(cs), kvslot, plan,  \
                            static_cast<bf16_t*>(p->k_pool), static_cast<bf16_t*>(p->v_pool), p->n_pages, layer,      \
                            s.n_q_heads, s.n_kv_heads, scale_log2, part_o, part_ml, arrive,                           \
-                           static_cast<bf16_t*>(X_out), x_plane);                                                    \
+                           static_cast<bf16_t*>(X_out), x_plane, stream);                                            \
     }
 #define SLED_ATTN_CASE(N)                \
     case N:                              \

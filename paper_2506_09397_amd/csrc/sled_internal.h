@@ -224,6 +224,7 @@ struct sled_step_meta {
     const int32_t* work;       // [n_work * 4]  attention work items: batch index, kv head, first page, n pages
     const int32_t* cu_work;    // [B*Hkv][2]    first and end work item of each (batch index, kv head)
     int B, T, n_work;
+    int64_t n_pages;           // entries of `pages`: what one layer's attention reads at least once
 };
 
 // ------------------------------------------------------------------------------------------
