@@ -834,19 +834,23 @@ int run_forward(sled_model* m, sled_kvpool* p, const std::vector<step_entry>& en
     if (!m->batch_invariant) std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return np_all[a] > np_all[b]; });
     const int tgt = m->batch_invariant ? 0 : attn_pages_per_item(np_all, order, Hkv);
     std::vector<int32_t> work;
-    std::vector<int32_t> cu_work(2 * B * Hkv);   // first and end item of (block, kv head), by block and head
+    // first item of (block, kv head) and how many there are, Hkv places apart: the items of a pair all read the same q rows, and with a
+    // multiple of eight heads they run on one XCD and share its L2
+    std::vector<int32_t> cu_work(2 * B * Hkv);
     for (int i : order) {
         const int np = np_all[i];
         const int chunk = m->batch_invariant ? SLED_FIXED_CHUNK_PAGES : attn_chunk(np, tgt);
-        for (int g = 0; g < Hkv; g++) {
-            cu_work[2 * (i * Hkv + g)] = (int)(work.size() / 4);
-            for (int p0 = 0; p0 < np; p0 += chunk) {
+        const int first = (int)(work.size() / 4);
+        for (int p0 = 0; p0 < np; p0 += chunk)
+            for (int g = 0; g < Hkv; g++) {
                 work.push_back(i);
                 work.push_back(g);
                 work.push_back(p0);
                 work.push_back(std::min(chunk, np - p0));
             }
-            cu_work[2 * (i * Hkv + g) + 1] = (int)(work.size() / 4);
+        for (int g = 0; g < Hkv; g++) {
+            cu_work[2 * (i * Hkv + g)] = first + g;
+            cu_work[2 * (i * Hkv + g) + 1] = ceil_div(np, chunk);
         }
     }
     const int n_work = (int)(work.size() / 4);

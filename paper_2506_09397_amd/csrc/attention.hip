@@ -31,6 +31,13 @@
 // the cache pages (the work item that holds a row's page does), while the producers already stream the context
 // pages, which depend on none of this.  Only the pages that hold new rows wait for those stores.
 //
+// A launch for a few requests is a chain of round trips to the memory side, about 1 us each, and of work that one wavefront does while
+// the others wait, so both are kept short: everything the prologue looks up is asked for together, the page groups share the adding
+// up of their states by dims, and the merge asks for all states of up to four items before it uses the first.  Clocks of one workgroup before
+// and after (25 rows, 128 workgroups): prologue 7300 -> 5300, page loop 11600 -> 11100, fold 3100 -> 2400, store and arrival 4100 ->
+// 2400, merge by the last one 15200 -> 4100.  Per layer of the 8B shape: one row 14.8 -> 10.6 us, 25 rows 20.4 -> 15.5, 58 rows 26.1 ->
+// 20.5, 101 rows 31.3 -> 25.7 (26.5 before the items of a pair shared an XCD); 372 rows, where the page loop is nearly all, 93.8 -> 92.5.
+//
 // fp32 kernel (fp32 models): one wavefront per (row, query head), lanes over keys.
 #include "sled_internal.h"
 
@@ -47,6 +54,15 @@ constexpr float NEG_BIG = -1.0e30f;
 // issues in order and a direct-to-LDS load can hold the issue slot for a couple of hundred clocks.
 __host__ __device__ constexpr int attn_groups(int QT) { return QT <= 3 ? 4 : (QT == 4 ? 3 : 2); }
 constexpr int ATTN_RING = 3;  // page buffers per page group: the one being read and two in flight
+
+// the largest of x over the lanes l, l ^ 16, l ^ 32, l ^ 48: two exchanges between halves of the registers, without the LDS round trip that a
+// shuffle takes (it sits in the chain of every page)
+__device__ __forceinline__ float max_over_groups(float x) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
 
 // floats of one parked state in LDS: O tile [8][64 lanes][4] + max[16] + sum[16]
 constexpr int ATTN_PARK_F = 8 * 64 * 4 + 32;
@@ -118,13 +134,18 @@ __global__ __launch_bounds__(64 * (QT + 1) * attn_groups(QT)) void attn_bf16_ker
             int jr[2], ci[2];     // row (q: query row of the tile set; k, v: row of the request), quad / group index
             const float* src[2];  // first element of the item in K slice 0 (second quad of a rotary item 64 further)
             float4 acc[2][2];
+            // the angles of a rotary item and the place of a k or v row in the cache are asked for here, ahead of the sums: each
+            // look-up behind them would cost a round trip of its own
+            float4 ang[2][2];
+            int place[2];
 #pragma unroll
             for (int u = 0; u < 2; u++) {
                 const int it = it0 + u * nc;
                 kind[u] = -1;
                 jr[u] = ci[u] = 0;
                 src[u] = qkv_partial;
-                acc[u][0] = acc[u][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+                acc[u][0] = acc[u][1] = ang[u][0] = ang[u][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+                place[u] = 0;
                 if (it < NQ) {
                     jr[u] = it >> 4;
                     ci[u] = it & 15;
@@ -144,6 +165,17 @@ __global__ __launch_bounds__(64 * (QT + 1) * attn_groups(QT)) void attn_bf16_ker
                         src[u] = qkv_partial + (size_t)(row0 + jr[u]) * n_qkv + (Hq + (isk ? 0 : Hkv) + g) * D + 4 * ci[u];
                     }
                 }
+            }
+#pragma unroll
+            for (int u = 0; u < 2; u++) {
+                const int it = it0 + u * nc;
+                const int t = row0 + (it < NQ ? jr[u] / G : jr[u]);
+                if (kind[u] == 0 || kind[u] == 1) {
+                    const float4* a = reinterpret_cast<const float4*>(cs + (size_t)t * (D / 2) + 4 * ci[u]);
+                    ang[u][0] = a[0];
+                    ang[u][1] = a[1];
+                }
+                if (kind[u] > 0) place[u] = kvslot[t];
             }
             for (int sp0 = 0; sp0 < n_split; sp0 += 4) {   // K slices in ascending order, four at a time
                 float4 v[2][4][2];
@@ -178,9 +210,7 @@ __global__ __launch_bounds__(64 * (QT + 1) * attn_groups(QT)) void attn_bf16_ker
                     // q quad -> the tile's operand image in LDS: row r = qt'*16 + lq', dim d -> [plane][d/32][lane (d%32/8)*16 + lq'][d%8]
                     uint32_t h1[2] = {0u, 0u}, l1[2] = {0u, 0u}, h2[2] = {0u, 0u}, l2[2] = {0u, 0u};
                     if (kind[u] == 0) {
-                        const int j = jr[u] / G;
-                        const float4 c01 = *reinterpret_cast<const float4*>(cs + (size_t)(row0 + j) * (D / 2) + 4 * ci[u]);
-                        const float4 c23 = *reinterpret_cast<const float4*>(cs + (size_t)(row0 + j) * (D / 2) + 4 * ci[u] + 2);
+                        const float4 c01 = ang[u][0], c23 = ang[u][1];
                         const float cc[4] = {c01.x, c01.z, c23.x, c23.z}, ss[4] = {c01.y, c01.w, c23.y, c23.w};
                         float y1[4], y2[4];
 #pragma unroll
@@ -203,14 +233,13 @@ __global__ __launch_bounds__(64 * (QT + 1) * attn_groups(QT)) void attn_bf16_ker
                     *reinterpret_cast<uint2*>(base + (0 * 4 + ks + 2) * 512) = make_uint2(h2[0], h2[1]);
                     *reinterpret_cast<uint2*>(base + (1 * 4 + ks + 2) * 512) = make_uint2(l2[0], l2[1]);
                 } else if (kind[u] == 1) {
-                    const int t = row0 + jr[u], i = 4 * ci[u];
-                    const float4 c01 = *reinterpret_cast<const float4*>(cs + (size_t)t * (D / 2) + i);
-                    const float4 c23 = *reinterpret_cast<const float4*>(cs + (size_t)t * (D / 2) + i + 2);
+                    const int i = 4 * ci[u];
+                    const float4 c01 = ang[u][0], c23 = ang[u][1];
                     const float cc[4] = {c01.x, c01.z, c23.x, c23.z}, ss[4] = {c01.y, c01.w, c23.y, c23.w};
                     float y1[4], y2[4];
 #pragma unroll
                     for (int e = 0; e < 4; e++) rope_pair(x1[e], x2[e], cc[e], ss[e], y1[e], y2[e]);
-                    const int ps = kvslot[t];
+                    const int ps = place[u];
                     bf16_t* kp = k_pool + (((size_t)layer * n_pages + (ps >> 4)) * Hkv + g) * (16 * D);
                     // four neighbouring dims share an 8-byte piece of the page's operand order
                     *reinterpret_cast<uint2*>(kp + kpage_offset(ps & 15, i)) =
@@ -220,8 +249,8 @@ __global__ __launch_bounds__(64 * (QT + 1) * attn_groups(QT)) void attn_bf16_ker
                         make_uint2((uint32_t)f32_to_bf16(y2[0]) | ((uint32_t)f32_to_bf16(y2[1]) << 16),
                                    (uint32_t)f32_to_bf16(y2[2]) | ((uint32_t)f32_to_bf16(y2[3]) << 16));
                 } else if (kind[u] == 2) {
-                    const int t = row0 + jr[u], dd = 4 * ci[u];
-                    const int ps = kvslot[t];
+                    const int dd = 4 * ci[u];
+                    const int ps = place[u];
                     bf16_t* vp = v_pool + (((size_t)layer * n_pages + (ps >> 4)) * Hkv + g) * (16 * D);
 #pragma unroll
                     for (int e = 0; e < 4; e++) vp[vpage_offset(ps & 15, dd + e)] = f32_to_bf16(x1[e]);
@@ -293,8 +322,7 @@ __global__ __launch_bounds__(64 * (QT + 1) * attn_groups(QT)) void attn_bf16_ker
             }
         }
         float mloc = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+        mloc = max_over_groups(mloc);
         // The running reference is kept on whole numbers (scores are in log2 units), so every
         // rescale is an exact power of two and the rounding of p does not depend on the order in
         // which pages are visited: bf16(2^(s-M)) * 2^(M-M') == bf16(2^(s-M')).
@@ -401,78 +429,84 @@ __global__ __launch_bounds__(64 * (QT + 1) * attn_groups(QT)) void attn_bf16_ker
     // lane-partial sums -> per-qrow sums
     lsum += __shfl_xor(lsum, 16);
     lsum += __shfl_xor(lsum, 32);
-    // page groups 1 .. NPG-1 park their states in LDS; group 0 folds them in, in ascending order
-    // (exact: every rescale is a power of two)
-    float* park = reinterpret_cast<float*>(smem);
-    auto fold = [&](float m2, float l2, auto o2_of) {
-        const float mnew = fmaxf(m, m2);
-        const float a1 = exp2f(m - mnew), a2 = exp2f(m2 - mnew);
-        lsum = lsum * a1 + l2 * a2;
-        m = mnew;
-#pragma unroll
-        for (int dt = 0; dt < 8; dt++) {
-            const float4_t o2 = o2_of(dt);
-#pragma unroll
-            for (int i = 0; i < 4; i++) o[dt][i] = o[dt][i] * a1 + o2[i] * a2;
-        }
-    };
-    auto fold_groups = [&]() {  // called by every wavefront that is still alive
-        if (!producer && pgid > 0) {
-            float* slot = park + (size_t)((pgid - 1) * QT + qt) * ATTN_PARK_F;
+    // The page groups' states are added up in LDS, in ascending order (exact but for the additions: every rescale is a power of two).
+    // All groups share the work: group p adds up, and from here on owns, the dims of tiles dt0 .. dt0 + DPG - 1.
+    constexpr int DPG = (8 + NPG - 1) / NPG;
+    const int dt0 = pgid * DPG;
+    float4_t own[DPG];
+    {
+        float* park = reinterpret_cast<float*>(smem);
+        if (!producer) {
+            float* slot = park + (size_t)(pgid * QT + qt) * ATTN_PARK_F;
             if (lg == 0) {
                 slot[2048 + lq] = m;
                 slot[2048 + 16 + lq] = lsum;
             }
 #pragma unroll
-            for (int dt = 0; dt < 8; dt++) *reinterpret_cast<float4_t*>(slot + (dt * 64 + lane) * 4) = o[dt];
-        }
-        __syncthreads();
-        if (!producer && pgid == 0) {
-            for (int p2 = 1; p2 < NPG; p2++) {
-                const float* slot = park + (size_t)((p2 - 1) * QT + qt) * ATTN_PARK_F;
-                fold(slot[2048 + lq], slot[2048 + 16 + lq],
-                     [&](int dt) { return *reinterpret_cast<const float4_t*>(slot + (dt * 64 + lane) * 4); });
+            for (int dt = 0; dt < 8; dt++) {
+                if (dt / DPG == pgid)
+                    own[dt % DPG] = o[dt];
+                else
+                    *reinterpret_cast<float4_t*>(slot + (dt * 64 + lane) * 4) = o[dt];
             }
         }
-    };
-    fold_groups();
+        __syncthreads();
+        if (!producer) {
+            float gm[NPG], gl[NPG];
+            float4_t go[NPG][DPG];
+#pragma unroll
+            for (int p = 0; p < NPG; p++) {
+                const float* slot = park + (size_t)(p * QT + qt) * ATTN_PARK_F;
+                gm[p] = slot[2048 + lq];
+                gl[p] = slot[2048 + 16 + lq];
+#pragma unroll
+                for (int i = 0; i < DPG; i++)
+                    go[p][i] = p == pgid || dt0 + i >= 8 ? own[i] : *reinterpret_cast<const float4_t*>(slot + ((dt0 + i) * 64 + lane) * 4);
+            }
+            m = gm[0];
+#pragma unroll
+            for (int p = 1; p < NPG; p++) m = fmaxf(m, gm[p]);
+            lsum = 0.f;
+#pragma unroll
+            for (int i = 0; i < DPG; i++) own[i] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int p = 0; p < NPG; p++) {
+                const float f = exp2f(gm[p] - m);
+                lsum += gl[p] * f;
+#pragma unroll
+                for (int i = 0; i < DPG; i++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++) own[i][e] += go[p][i][e] * f;
+            }
+        }
+    }
 
-    // The wavefronts of page group 0 now hold the state of work item w, one query tile each.  If the
+    // The wavefronts now hold the state of work item w: wavefront (p, qt) the dims of group p for query tile qt.  If the
     // (request, kv head) has several work items, each stores its state; the one that arrives last
-    // merges them all in a fixed order (so the result does not depend on which one that is) and writes
-    // the output.  Reading a stored state is a round trip to the memory side, so the page groups share
-    // the merge: group p takes items p, p + NPG, ... in ascending order, then the groups are folded
-    // through LDS as above.
+    // merges them all in ascending order (so the result does not depend on which one that is) and writes the output.
     const int bg = b * Hkv + g;
-    const int w0 = rec[8], w1 = rec[9];
-    const bool single = (w1 - w0) == 1;
+    const int w0 = rec[8], n_items = rec[9];   // the pair's items: w0, w0 + Hkv, ...
+    const bool single = n_items == 1;
     // Cross-workgroup hand-over without a device-scope fence (which writes back and invalidates a whole
     // L2 and, with one per workgroup, serialises on each XCD): the partial states are written and read
     // with device-scope atomic accesses, which go to the memory-side coherence point themselves, and
     // the arrival counter is bumped only after this workgroup's stores have been acknowledged.
-    auto put = [&](float* q4, const float4_t& v) {  // 16 bytes at q4 as two 8-byte coherent stores
-        const uint2 a = make_uint2(__float_as_uint(v[0]), __float_as_uint(v[1])), c = make_uint2(__float_as_uint(v[2]), __float_as_uint(v[3]));
-        __hip_atomic_store(reinterpret_cast<unsigned long long*>(q4), __builtin_bit_cast(unsigned long long, a), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(reinterpret_cast<unsigned long long*>(q4) + 1, __builtin_bit_cast(unsigned long long, c), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    };
-    auto get = [&](const float* q4) {
-        const unsigned long long a = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(q4), __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-        const unsigned long long c = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(q4) + 1, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-        const uint2 a2 = __builtin_bit_cast(uint2, a), c2 = __builtin_bit_cast(uint2, c);
-        return float4_t{__uint_as_float(a2.x), __uint_as_float(a2.y), __uint_as_float(c2.x), __uint_as_float(c2.y)};
-    };
+    // A state is laid out as its lanes hold it, [query tile][dim tile][element][lane], so an access is 256 contiguous bytes; and
+    // such an access is a round trip of about 1 us to the memory side, so the merge asks for everything before it uses anything.
     if (!single) {
-        if (!producer && pgid == 0) {
-            if (lg == 0) {
+        float* const part = part_o + (size_t)w * (QT * 16 * D) + (size_t)(qt * 8 + dt0) * 256 + lane;
+        if (!producer) {
+            if (pgid == 0 && lg == 0) {
                 __hip_atomic_store(&part_ml[((size_t)w * 2 + 0) * (QT * 16) + r_mine], m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&part_ml[((size_t)w * 2 + 1) * (QT * 16) + r_mine], lsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
 #pragma unroll
-            for (int dt = 0; dt < 8; dt++) put(part_o + ((size_t)w * (QT * 16) + r_mine) * D + dt * 16 + lg * 4, o[dt]);
+            for (int i = 0; i < DPG; i++) {
+                if (dt0 + i >= 8) continue;
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+                    __hip_atomic_store(part + i * 256 + e * 64, own[i][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
             // every store above has been acknowledged before this wavefront reaches the barrier
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             __builtin_amdgcn_s_waitcnt(0);
@@ -480,7 +514,7 @@ __global__ __launch_bounds__(64 * (QT + 1) * attn_groups(QT)) void attn_bf16_ker
         __syncthreads();
         if (tid == 0) {
             const int old = __hip_atomic_fetch_add(&arrive[bg], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const int last = old == (w1 - w0 - 1);
+            const int last = old == n_items - 1;
             if (last) __hip_atomic_store(&arrive[bg], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next layer
             sh_last = last;
         }
@@ -490,15 +524,43 @@ __global__ __launch_bounds__(64 * (QT + 1) * attn_groups(QT)) void attn_bf16_ker
         m = NEG_BIG;
         lsum = 0.f;
 #pragma unroll
-        for (int dt = 0; dt < 8; dt++) o[dt] = float4_t{0.f, 0.f, 0.f, 0.f};
-        for (int ww = w0 + pgid; ww < w1; ww += NPG) {
-            const float m2 = __hip_atomic_load(&part_ml[((size_t)ww * 2 + 0) * (QT * 16) + r_mine], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const float l2 = __hip_atomic_load(&part_ml[((size_t)ww * 2 + 1) * (QT * 16) + r_mine], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            fold(m2, l2, [&](int dt) { return get(part_o + ((size_t)ww * (QT * 16) + r_mine) * D + dt * 16 + lg * 4); });
+        for (int i = 0; i < DPG; i++) own[i] = float4_t{0.f, 0.f, 0.f, 0.f};
+        constexpr int CH = DPG == 2 ? 4 : 2;   // items in flight
+        for (int c0 = 0; c0 < n_items; c0 += CH) {
+            float im[CH], il[CH], io[CH][DPG][4];
+#pragma unroll
+            for (int c = 0; c < CH; c++) {
+                // past the last item: that item again, with no weight
+                const int wc = w0 + min(c0 + c, n_items - 1) * Hkv;
+                im[c] = __hip_atomic_load(&part_ml[((size_t)wc * 2 + 0) * (QT * 16) + r_mine], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                il[c] = __hip_atomic_load(&part_ml[((size_t)wc * 2 + 1) * (QT * 16) + r_mine], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const float* src = part_o + (size_t)wc * (QT * 16 * D) + (size_t)(qt * 8) * 256 + lane;
+#pragma unroll
+                for (int i = 0; i < DPG; i++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++)
+                        io[c][i][e] = __hip_atomic_load(src + min(dt0 + i, 7) * 256 + e * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            float mnew = m;
+#pragma unroll
+            for (int c = 0; c < CH; c++) mnew = fmaxf(mnew, im[c]);
+            const float fo = exp2f(m - mnew);
+            m = mnew;
+            lsum *= fo;
+#pragma unroll
+            for (int i = 0; i < DPG; i++) own[i] *= fo;
+#pragma unroll
+            for (int c = 0; c < CH; c++) {
+                if (c0 + c >= n_items) continue;
+                const float f = exp2f(im[c] - m);
+                lsum += il[c] * f;
+#pragma unroll
+                for (int i = 0; i < DPG; i++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++) own[i][e] += io[c][i][e] * f;
+            }
         }
-        fold_groups();  // the barrier inside also orders group 0's earlier reads of the parking slots before these writes
-        if (pgid != 0) return;
-    } else if (producer || pgid != 0) {
+    } else if (producer) {
         return;
     }
     // normalise and write the attention output as a bf16 pair, in the operand order of the O
@@ -509,12 +571,13 @@ __global__ __launch_bounds__(64 * (QT + 1) * attn_groups(QT)) void attn_bf16_ker
     const int hh = r_mine - jrow * G;
     const int t = row0 + jrow;
 #pragma unroll
-    for (int dt = 0; dt < 8; dt++) {
-        const int col = (g * G + hh) * D + dt * 16 + lg * 4;
+    for (int i = 0; i < DPG; i++) {
+        if (dt0 + i >= 8) continue;
+        const int col = (g * G + hh) * D + (dt0 + i) * 16 + lg * 4;
         uint32_t hi2[2], lo2[2];
 #pragma unroll
         for (int e = 0; e < 2; e++) {
-            const float x0 = o[dt][2 * e] * inv, x1 = o[dt][2 * e + 1] * inv;
+            const float x0 = own[i][2 * e] * inv, x1 = own[i][2 * e + 1] * inv;
             const bf16_t h0 = f32_to_bf16(x0), h1 = f32_to_bf16(x1);
             hi2[e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
             lo2[e] = (uint32_t)f32_to_bf16(x0 - bf16_to_f32(h0)) | ((uint32_t)f32_to_bf16(x1 - bf16_to_f32(h1)) << 16);
@@ -591,7 +654,7 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(sled_step_meta meta, const
 size_t sled_attn_lds_bytes(int QT) {
     const int npg = attn_groups(QT);
     const size_t loop_bytes = (size_t)npg * ATTN_RING * 8192 + (size_t)QT * 8192;                  // page rings, q tiles (fused prologue)
-    const size_t merge_bytes = (size_t)(npg - 1) * QT * ATTN_PARK_F * sizeof(float);              // parked states
+    const size_t merge_bytes = (size_t)npg * QT * ATTN_PARK_F * sizeof(float);                    // parked states
     return loop_bytes > merge_bytes ? loop_bytes : merge_bytes;
 }
 

@@ -225,7 +225,7 @@ __global__ void rope_table_kernel(sled_step_meta meta, const int32_t* __restrict
 // page, gathered into one 48-byte record -- otherwise each of the step's attention launches starts with a chain of
 // four dependent look-ups (item -> block -> request -> committed length).
 //   [0] block  [1] kv head  [2] first page  [3] pages  [4] L = context length of the block  [5] rows of the block
-//   [6] first packed row  [7] first entry of the block's page list  [8], [9] items of this (block, kv head): first, end
+//   [6] first packed row  [7] first entry of the block's page list  [8], [9] items of this (block, kv head): the first (the others follow Hkv places apart), how many
 __global__ void attn_plan_kernel(sled_step_meta meta, const int32_t* __restrict__ len_dev, int Hkv, int32_t* __restrict__ plan) {
     const int w = blockIdx.x * blockDim.x + threadIdx.x;
     if (w >= meta.n_work) return;
