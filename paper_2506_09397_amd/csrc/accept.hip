@@ -1,7 +1,8 @@
 // Vocab-parallel acceptance (greedy match or speculative sampling, Eq. 1 of Sec. 3.1).
 //
 // Four kinds of kernel, the second and third for large and for small batches only:
-//   accept_row_stats   per row of logits (split over a few workgroups when the batch is small) the maximum, its
+//   accept_row_stats   (.. _first and _part where a large batch's rows are scanned in parts)
+//                      per row of logits (split over a few workgroups when the batch is small) the maximum, its
 //                      lowest index, and sum exp((z - max)/tau).  Pure HBM scan: four float4 loads in flight per
 //                      thread, wavefront reductions.
 //   accept_over        a large batch is scanned in up to four launches that take the requests' rows from the front; between
@@ -28,6 +29,12 @@ struct RowStat {
     double s;   // sum of exp((z - m) / tau) over the segment
     float m;    // maximum over the segment
     int idx;    // lowest index attaining it
+};
+
+// how the rows of a request are cut into segments: rows before `cut` into n0, the others into n1; `stride` statistics lie between two rows
+struct Split {
+    int n0, n1, cut, stride;
+    __host__ __device__ int of(int j) const { return j < cut ? n0 : n1; }
 };
 
 template <bool SAMPLE>
@@ -157,7 +164,7 @@ struct Judged {
 
 // The accept test of up to 64 drafts of one request at once: lane l judges draft j0+l+1 against row j0+l, for the rows
 // below jn (Eq. 1; in greedy mode equality with the row's argmax).
-__device__ inline Judged judge_rows(int mode, int row0, int d0, int j0, int jn, int V, int n_split, float inv_tau, double it,
+__device__ inline Judged judge_rows(int mode, int row0, int d0, int j0, int jn, int V, const Split& sp, float inv_tau, double it,
                                     const float* __restrict__ logits, const int32_t* __restrict__ tokens, const QSrc& draft_q,
                                     const float* __restrict__ u_acc, const RowStat* __restrict__ stats, int lane) {
     const int j = j0 + lane;
@@ -169,7 +176,7 @@ __device__ inline Judged judge_rows(int mode, int row0, int d0, int j0, int jn, 
         if (on) {
             int amax;
             double S;
-            row_stat(stats + (size_t)(row0 + j) * n_split, n_split, inv_tau, r.m, amax, S);
+            row_stat(stats + (size_t)(row0 + j) * sp.stride, sp.of(j), inv_tau, r.m, amax, S);
             r.fail = d != amax;
         }
         return r;
@@ -179,7 +186,7 @@ __device__ inline Judged judge_rows(int mode, int row0, int d0, int j0, int jn, 
     if (real) {
         int amax;
         double S;
-        row_stat(stats + (size_t)(row0 + j) * n_split, n_split, inv_tau, r.m, amax, S);
+        row_stat(stats + (size_t)(row0 + j) * sp.stride, sp.of(j), inv_tau, r.m, amax, S);
         r.zd = (double)zf;
         const double pd = exp((r.zd - (double)r.m) * it) / S;
         r.lhs = (double)u_acc[d0 + j] * qd;
@@ -209,7 +216,8 @@ __device__ inline float expf_nonpos(float a) {
 
 // statistics of elements v0 .. v1-1 of a row, by the whole workgroup of 256; the sum of exponentials only with SAMPLE, and for a
 // result of its own (SHOWN) by expf
-template <bool SAMPLE, bool SHOWN>
+// STREAM: rows of a batch that no cache holds are read past the replacement order.
+template <bool SAMPLE, bool SHOWN, bool STREAM = false>
 __device__ inline void scan_segment(const float* __restrict__ z, bool vec, int v0, int v1, float inv_tau, RowStat* __restrict__ dst) {
     auto e_to = [](float a) { return SHOWN ? expf(a) : expf_nonpos(a); };
     float m = -INFINITY;
@@ -250,7 +258,15 @@ __device__ inline void scan_segment(const float* __restrict__ z, bool vec, int v
 #pragma unroll
             for (int u = 0; u < 4; u++) {
                 const int vv = v + 256 * u;
-                q[u] = vv < e4 ? z4[vv] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+                q[u] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+                if (vv < e4) {
+                    if (STREAM) {
+                        const float4_t y = __builtin_nontemporal_load(reinterpret_cast<const float4_t*>(z4 + vv));
+                        q[u] = make_float4(y[0], y[1], y[2], y[3]);
+                    } else {
+                        q[u] = z4[vv];
+                    }
+                }
             }
             const float x[16] = {q[0].x, q[0].y, q[0].z, q[0].w, q[1].x, q[1].y, q[1].z, q[1].w,
                                  q[2].x, q[2].y, q[2].z, q[2].w, q[3].x, q[3].y, q[3].z, q[3].w};
@@ -299,43 +315,109 @@ __device__ inline void scan_segment(const float* __restrict__ z, bool vec, int v
 // Between two parts of the row scan: over[i] = 1 where one of request i's rows before jn, which the parts so far have scanned
 // (or left out behind a rejection that this test sees first), ends the prefix for certain.  A close test, which the finish
 // decides, ends nothing here.  One wavefront per request.
-__global__ __launch_bounds__(64) void accept_over(int mode, KPack kp, int jn, int V, int n_split, float inv_tau, float temperature,
+__global__ __launch_bounds__(64) void accept_over(int mode, KPack kp, int jn, int V, Split sp, float inv_tau, float temperature,
                                                   const float* __restrict__ logits, const int32_t* __restrict__ tokens, QSrc qsrc,
                                                   const float* __restrict__ u_acc, const RowStat* __restrict__ stats, int32_t* __restrict__ over) {
     const int i = blockIdx.x, lane = threadIdx.x;
     const int d0 = drafts_before(kp, i, lane);
-    const Judged jd = judge_rows(mode, d0 + i, d0, 0, min(jn, (int)kp.k[i]), V, n_split, inv_tau, 1.0 / (double)temperature, logits, tokens,
+    const Judged jd = judge_rows(mode, d0 + i, d0, 0, min(jn, (int)kp.k[i]), V, sp, inv_tau, 1.0 / (double)temperature, logits, tokens,
                                  qsrc, u_acc, stats, lane);
     const unsigned long long certain = __ballot(jd.fail && !jd.close);
     if (lane == 0) over[i] = certain != 0ull;
 }
 
-// rows j0 .. of every request: what one launch of the row scan takes when it works in parts
-struct RowPart {
-    int B, j0;
-    KPack kp;
-    const int32_t* over;   // accept_over's word on every request; not read for the part that starts at row 0
-};
-
-// blockIdx.x: the packed row; in parts request + B * (row of the request - j0).  (One workgroup for all of a request's rows of
-// a part would start fewer, but the few requests that are left do not fill the chip then: 93 us for rows 4 .. 8 of 256
-// requests.  Making the test in each workgroup instead of ahead of the launch: 59 us.)
-template <bool SAMPLE, bool PART, bool SHOWN = false>
+// blockIdx.x: the packed row
+template <bool SAMPLE, bool SHOWN = false>
 __global__ __launch_bounds__(256) void accept_row_stats(const float* __restrict__ logits, int V, int n_split, int seg,
-                                                        float inv_tau, std::conditional_t<PART, RowPart, int> part, RowStat* __restrict__ stats) {
+                                                        float inv_tau, RowStat* __restrict__ stats) {
     const int split = blockIdx.y;
     const int v0 = split * seg;
     const int v1 = min(V, v0 + seg);
     const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;   // (seg is a multiple of 4)
-    int row = blockIdx.x;
-    if constexpr (PART) {
-        // Workgroups go to the XCDs round robin, so with a batch of a multiple of eight all rows and segments of a request would
-        // meet on one of them, and of the later parts' few requests some XCDs get twice their share: turned by row and segment.
-        const int jj = row / part.B, i = (row - jj * part.B + jj + 3 * split) % part.B, j = part.j0 + jj;
-        if (j > part.kp.k[i] || (part.j0 > 0 && part.over[i])) return;
-        row = drafts_before(part.kp, i, threadIdx.x & 63) + i + j;
+    scan_segment<SAMPLE, SHOWN>(logits + (size_t)blockIdx.x * V, vec, v0, v1, inv_tau, stats + (size_t)blockIdx.x * n_split + split);
+}
+
+// The scan in parts.  The first: rows 0 .. of every request, blockIdx.x = request + B * row of the request.
+template <bool SAMPLE>
+__global__ __launch_bounds__(256) void accept_row_stats_first(const float* __restrict__ logits, int V, Split sp, float inv_tau, int B, KPack kp,
+                                                              RowStat* __restrict__ stats) {
+    const int split = blockIdx.y, seg = ((V + sp.n0 - 1) / sp.n0 + 3) & ~3;
+    const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;
+    // Workgroups go to the XCDs round robin, so with a batch of a multiple of eight all rows and segments of a request would
+    // meet on one of them: turned by row and segment.
+    const int j = blockIdx.x / B, i = (blockIdx.x - j * B + j + 3 * split) % B;
+    if (j > kp.k[i]) return;
+    const int row = drafts_before(kp, i, threadIdx.x & 63) + i + j;
+    const int v0 = min(V, split * seg), v1 = min(V, v0 + seg);
+    scan_segment<SAMPLE, false, true>(logits + (size_t)row * V, vec, v0, v1, inv_tau, stats + (size_t)row * sp.stride + split);
+}
+
+// The later parts: rows j0 .. j1-1 of the requests that no test so far has ended.  How many those are only the GPU
+// knows, so a fixed number of workgroups deals them out by itself: every workgroup adds up the rows that are left (four requests to a
+// thread) and takes items blockIdx.x, + gridDim.x, .. of (row, segment), the segment running slowest, so that neighbouring workgroups,
+// which go to different XCDs, have different rows.  Few rows are left behind a cut, so they are cut finer than the first
+// ones (Split): a workgroup's own time for a long segment is what such a launch takes.  256 requests x 8 drafts x 128256 tokens, 62 %
+// accepted: rows 2, 3 take 23.5 us and rows 4 .. 8 23.7, 33.1 and 36.4 as launches of a workgroup for every row and segment there might be
+// (their 170 and 190 rows are 15 and 17 us at a large copy's rate).
+// (One workgroup for all of a request's rows of a part: 93 us for rows 4 .. 8.  Making the test in each workgroup instead of ahead of
+// the launch: 59 us.)
+template <bool SAMPLE>
+__global__ __launch_bounds__(256) void accept_row_stats_part(const float* __restrict__ logits, int V, Split sp, float inv_tau, int B, int j0,
+                                                             int j1, KPack kp, const int32_t* __restrict__ over, RowStat* __restrict__ stats) {
+    __shared__ int sh_sum[2][4], sh_row;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const uint32_t ks = reinterpret_cast<const uint32_t*>(kp.k)[tid];
+    int left[4], rows[4], mine = 0, mine_rows = 0;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+        const int i = 4 * tid + e, k = (int)((ks >> (8 * e)) & 0xffu);
+        const bool live = i < B && !over[i];
+        rows[e] = i < B ? k + 1 : 0;
+        left[e] = live ? max(0, min(j1, k + 1) - j0) : 0;
+        mine += left[e];
+        mine_rows += rows[e];
     }
-    scan_segment<SAMPLE, SHOWN>(logits + (size_t)row * V, vec, v0, v1, inv_tau, stats + (size_t)row * n_split + split);
+    int before = mine, before_rows = mine_rows;   // running sums over the threads
+    for (int off = 1; off < 64; off <<= 1) {
+        const int a = __shfl_up(before, off), b = __shfl_up(before_rows, off);
+        if (lane >= off) {
+            before += a;
+            before_rows += b;
+        }
+    }
+    if (lane == 63) {
+        sh_sum[0][wv] = before;
+        sh_sum[1][wv] = before_rows;
+    }
+    __syncthreads();
+    int total = 0;
+#pragma unroll
+    for (int w = 0; w < 4; w++) {
+        if (w < wv) {
+            before += sh_sum[0][w];
+            before_rows += sh_sum[1][w];
+        }
+        total += sh_sum[0][w];
+    }
+    before -= mine;
+    before_rows -= mine_rows;
+    const int n_split = sp.n1, seg = ((V + n_split - 1) / n_split + 3) & ~3;
+    const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;
+    for (int item = blockIdx.x; item < total * n_split; item += gridDim.x) {
+        const int split = item / total, r = item - split * total;
+        int a = before, row0 = before_rows;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            if (r >= a && r < a + left[e]) sh_row = row0 + j0 + (r - a);
+            a += left[e];
+            row0 += rows[e];
+        }
+        __syncthreads();
+        const int row = sh_row;
+        const int v0 = min(V, split * seg), v1 = min(V, v0 + seg);
+        scan_segment<SAMPLE, false, true>(logits + (size_t)row * V, vec, v0, v1, inv_tau, stats + (size_t)row * sp.stride + split);
+        __syncthreads();   // sh_row and the scan's own words have been read
+    }
 }
 
 struct Decision {
@@ -347,7 +429,7 @@ struct Decision {
 };
 
 // One wavefront decides one request: the first failing lane of judge_rows ends the accepted prefix.
-__device__ inline Decision decide_request(int mode, int i, const KPack& kp, int V, int n_split, float inv_tau, double it,
+__device__ inline Decision decide_request(int mode, int i, const KPack& kp, int V, const Split& sp, float inv_tau, double it,
                                           const float* __restrict__ logits, const int32_t* __restrict__ tokens,
                                           const QSrc& draft_q, const float* __restrict__ u_acc,
                                           const RowStat* __restrict__ stats, int lane) {
@@ -356,7 +438,7 @@ __device__ inline Decision decide_request(int mode, int i, const KPack& kp, int 
     const int k = kp.k[i];
     int a = k;
     for (int j0 = 0; j0 < k; j0 += 64) {
-        const Judged jd = judge_rows(mode, row0, d0, j0, k, V, n_split, inv_tau, it, logits, tokens, draft_q, u_acc, stats, lane);
+        const Judged jd = judge_rows(mode, row0, d0, j0, k, V, sp, inv_tau, it, logits, tokens, draft_q, u_acc, stats, lane);
         bool fail = jd.fail;
         // Rare: the two sides of Eq. 1 agree to four digits.  The whole wavefront then sums the row's normaliser in
         // float64, in a fixed order (lane-strided partial sums, then a butterfly), and the lane decides again.  Rows
@@ -385,7 +467,7 @@ __device__ inline Decision decide_request(int mode, int i, const KPack& kp, int 
     dc.row = row0 + a;
     dc.qrow = a < k ? d0 + a : -1;
     double S;
-    row_stat(stats + (size_t)dc.row * n_split, n_split, inv_tau, dc.m, dc.amax, S);
+    row_stat(stats + (size_t)dc.row * sp.stride, sp.of(a), inv_tau, dc.m, dc.amax, S);
     return dc;
 }
 
@@ -481,7 +563,7 @@ __device__ inline double tile_total(const double* tile_sum, int n_tiles, int lan
 // workgroups per request, and leave their tile sums in the workspace (per request n_tiles of p, then n_tiles of the residual)
 // for accept_finish.  SECOND: the residual's, which need the total of the first; same sums in the same order either way.
 template <bool SECOND>
-__global__ __launch_bounds__(512) void accept_sweep(KPack kp, int V, int n_split, float inv_tau, float temperature,
+__global__ __launch_bounds__(512) void accept_sweep(KPack kp, int V, Split sp, float inv_tau, float temperature,
                                                     const float* __restrict__ logits, const int32_t* __restrict__ tokens, QSrc qsrc,
                                                     const float* __restrict__ u_acc, const RowStat* __restrict__ stats,
                                                     Decision* __restrict__ decisions, double* __restrict__ tile_sums) {
@@ -502,7 +584,7 @@ __global__ __launch_bounds__(512) void accept_sweep(KPack kp, int V, int n_split
                 sh_dc = decisions[i];
             }
         } else {
-            const Decision dc = decide_request(SLED_SAMPLE, i, kp, V, n_split, inv_tau, it, logits, tokens, qsrc, u_acc, stats, lane);
+            const Decision dc = decide_request(SLED_SAMPLE, i, kp, V, sp, inv_tau, it, logits, tokens, qsrc, u_acc, stats, lane);
             if (lane == 0) {
                 sh_dc = dc;
                 if (blockIdx.y == 0) decisions[i] = dc;
@@ -531,7 +613,7 @@ __global__ __launch_bounds__(512) void accept_sweep(KPack kp, int V, int n_split
                 SECOND ? sums + n_tiles : sums, lane);
 }
 
-__global__ __launch_bounds__(1024) void accept_finish(int mode, KPack kp, int V, int n_split, float inv_tau, float temperature,
+__global__ __launch_bounds__(1024) void accept_finish(int mode, KPack kp, int V, Split sp, float inv_tau, float temperature,
                                                       const float* __restrict__ logits, const int32_t* __restrict__ tokens,
                                                       QSrc qsrc, const float* __restrict__ u_acc,
                                                       const float* __restrict__ u_smp, const RowStat* __restrict__ stats,
@@ -548,7 +630,7 @@ __global__ __launch_bounds__(1024) void accept_finish(int mode, KPack kp, int V,
     if (wv == 0) {
         // float64 work divides by the temperature as given (a float32 number), exactly as a float64 reference does
         const Decision dc = decisions ? decisions[i]   // accept_sweep has decided
-                                      : decide_request(mode, i, kp, V, n_split, inv_tau, 1.0 / (double)temperature, logits, tokens, qsrc, u_acc, stats, lane);
+                                      : decide_request(mode, i, kp, V, sp, inv_tau, 1.0 / (double)temperature, logits, tokens, qsrc, u_acc, stats, lane);
         if (lane == 0) {
             sh_dc = dc;
             accept_len[i] = dc.a;
@@ -815,7 +897,7 @@ int sled_launch_accept(int mode, int B, int T, const int* k_host, int vocab, flo
     // The scan in parts.  A cut at row c saves the rows from c on of every request that ends before c and costs a launch
     // and its drain, about 8 us: made where the rows behind it are at least 64 MB x c (the longer the prefix, the fewer
     // requests still get there), unless so few requests have long drafts that most workgroups of a part would be empty.
-    // 256 requests x 8 drafts x 128256 tokens, 62 % accepted: 204 us in one launch, 115 + 10 in three.
+    // 256 requests x 8 drafts x 128256 tokens, 62 % accepted: 204 us in one launch, 93 + 10 in three.
     auto rows_from = [&](int c) {
         int64_t n = 0;
         for (int i = 0; i < B; i++) n += std::max(0, k_host[i] + 1 - c);
@@ -833,38 +915,48 @@ int sled_launch_accept(int mode, int B, int T, const int* k_host, int vocab, flo
         const int64_t rows_first = n_part > 1 ? T - rows_from(cuts[1]) : T;
         return std::min(sled_accept_pick_split(T, vocab), (int)std::max<int64_t>(1, (2048 + rows_first / 2) / rows_first));
     };
+    // Rows behind a cut are few and are cut finer, where the workspace holds as many statistics for all rows: eight segments (sixteen
+    // scan no faster, and the next test, which adds up a row's segments, takes 6.9 instead of 5.4 us).
     int n_split = segments();
-    if (n_part > 1 && ws_bytes < sled_accept_ws_bytes(B, T, n_split) + over_ws_bytes(B)) {
-        n_part = 1;
+    const int n_fine = std::min(8, sled_accept_pick_split(1, vocab));
+    Split sp{n_split, n_fine, cuts[1], std::max(n_split, n_fine)};
+    if (n_part > 1 && ws_bytes < sled_accept_ws_bytes(B, T, sp.stride) + over_ws_bytes(B)) sp = Split{n_split, n_split, cuts[1], n_split};
+    if (n_part > 1 && ws_bytes < sled_accept_ws_bytes(B, T, sp.stride) + over_ws_bytes(B)) n_part = 1;
+    if (n_part == 1) {
         n_split = segments();
+        sp = Split{n_split, n_split, 0, n_split};
     }
-    int seg = (vocab + n_split - 1) / n_split;
-    seg = (seg + 3) & ~3;
     RowStat* stats = reinterpret_cast<RowStat*>(ws);
-    const size_t over_at = sled_accept_ws_bytes(B, T, n_split), sums_at = over_at + over_ws_bytes(B);
+    const size_t over_at = sled_accept_ws_bytes(B, T, sp.stride), sums_at = over_at + over_ws_bytes(B);
     int32_t* over = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + over_at);   // there when the scan comes in parts
     const bool sweep_room = ws_bytes >= sums_at + sweep_ws_bytes(B, vocab);
-    for (int part = 0; part < n_part && n_part > 1; part++) {
-        const int j0 = cuts[part], j1 = part + 1 < n_part ? cuts[part + 1] : k_top + 1;
-        const RowPart rp{B, j0, kp, over};
-        if (j0 > 0) {
-            hipLaunchKernelGGL(accept_over, dim3(B), dim3(64), 0, st, mode, kp, j0, vocab, n_split, inv_tau, temperature, logits, tokens, qsrc, u_acc,
-                               stats, over);
-            SLED_LAUNCH_CHECK();
-        }
-        const dim3 grid(B * (j1 - j0), n_split);
+    if (n_part > 1) {
+        const dim3 grid(B * cuts[1], n_split);
         if (mode == SLED_SAMPLE)
-            hipLaunchKernelGGL((accept_row_stats<true, true>), grid, dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, rp, stats);
+            hipLaunchKernelGGL(accept_row_stats_first<true>, grid, dim3(256), 0, st, logits, vocab, sp, inv_tau, B, kp, stats);
         else
-            hipLaunchKernelGGL((accept_row_stats<false, true>), grid, dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, rp, stats);
+            hipLaunchKernelGGL(accept_row_stats_first<false>, grid, dim3(256), 0, st, logits, vocab, sp, inv_tau, B, kp, stats);
+        SLED_LAUNCH_CHECK();
+    }
+    for (int part = 1; part < n_part; part++) {
+        const int j0 = cuts[part], j1 = part + 1 < n_part ? cuts[part + 1] : k_top + 1;
+        hipLaunchKernelGGL(accept_over, dim3(B), dim3(64), 0, st, mode, kp, j0, vocab, sp, inv_tau, temperature, logits, tokens, qsrc, u_acc, stats, over);
+        SLED_LAUNCH_CHECK();
+        const int64_t items = (rows_from(j0) - (part + 1 < n_part ? rows_from(j1) : 0)) * sp.n1;
+        const dim3 grid((unsigned)std::min<int64_t>(items, 2048));   // eight workgroups fill a CU
+        if (mode == SLED_SAMPLE)
+            hipLaunchKernelGGL(accept_row_stats_part<true>, grid, dim3(256), 0, st, logits, vocab, sp, inv_tau, B, j0, j1, kp, over, stats);
+        else
+            hipLaunchKernelGGL(accept_row_stats_part<false>, grid, dim3(256), 0, st, logits, vocab, sp, inv_tau, B, j0, j1, kp, over, stats);
         SLED_LAUNCH_CHECK();
     }
     if (n_part == 1) {
+        const int seg = ((vocab + n_split - 1) / n_split + 3) & ~3;
         const dim3 grid(T, n_split);
         if (mode == SLED_SAMPLE)
-            hipLaunchKernelGGL((accept_row_stats<true, false>), grid, dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, 0, stats);
+            hipLaunchKernelGGL((accept_row_stats<true>), grid, dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, stats);
         else
-            hipLaunchKernelGGL((accept_row_stats<false, false>), grid, dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, 0, stats);
+            hipLaunchKernelGGL((accept_row_stats<false>), grid, dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, stats);
         SLED_LAUNCH_CHECK();
     }
     // The two float64 sweeps over a request's row are what the finish spends its time on: 93 us with one workgroup per request,
@@ -879,15 +971,15 @@ int sled_launch_accept(int mode, int B, int T, const int* k_host, int vocab, flo
         tile_sums = reinterpret_cast<double*>(static_cast<char*>(ws) + sums_at);
         decisions = reinterpret_cast<Decision*>(tile_sums + (size_t)B * 2 * n_tiles);
         const dim3 grid(B, std::min((n_tiles + 7) / 8, std::max(2, 512 / B)));   // a workgroup has eight wavefronts, a tile each at a time
-        hipLaunchKernelGGL(accept_sweep<false>, grid, dim3(512), 0, st, kp, vocab, n_split, inv_tau, temperature, logits, tokens, qsrc, u_acc, stats,
+        hipLaunchKernelGGL(accept_sweep<false>, grid, dim3(512), 0, st, kp, vocab, sp, inv_tau, temperature, logits, tokens, qsrc, u_acc, stats,
                            decisions, tile_sums);
         SLED_LAUNCH_CHECK();
-        hipLaunchKernelGGL(accept_sweep<true>, grid, dim3(512), 0, st, kp, vocab, n_split, inv_tau, temperature, logits, tokens, qsrc, u_acc, stats,
+        hipLaunchKernelGGL(accept_sweep<true>, grid, dim3(512), 0, st, kp, vocab, sp, inv_tau, temperature, logits, tokens, qsrc, u_acc, stats,
                            decisions, tile_sums);
         SLED_LAUNCH_CHECK();
     }
     // greedy needs only the deciding wavefront
-    hipLaunchKernelGGL(accept_finish, dim3(B), dim3(mode == SLED_SAMPLE ? 1024 : 64), 0, st, mode, kp, vocab, n_split, inv_tau,
+    hipLaunchKernelGGL(accept_finish, dim3(B), dim3(mode == SLED_SAMPLE ? 1024 : 64), 0, st, mode, kp, vocab, sp, inv_tau,
                        temperature, logits, tokens, qsrc, u_acc, u_smp, stats, accept_len, out_token, decisions, tile_sums);
     SLED_LAUNCH_CHECK();
     return SLED_OK;
@@ -954,7 +1046,7 @@ int sled_launch_row_confidence(int T, int vocab, float temperature, const float*
     seg = (seg + 3) & ~3;
     RowStat* stats = reinterpret_cast<RowStat*>(ws);
     const float inv_tau = 1.0f / temperature;
-    hipLaunchKernelGGL((accept_row_stats<true, false, true>), dim3(T, n_split), dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, 0, stats);
+    hipLaunchKernelGGL((accept_row_stats<true, true>), dim3(T, n_split), dim3(256), 0, st, logits, vocab, n_split, seg, inv_tau, stats);
     SLED_LAUNCH_CHECK();
     hipLaunchKernelGGL(row_confidence_finish, dim3((T + 255) / 256), dim3(256), 0, st, stats, T, n_split, inv_tau, conf, top);
     SLED_LAUNCH_CHECK();
