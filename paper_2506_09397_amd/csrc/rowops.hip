@@ -12,11 +12,25 @@
 
 namespace {
 
-// sum over the workgroup (blockDim.x a multiple of 64, at most 1024); every thread gets the result;
+// x + its value in the lane whose number differs in one bit, for the bits 5 .. 0 in turn: the sum over the wavefront in every lane.  Exchanges
+// between register halves (bits 5, 4) and rotations within 16 lanes, which by then hold equal values in the lanes that a
+// rotation and an exchange would tell apart; through LDS (shuffles) the six steps are as many round trips.
+__device__ inline float wave_sum(float x) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x128, 0xf, 0xf, false));   // row_ror:8
+    x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x124, 0xf, 0xf, false));   // row_ror:4
+    x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x122, 0xf, 0xf, false));   // row_ror:2
+    x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x121, 0xf, 0xf, false));   // row_ror:1
+    return x;
+}
+
+// sum over the workgroup (blockDim.x a multiple of 64, at most 1024), once per kernel; every thread gets the result;
 // the order of additions is fixed
 __device__ inline float block_sum(float x, float* sh /*[16]*/) {
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-    __syncthreads();
+    x = wave_sum(x);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = x;
     __syncthreads();
     float t = 0.f;
@@ -155,15 +169,26 @@ __device__ inline void store_act4(void* X, size_t plane, int t, int c0, int K, c
     }
 }
 
+// Workgroups go to the eight XCDs round robin, and each XCD has its own L2.  Where `group` neighbouring rows share the lines that a kernel
+// writes (16 bytes of each: eight rows of an activation, sixteen tokens of a page), the group's workgroups are put on one XCD, so that
+// its L2 gathers whole lines instead of eight of them writing pieces back.  The grid is rounded up to whole rounds of groups.
+constexpr int XCDS = 8, ACT_LINE_ROWS = 8;
+__device__ inline int row_of_block(int w, int group) {
+    const int xcd = w % XCDS, local = w / XCDS;   // (group 1: row w)
+    return (local / group * XCDS + xcd) * group + local % group;
+}
+inline int blocks_for_rows(int rows, int group) { return (rows + XCDS * group - 1) / (XCDS * group) * (XCDS * group); }
+
 // h[t,:] += sum_s partial[s][t][:]  (s ascending);  X[t,:] = rmsnorm(h) * gain.  A thread owns 4 consecutive
 // columns per trip over the row; rows of up to 8 * blockDim.x columns (two trips) stay in registers between the
 // sum of squares and the scaling, longer rows are read back from h.
 template <bool BF16>
 __global__ __launch_bounds__(1024) void residual_norm_kernel(const float* __restrict__ partial, int n_split, int T_pad,
                                                             int d, float eps, const float* __restrict__ gain,
-                                                            float* __restrict__ h, void* __restrict__ X, size_t plane) {
+                                                            float* __restrict__ h, void* __restrict__ X, size_t plane, int T, int group) {
     __shared__ float sh[16];
-    const int t = blockIdx.x;
+    const int t = row_of_block(blockIdx.x, group);
+    if (t >= T) return;
     const size_t stride = (size_t)T_pad * d;
     const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
     float ss = 0.f;
@@ -244,68 +269,85 @@ __global__ void attn_plan_kernel(sled_step_meta meta, const int32_t* __restrict_
     r[10] = r[11] = 0;
 }
 
-// Reduce the QKV partial sums of one head of row t (blockIdx = (t, head), heads ordered q, k, v),
-// rotate q and k, write q to Q[T, Hq, D] and k, v into the request's page slot for position L + j.
-template <bool BF16>
-__global__ __launch_bounds__(64) void qkv_rope_store_kernel(const float* __restrict__ partial, int n_split, int T_pad,
-                                                            int Hq, int Hkv, int D, const float2* __restrict__ cs,
-                                                            const int32_t* __restrict__ kvslot, void* __restrict__ Q, size_t q_plane, void* __restrict__ k_pool,
-                                                            void* __restrict__ v_pool, int64_t n_pages, int layer) {
+// Reduce the QKV partial sums of row t, rotate q and k, write q to Q[T, Hq, D] as a bf16 pair and k, v into the request's page slot for
+// position L + j.  (Prompt slices; a verification step's attention does this itself.)  A thread takes four neighbouring rotary pairs of a
+// q or k head, or four dims of a v head, so that all loads are 16 bytes and all stores but v's 8; sixteen rows, the tokens of a page, meet on
+// one XCD.  1080 rows of the 8B shape (a wavefront per row and head, two bytes a store, rows spread over the XCDs before): 26.4 -> 13.8 us.
+constexpr int QKV_ROWS = 16;
+__global__ __launch_bounds__(256) void qkv_rope_store_bf16_kernel(const float* __restrict__ partial, int n_split, int T, int T_pad, int Hq, int Hkv,
+                                                                  const float2* __restrict__ cs, const int32_t* __restrict__ kvslot,
+                                                                  bf16_t* __restrict__ Q, size_t q_plane, bf16_t* __restrict__ k_pool,
+                                                                  bf16_t* __restrict__ v_pool, int64_t n_pages, int layer, int blocks_per_row) {
+    constexpr int D = 128, half = D / 2;
+    const int w = blockIdx.x, xcd = w % XCDS, local = w / XCDS;
+    const int t = row_of_block(local / blocks_per_row * XCDS + xcd, QKV_ROWS);
+    if (t >= T) return;
+    const int n_rot = (Hq + Hkv) * (half / 4), item = local % blocks_per_row * 256 + threadIdx.x;
+    const int n_qkv = (Hq + 2 * Hkv) * D;
+    const float* prow = partial + (size_t)t * n_qkv;
+    const size_t stride = (size_t)T_pad * n_qkv;
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto pair2 = [](float a, float b) { return (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16); };
+    if (item < n_rot) {
+        const int head = item / (half / 4), i = item % (half / 4) * 4;
+        const float4 c01 = *reinterpret_cast<const float4*>(cs + (size_t)t * half + i), c23 = *reinterpret_cast<const float4*>(cs + (size_t)t * half + i + 2);
+        const int ps = head < Hq ? 0 : kvslot[t];
+        const float4 x1 = add_slices4(zero, prow + head * D + i, stride, n_split), x2 = add_slices4(zero, prow + head * D + i + half, stride, n_split);
+        float y1[4], y2[4];
+        rope_pair(x1.x, x2.x, c01.x, c01.y, y1[0], y2[0]);
+        rope_pair(x1.y, x2.y, c01.z, c01.w, y1[1], y2[1]);
+        rope_pair(x1.z, x2.z, c23.x, c23.y, y1[2], y2[2]);
+        rope_pair(x1.w, x2.w, c23.z, c23.w, y1[3], y2[3]);
+        const uint2 h1 = make_uint2(pair2(y1[0], y1[1]), pair2(y1[2], y1[3])), h2 = make_uint2(pair2(y2[0], y2[1]), pair2(y2[2], y2[3]));
+        if (head < Hq) {   // q is kept as a bf16 pair, like every activation that is not cached
+            auto low = [](float y) { return y - bf16_to_f32(f32_to_bf16(y)); };
+            bf16_t* q = Q + ((size_t)t * Hq + head) * D + i;
+            *reinterpret_cast<uint2*>(q) = h1;
+            *reinterpret_cast<uint2*>(q + half) = h2;
+            *reinterpret_cast<uint2*>(q + q_plane) = make_uint2(pair2(low(y1[0]), low(y1[1])), pair2(low(y1[2]), low(y1[3])));
+            *reinterpret_cast<uint2*>(q + q_plane + half) = make_uint2(pair2(low(y2[0]), low(y2[1])), pair2(low(y2[2]), low(y2[3])));
+        } else {           // four neighbouring dims share an 8-byte piece of the page's operand order
+            bf16_t* kp = k_pool + (((size_t)layer * n_pages + (ps >> 4)) * Hkv + (head - Hq)) * (16 * D);
+            *reinterpret_cast<uint2*>(kp + kpage_offset(ps & 15, i)) = h1;
+            *reinterpret_cast<uint2*>(kp + kpage_offset(ps & 15, i + half)) = h2;
+        }
+    } else if (item < n_rot + Hkv * (D / 4)) {
+        const int e = item - n_rot, g = e / (D / 4), dd = e % (D / 4) * 4;
+        const int ps = kvslot[t];
+        const float4 x = add_slices4(zero, prow + (Hq + Hkv + g) * D + dd, stride, n_split);
+        bf16_t* vp = v_pool + (((size_t)layer * n_pages + (ps >> 4)) * Hkv + g) * (16 * D);
+        vp[vpage_offset(ps & 15, dd)] = f32_to_bf16(x.x);
+        vp[vpage_offset(ps & 15, dd + 1)] = f32_to_bf16(x.y);
+        vp[vpage_offset(ps & 15, dd + 2)] = f32_to_bf16(x.z);
+        vp[vpage_offset(ps & 15, dd + 3)] = f32_to_bf16(x.w);
+    }
+}
+
+// The same for fp32 models, one head of row t (blockIdx = (t, head), heads ordered q, k, v) per workgroup.
+__global__ __launch_bounds__(64) void qkv_rope_store_f32_kernel(const float* __restrict__ partial, int n_split, int T_pad, int Hq, int Hkv, int D,
+                                                                const float2* __restrict__ cs, const int32_t* __restrict__ kvslot,
+                                                                float* __restrict__ Q, float* __restrict__ k_pool, float* __restrict__ v_pool,
+                                                                int64_t n_pages, int layer) {
     const int t = blockIdx.x, head = blockIdx.y;
     const int half = D >> 1;
     const int n_qkv = (Hq + 2 * Hkv) * D;
-    const size_t head_elems = (size_t)16 * D;
     const float* prow = partial + (size_t)t * n_qkv;
     const size_t stride = (size_t)T_pad * n_qkv;
-    const int ps = kvslot[t], page = ps >> 4, slot = ps & 15;
+    const int ps = kvslot[t];
+    auto slot = [&](float* pool, int g) { return pool + (((size_t)layer * n_pages + (ps >> 4)) * Hkv + g) * (16 * D) + (size_t)(ps & 15) * D; };
     if (head < Hq + Hkv) {
+        float* out = head < Hq ? Q + ((size_t)t * Hq + head) * D : slot(k_pool, head - Hq);
         for (int i = threadIdx.x; i < half; i += 64) {
             const int c1 = head * D + i, c2 = c1 + half;
             const float2 sc = cs[(size_t)t * half + i];
             float x1 = 0.f, x2 = 0.f;
             add_slices1x2(x1, x2, prow + c1, prow + c2, stride, n_split);
-            float y1, y2;
-            rope_pair(x1, x2, sc.x, sc.y, y1, y2);
-            if (head < Hq) {
-                if (BF16) {  // q is kept as a bf16 pair, like every activation that is not cached
-                    bf16_t* q = static_cast<bf16_t*>(Q) + ((size_t)t * Hq + head) * D;
-                    const bf16_t h1 = f32_to_bf16(y1), h2 = f32_to_bf16(y2);
-                    q[i] = h1;
-                    q[i + half] = h2;
-                    q[q_plane + i] = f32_to_bf16(y1 - bf16_to_f32(h1));
-                    q[q_plane + i + half] = f32_to_bf16(y2 - bf16_to_f32(h2));
-                } else {
-                    float* q = static_cast<float*>(Q) + ((size_t)t * Hq + head) * D;
-                    q[i] = y1;
-                    q[i + half] = y2;
-                }
-            } else {
-                const int g = head - Hq;
-                const size_t base = (((size_t)layer * n_pages + page) * Hkv + g) * head_elems;
-                if (BF16) {
-                    // K page-head block in operand order
-                    bf16_t* kp = static_cast<bf16_t*>(k_pool) + base;
-                    kp[kpage_offset(slot, i)] = f32_to_bf16(y1);
-                    kp[kpage_offset(slot, i + half)] = f32_to_bf16(y2);
-                } else {
-                    float* kp = static_cast<float*>(k_pool) + base + (size_t)slot * D;
-                    kp[i] = y1;
-                    kp[i + half] = y2;
-                }
-            }
+            rope_pair(x1, x2, sc.x, sc.y, out[i], out[i + half]);
         }
-    } else {
-        // v head: no rotation
+    } else {   // v head: no rotation
         const int g = head - Hq - Hkv;
-        for (int dd = threadIdx.x; dd < D; dd += 64) {
-            const float v = add_slices1(0.f, prow + (Hq + Hkv) * D + g * D + dd, stride, n_split);
-            const size_t base = (((size_t)layer * n_pages + page) * Hkv + g) * head_elems;
-            if (BF16) {
-                static_cast<bf16_t*>(v_pool)[base + vpage_offset(slot, dd)] = f32_to_bf16(v);
-            } else {
-                static_cast<float*>(v_pool)[base + (size_t)slot * D + dd] = v;
-            }
-        }
+        float* out = slot(v_pool, g);
+        for (int dd = threadIdx.x; dd < D; dd += 64) out[dd] = add_slices1(0.f, prow + (Hq + Hkv) * D + g * D + dd, stride, n_split);
     }
 }
 
@@ -674,13 +716,16 @@ int sled_launch_embed_norm(const sled_model* m, const int32_t* tokens, int T, fl
 int sled_launch_residual_norm(const sled_model* m, const float* partial, int n_split, int T, int T_pad, float* h, void* X,
                               size_t plane, const float* gain, hipStream_t st) {
     // four columns per thread per trip: short rows get small workgroups
+    // Rows of an activation line on one XCD: 101 rows 6.4 -> 6.1 us, 372 rows 11.4 -> 10.0, 700 rows 15.0 -> 11.7, 1080 rows 25.6 -> 20.2.  Few
+    // rows fill few XCDs then and gain nothing (25 rows: the same, and the next projection 10.0 -> 10.5).
+    const int group = T > 64 ? ACT_LINE_ROWS : 1;
     const int bs = m->s.d_model >= 4096 ? 1024 : m->s.d_model >= 2048 ? 512 : m->s.d_model >= 1024 ? 256 : 128;
     if (m->s.dtype == SLED_BF16)
-        hipLaunchKernelGGL(residual_norm_kernel<true>, dim3(T), dim3(bs), 0, st, partial, n_split, T_pad, m->s.d_model,
-                           m->s.rms_eps, gain, h, X, plane);
+        hipLaunchKernelGGL(residual_norm_kernel<true>, dim3(group > 1 ? blocks_for_rows(T, group) : T), dim3(bs), 0, st, partial, n_split,
+                           T_pad, m->s.d_model, m->s.rms_eps, gain, h, X, plane, T, group);
     else
         hipLaunchKernelGGL(residual_norm_kernel<false>, dim3(T), dim3(bs), 0, st, partial, n_split, T_pad, m->s.d_model,
-                           m->s.rms_eps, gain, h, X, plane);
+                           m->s.rms_eps, gain, h, X, plane, T, 1);
     SLED_LAUNCH_CHECK();
     return SLED_OK;
 }
@@ -713,15 +758,17 @@ int sled_launch_attn_plan(const sled_model* m, const sled_kvpool* p, const sled_
 
 int sled_launch_qkv_rope_store(const sled_model* m, const sled_kvpool* p, int T, int layer, const float* partial, int n_split,
                                int T_pad, const float* cs, const int32_t* kvslot, void* Q, size_t q_plane, hipStream_t st) {
-    const dim3 grid(T, m->s.n_q_heads + 2 * m->s.n_kv_heads);
-    if (m->s.dtype == SLED_BF16)
-        hipLaunchKernelGGL(qkv_rope_store_kernel<true>, grid, dim3(64), 0, st, partial, n_split, T_pad, m->s.n_q_heads,
-                           m->s.n_kv_heads, m->s.head_dim, reinterpret_cast<const float2*>(cs), kvslot, Q, q_plane, p->k_pool,
-                           p->v_pool, p->n_pages, layer);
-    else
-        hipLaunchKernelGGL(qkv_rope_store_kernel<false>, grid, dim3(64), 0, st, partial, n_split, T_pad, m->s.n_q_heads,
-                           m->s.n_kv_heads, m->s.head_dim, reinterpret_cast<const float2*>(cs), kvslot, Q, q_plane, p->k_pool,
-                           p->v_pool, p->n_pages, layer);
+    const int Hq = m->s.n_q_heads, Hkv = m->s.n_kv_heads;
+    if (m->s.dtype == SLED_BF16) {
+        const int blocks_per_row = ((Hq + Hkv) * 16 + Hkv * 32 + 255) / 256;
+        hipLaunchKernelGGL(qkv_rope_store_bf16_kernel, dim3(blocks_for_rows(T, QKV_ROWS) * blocks_per_row), dim3(256), 0, st, partial, n_split, T, T_pad,
+                           Hq, Hkv, reinterpret_cast<const float2*>(cs), kvslot, static_cast<bf16_t*>(Q), q_plane,
+                           static_cast<bf16_t*>(p->k_pool), static_cast<bf16_t*>(p->v_pool), p->n_pages, layer, blocks_per_row);
+    } else {
+        hipLaunchKernelGGL(qkv_rope_store_f32_kernel, dim3(T, Hq + 2 * Hkv), dim3(64), 0, st, partial, n_split, T_pad, Hq, Hkv, m->s.head_dim,
+                           reinterpret_cast<const float2*>(cs), kvslot, static_cast<float*>(Q), static_cast<float*>(p->k_pool),
+                           static_cast<float*>(p->v_pool), p->n_pages, layer);
+    }
     SLED_LAUNCH_CHECK();
     return SLED_OK;
 }
