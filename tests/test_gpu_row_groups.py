@@ -56,3 +56,17 @@ def test_prompt_rows_and_heads(n_q, n_kv, rows):
         assert bool(((x - y).abs() <= 2.0**-7 * y.abs() + 1e-3 * rms).all()) and float((x != y).float().mean()) < 0.05
     assert np.abs(logits - last).max() < 5e-3
     v.destroy()
+
+
+@pytest.mark.parametrize("heads", [12, 16])
+def test_pages_of_many_heads_move_unchanged(heads):
+    shape = synth.scaled_shape(synth.SHAPES["tiny_bf16"], n_q_heads=heads, n_kv_heads=heads)
+    w = synth.SynthWeights(shape, seed=5, device="cuda")
+    v = Verifier(shape, w, 16, 1, 1, 128)
+    r = v.open()
+    K, V = synth.context_kv(shape, 70, seed=2, req=0, device="cuda")
+    for a, b in ((0, 3), (3, 16), (16, 48), (48, 70)):      # part of a page, its rest, whole pages, whole and part
+        v.append_context([r], [K[:, a:b].contiguous()], [V[:, a:b].contiguous()])
+    K2, V2 = v.read_kv(r, 0, 70)
+    assert torch.equal(K, K2) and torch.equal(V, V2)
+    v.destroy()
