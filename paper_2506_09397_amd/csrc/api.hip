@@ -479,13 +479,12 @@ static void poll_readbacks(sled_kvpool* p) {
 
 // the device-side length of a request that has just been opened is reset here, on the first stream that names it
 static int reset_fresh_lengths(sled_kvpool* p, int B, const int* req_ids, hipStream_t st) {
-    for (int i = 0; i < B; i++) {
-        sled_request& rq = p->reqs[req_ids[i]];
-        if (!rq.fresh) continue;
-        int rc = sled_launch_fill_i32(p->len_dev + req_ids[i], 0, 1, st);
-        if (rc != SLED_OK) return rc;
-        rq.fresh = false;
-    }
+    std::vector<int> ids;
+    for (int i = 0; i < B; i++)
+        if (p->reqs[req_ids[i]].fresh) ids.push_back(req_ids[i]);
+    const int rc = sled_launch_len_zero(p->len_dev, ids.data(), (int)ids.size(), st);
+    if (rc != SLED_OK) return rc;
+    for (int r : ids) p->reqs[r].fresh = false;
     return SLED_OK;
 }
 
@@ -567,7 +566,7 @@ extern "C" int sled_kv_append(sled_kvpool* p, int B, const int* req_ids, const i
         if ((rc = stage_acquire(p, B, &sl)) != SLED_OK) return rc;
         for (int i = 0; i < B; i++) sl->host[i] = req_ids[i];
         SLED_HIP(hipMemcpyAsync(sl->dev, sl->host, B * sizeof(int32_t), hipMemcpyHostToDevice, st));
-        if ((rc = sled_launch_len_add(p->len_dev, sl->dev, nullptr, accept_len, B, st)) != SLED_OK) return rc;
+        if ((rc = sled_launch_len_add(p->len_dev, sl->dev, nullptr, nullptr, accept_len, B, st)) != SLED_OK) return rc;
         if ((rc = stage_release(sl, st)) != SLED_OK) return rc;
         for (int i = 0; i < B; i++) {
             sled_request& rq = p->reqs[req_ids[i]];
@@ -580,8 +579,7 @@ extern "C" int sled_kv_append(sled_kvpool* p, int B, const int* req_ids, const i
         return enqueue_readback(p, B, req_ids, st);
     }
     if (!n_tokens || !k_src || !v_src) SLED_FAIL(SLED_EINVAL, "sled_kv_append: null argument");
-    if ((rc = reset_fresh_lengths(p, B, req_ids, st)) != SLED_OK) return rc;
-    size_t need = 2 * (size_t)B;
+    size_t need = 3 * (size_t)B;
     for (int i = 0; i < B; i++) {
         if (n_tokens[i] < 0 || (n_tokens[i] > 0 && (!k_src[i] || !v_src[i])))
             SLED_FAIL(SLED_EINVAL, "sled_kv_append: bad entry %d", i);
@@ -590,24 +588,27 @@ extern "C" int sled_kv_append(sled_kvpool* p, int B, const int* req_ids, const i
     }
     sled_stage_slot* sl;
     if ((rc = stage_acquire(p, need, &sl)) != SLED_OK) return rc;
-    size_t off = 2 * (size_t)B;
-    std::vector<size_t> page_off(B);
+    size_t off = 3 * (size_t)B;
+    std::vector<sled_kv_piece> pieces;
+    pieces.reserve(B);
     for (int i = 0; i < B; i++) {
         sl->host[i] = req_ids[i];
         sl->host[B + i] = n_tokens[i];
-        page_off[i] = off;
-        for (int pg : p->reqs[req_ids[i]].pages) sl->host[off++] = pg;
+        // a request that has just been opened has length zero whatever its slot held: nothing reads the slot, the update below sets it
+        const sled_request& rq = p->reqs[req_ids[i]];
+        sl->host[2 * B + i] = rq.fresh;
+        if (n_tokens[i] > 0)
+            pieces.push_back(sled_kv_piece{const_cast<void*>(k_src[i]), const_cast<void*>(v_src[i]), sl->dev + off,
+                                           rq.fresh ? nullptr : p->len_dev + req_ids[i], 0, n_tokens[i]});
+        for (int pg : rq.pages) sl->host[off++] = pg;
     }
     SLED_HIP(hipMemcpyAsync(sl->dev, sl->host, off * sizeof(int32_t), hipMemcpyHostToDevice, st));
-    for (int i = 0; i < B; i++) {
-        if (n_tokens[i] == 0) continue;
-        if ((rc = sled_launch_kv_ingest(m, p, k_src[i], v_src[i], n_tokens[i], req_ids[i], sl->dev + page_off[i], st)) != SLED_OK)
-            return rc;
-    }
-    if ((rc = sled_launch_len_add(p->len_dev, sl->dev, sl->dev + B, nullptr, B, st)) != SLED_OK) return rc;
+    if ((rc = sled_launch_kv_ingest(m, p, pieces.data(), (int)pieces.size(), st)) != SLED_OK) return rc;
+    if ((rc = sled_launch_len_add(p->len_dev, sl->dev, sl->dev + B, sl->dev + 2 * B, nullptr, B, st)) != SLED_OK) return rc;
     if ((rc = stage_release(sl, st)) != SLED_OK) return rc;
     for (int i = 0; i < B; i++) {
         sled_request& rq = p->reqs[req_ids[i]];
+        rq.fresh = false;
         rq.len_ub += n_tokens[i];
         rq.added += n_tokens[i];
         rq.staged = -1;   // rows staged by an uncommitted verify are overwritten: nothing of this request is left to commit
@@ -957,11 +958,7 @@ int run_forward(sled_model* m, sled_kvpool* p, const std::vector<step_entry>& en
         SLED_TRY(x);                       \
     } while (0)
 
-    // arrival counters of the attention work items start at zero (each layer leaves them at zero)
-    SLED_RUN(SLED_PROF_ROWS, sled_launch_fill_i32(arrive, 0, (size_t)B * Hkv, st));
-    SLED_RUN(SLED_PROF_ROWS, sled_launch_rope_table(m, p, meta, cs, kvslot, st));
-    if (bf) SLED_RUN(SLED_PROF_ROWS, sled_launch_attn_plan(m, p, meta, plan, st));
-    SLED_RUN(SLED_PROF_ROWS, sled_launch_embed_norm(m, tokens, T, h, xa, pl_d, m->layers[0].g_attn, st));
+    SLED_RUN(SLED_PROF_ROWS, sled_launch_step_setup(m, p, meta, tokens, cs, kvslot, plan, arrive, h, xa, pl_d, m->layers[0].g_attn, st));
     for (int l = 0; l < s.n_layers; l++) {
         const sled_layer_weights& w = m->layers[l];
         SLED_RUN(SLED_PROF_PROJ, sled_launch_gemm(m, xa, pl_d, w.w_qkv, w.s_qkv, T, T_pad, m->n_qkv, d, SLED_EPI_PARTIAL, g_qkv, partial, nullptr, 0, 0, st));
@@ -1094,7 +1091,7 @@ extern "C" int sled_prefill(sled_model* m, sled_kvpool* p, int req_id, int n_tok
         sl->host[0] = req_id;
         sl->host[1] = rows;
         SLED_HIP(hipMemcpyAsync(sl->dev, sl->host, 2 * sizeof(int32_t), hipMemcpyHostToDevice, st));
-        if ((rc = sled_launch_len_add(p->len_dev, sl->dev, sl->dev + 1, nullptr, 1, st)) != SLED_OK) return rc;
+        if ((rc = sled_launch_len_add(p->len_dev, sl->dev, sl->dev + 1, nullptr, nullptr, 1, st)) != SLED_OK) return rc;
         if ((rc = stage_release(sl, st)) != SLED_OK) return rc;
         rq.len_ub += rows;
         rq.added += rows;

@@ -61,43 +61,6 @@ __device__ inline void store_act8(void* X, size_t plane, int t, int c0, int K, c
     }
 }
 
-// h[t,:] = E[token]; X[t,:] = rmsnorm(h) * gain
-template <bool BF16>
-__global__ __launch_bounds__(256) void embed_norm_kernel(const int32_t* __restrict__ tokens, const void* __restrict__ E,
-                                                         int V, int d, float eps, const float* __restrict__ gain,
-                                                         float* __restrict__ h, void* __restrict__ X, size_t plane) {
-    __shared__ float sh[16];
-    const int t = blockIdx.x;
-    int tok = tokens[t];
-    tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
-    float ss = 0.f;
-    for (int c = threadIdx.x * 8; c < d; c += 256 * 8) {
-        float v[8];
-        if (BF16) {
-            uint4 raw = *reinterpret_cast<const uint4*>(static_cast<const bf16_t*>(E) + (size_t)tok * d + c);
-            const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-            for (int i = 0; i < 4; i++) {
-                v[2 * i] = bf16_to_f32((bf16_t)(w[i] & 0xffff));
-                v[2 * i + 1] = bf16_to_f32((bf16_t)(w[i] >> 16));
-            }
-        } else {
-            const float* p = static_cast<const float*>(E) + (size_t)tok * d + c;
-            for (int i = 0; i < 8; i++) v[i] = p[i];
-        }
-        for (int i = 0; i < 8; i++) {
-            h[(size_t)t * d + c + i] = v[i];
-            ss += v[i] * v[i];
-        }
-    }
-    const float tot = block_sum(ss, sh);
-    const float r = 1.0f / sqrtf(tot / (float)d + eps);
-    for (int c = threadIdx.x * 8; c < d; c += 256 * 8) {
-        float v[8];
-        for (int i = 0; i < 8; i++) v[i] = h[(size_t)t * d + c + i] * r * gain[c + i];
-        store_act8<BF16>(X, plane, t, c, d, v);
-    }
-}
-
 // a + sum over the K slices s = 0 .. n_split-1 (ascending) of p[s * stride .. + 3].  The loads of up to eight slices
 // are issued before the first is used: a row kernel is a chain of round trips to L2, not a stream, and a loop
 // that adds slice after slice would pay one round trip per slice.
@@ -230,43 +193,98 @@ __global__ __launch_bounds__(1024) void residual_norm_kernel(const float* __rest
     }
 }
 
-// Per packed row, once per step: cos/sin of pos * theta^(-2i/D), evaluated in float64 and stored as float32, and
-// where the row's K/V go (16 * page + slot) -- the chain of dependent lookups behind that is then paid once, not
-// in every layer's store kernel.
-__global__ void rope_table_kernel(sled_step_meta meta, const int32_t* __restrict__ len_dev, int half, double theta,
-                                  float2* __restrict__ cs, int32_t* __restrict__ kvslot) {
-    const int t = blockIdx.x;
-    const int b = meta.row_req[t];
-    const int pos = len_dev[meta.req_id[b]] + meta.pos0[b] + meta.row_j[t];
-    if (threadIdx.x == 0) kvslot[t] = meta.pages[meta.cu_pages[b] + (pos >> 4)] * 16 + (pos & 15);
-    for (int i = threadIdx.x; i < half; i += blockDim.x) {
-        double inv = pow(theta, -(double)i / (double)half);
-        double ang = (double)pos * inv;
-        cs[(size_t)t * half + i] = make_float2((float)cos(ang), (float)sin(ang));
+// Everything a step needs before its first projection, in one launch (four of them one after the other took 16 us, 5 of which are a launch's
+// own time each; together they take as long as the longest, the rotary table's float64 functions):
+//   rotary table   per packed row cos/sin of pos * theta^(-2i/D), evaluated in float64 and stored as float32, and where the row's K/V go
+//                  (16 * page + slot) -- the chain of dependent lookups behind that is then paid once, not in every layer
+//   work records   (bf16 models) per attention work item everything its workgroup needs to know before it can request its first
+//                  page, gathered into one 48-byte record -- otherwise each of the step's attention launches starts with a chain of
+//                  four dependent look-ups (item -> block -> request -> committed length); and the items' arrival counters, zero
+//                  [0] block  [1] kv head  [2] first page  [3] pages  [4] L = context length of the block  [5] rows of the block
+//                  [6] first packed row  [7] first entry of the block's page list  [8], [9] items of this (block, kv head): the
+//                  first (the others follow Hkv places apart), how many
+//   embedding      h[t,:] = E[token]; X[t,:] = rmsnorm(h) * gain
+struct step_setup {
+    const int32_t* len_dev;
+    int half, Hkv;
+    double theta;
+    float2* cs;
+    int32_t *kvslot, *plan, *arrive;
+    int n_arrive;
+    const int32_t* tokens;
+    const void* E;
+    int V, d;
+    float eps;
+    const float* gain;
+    float* h;
+    void* X;
+    size_t plane;
+    int rope_blocks, plan_blocks;
+};
+template <bool BF16>
+__global__ __launch_bounds__(256) void step_setup_kernel(sled_step_meta meta, step_setup a) {
+    __shared__ float sh[16];
+    if ((int)blockIdx.x < a.rope_blocks) {   // a wavefront per row
+        const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+        if (t >= meta.T) return;
+        const int b = meta.row_req[t];
+        const int pos = a.len_dev[meta.req_id[b]] + meta.pos0[b] + meta.row_j[t];
+        if (lane == 0) a.kvslot[t] = meta.pages[meta.cu_pages[b] + (pos >> 4)] * 16 + (pos & 15);
+        for (int i = lane; i < a.half; i += 64) {
+            double inv = pow(a.theta, -(double)i / (double)a.half);
+            double ang = (double)pos * inv;
+            a.cs[(size_t)t * a.half + i] = make_float2((float)cos(ang), (float)sin(ang));
+        }
+        return;
     }
-}
-
-// Per attention work item, once per step: everything its workgroup needs to know before it can request its first
-// page, gathered into one 48-byte record -- otherwise each of the step's attention launches starts with a chain of
-// four dependent look-ups (item -> block -> request -> committed length).
-//   [0] block  [1] kv head  [2] first page  [3] pages  [4] L = context length of the block  [5] rows of the block
-//   [6] first packed row  [7] first entry of the block's page list  [8], [9] items of this (block, kv head): the first (the others follow Hkv places apart), how many
-__global__ void attn_plan_kernel(sled_step_meta meta, const int32_t* __restrict__ len_dev, int Hkv, int32_t* __restrict__ plan) {
-    const int w = blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= meta.n_work) return;
-    const int b = meta.work[4 * w + 0], g = meta.work[4 * w + 1];
-    int32_t* r = plan + 12 * w;
-    r[0] = b;
-    r[1] = g;
-    r[2] = meta.work[4 * w + 2];
-    r[3] = meta.work[4 * w + 3];
-    r[4] = len_dev[meta.req_id[b]] + meta.pos0[b];
-    r[5] = meta.k[b] + 1;
-    r[6] = meta.cu_rows[b];
-    r[7] = meta.cu_pages[b];
-    r[8] = meta.cu_work[2 * (b * Hkv + g)];
-    r[9] = meta.cu_work[2 * (b * Hkv + g) + 1];
-    r[10] = r[11] = 0;
+    if ((int)blockIdx.x < a.rope_blocks + a.plan_blocks) {
+        const int w = (blockIdx.x - a.rope_blocks) * 256 + threadIdx.x;
+        if (w < a.n_arrive) a.arrive[w] = 0;   // each layer leaves them at zero
+        if (w >= meta.n_work) return;
+        const int b = meta.work[4 * w + 0], g = meta.work[4 * w + 1];
+        int32_t* r = a.plan + 12 * w;
+        r[0] = b;
+        r[1] = g;
+        r[2] = meta.work[4 * w + 2];
+        r[3] = meta.work[4 * w + 3];
+        r[4] = a.len_dev[meta.req_id[b]] + meta.pos0[b];
+        r[5] = meta.k[b] + 1;
+        r[6] = meta.cu_rows[b];
+        r[7] = meta.cu_pages[b];
+        r[8] = meta.cu_work[2 * (b * a.Hkv + g)];
+        r[9] = meta.cu_work[2 * (b * a.Hkv + g) + 1];
+        r[10] = r[11] = 0;
+        return;
+    }
+    const int t = blockIdx.x - a.rope_blocks - a.plan_blocks, d = a.d;
+    int tok = a.tokens[t];
+    tok = tok < 0 ? 0 : (tok >= a.V ? a.V - 1 : tok);
+    float ss = 0.f;
+    for (int c = threadIdx.x * 8; c < d; c += 256 * 8) {
+        float v[8];
+        if (BF16) {
+            uint4 raw = *reinterpret_cast<const uint4*>(static_cast<const bf16_t*>(a.E) + (size_t)tok * d + c);
+            const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+            for (int i = 0; i < 4; i++) {
+                v[2 * i] = bf16_to_f32((bf16_t)(w[i] & 0xffff));
+                v[2 * i + 1] = bf16_to_f32((bf16_t)(w[i] >> 16));
+            }
+        } else {
+            const float* p = static_cast<const float*>(a.E) + (size_t)tok * d + c;
+            for (int i = 0; i < 8; i++) v[i] = p[i];
+        }
+        for (int i = 0; i < 8; i++) {
+            a.h[(size_t)t * d + c + i] = v[i];
+            ss += v[i] * v[i];
+        }
+    }
+    const float tot = block_sum(ss, sh);
+    const float r = 1.0f / sqrtf(tot / (float)d + a.eps);
+    for (int c = threadIdx.x * 8; c < d; c += 256 * 8) {
+        float v[8];
+        for (int i = 0; i < 8; i++) v[i] = a.h[(size_t)t * d + c + i] * r * a.gain[c + i];
+        store_act8<BF16>(a.X, a.plane, t, c, d, v);
+    }
 }
 
 // Reduce the QKV partial sums of row t, rotate q and k, write q to Q[T, Hq, D] as a bf16 pair and k, v into the request's page slot for
@@ -406,13 +424,19 @@ __device__ inline void st_chunk(bf16_t* p, const chunk16& c, bool al) {
 }
 
 // Between positions first .. first+n_tok-1 of a request (first = *len when len is given) and [n_layers, n_tok, Hkv, D] in the
-// caller's buffers: INGEST into the pages, else out of them.  blockIdx.x counts the pages from the one that holds `first`.
+// caller's buffers: INGEST into the pages, else out of them.  blockIdx.x counts the pages from the one that holds `first`, blockIdx.z the
+// requests of the launch.
+struct kv_pieces {
+    sled_kv_piece p[SLED_KV_PIECES];
+};
 template <bool BF16, bool INGEST>
-__global__ __launch_bounds__(256) void kv_move_kernel(void* k_buf, void* v_buf, const int32_t* __restrict__ len, int first, int n_tok,
-                                                      int Hkv, int D, const int32_t* __restrict__ pages, void* k_pool, void* v_pool,
-                                                      int64_t n_pages, bool aligned, bool staged) {
+__global__ __launch_bounds__(256) void kv_move_kernel(kv_pieces pieces, int Hkv, int D, void* k_pool, void* v_pool, int64_t n_pages, bool staged) {
     extern __shared__ __attribute__((aligned(16))) uint4 stage[];
-    if (len) first = *len;
+    const sled_kv_piece& pc = pieces.p[blockIdx.z];
+    void *const k_buf = pc.k, *const v_buf = pc.v;
+    const int32_t* const pages = pc.pages;
+    const int first = pc.len ? *pc.len : pc.first, n_tok = pc.n_tok;
+    const bool aligned = ((reinterpret_cast<uintptr_t>(k_buf) | reinterpret_cast<uintptr_t>(v_buf)) & 15) == 0;   // rows are multiples of 256 bytes
     const int layer = blockIdx.y, lp = (first >> 4) + blockIdx.x;
     // slots lo .. hi-1 of this page take part; slot s is token s - off of the caller's buffers
     const int off = first - lp * 16, lo = max(off, 0), hi = min(16, off + n_tok);
@@ -561,15 +585,20 @@ __global__ __launch_bounds__(256) void copy_act_row_kernel(const void* __restric
 
 // len[req_ids[i]] += add[i]            (accept == nullptr)
 // len[req_ids[i]] += accept[i] + 1     (otherwise)
-__global__ void len_add_kernel(int32_t* __restrict__ len_dev, const int32_t* __restrict__ req_ids,
-                               const int32_t* __restrict__ add, const int32_t* __restrict__ accept, int B) {
+// committed lengths after an append (+ add[i]) or a commit (+ accept[i] + 1); `fresh`: the request starts from zero whatever the slot held
+__global__ void len_add_kernel(int32_t* __restrict__ len_dev, const int32_t* __restrict__ req_ids, const int32_t* __restrict__ add,
+                               const int32_t* __restrict__ fresh, const int32_t* __restrict__ accept, int B) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= B) return;
-    len_dev[req_ids[i]] += accept ? accept[i] + 1 : add[i];
+    const int r = req_ids[i], from = fresh && fresh[i] ? 0 : len_dev[r];
+    len_dev[r] = from + (accept ? accept[i] + 1 : add[i]);
 }
-
-__global__ void fill_i32_kernel(int32_t* p, int32_t v, size_t n) {
-    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x) p[e] = v;
+// the lengths of requests that have just been opened, up to 128 in a launch
+struct len_ids {
+    int id[128];
+};
+__global__ void len_zero_kernel(int32_t* __restrict__ len_dev, len_ids ids, int n) {
+    if ((int)threadIdx.x < n) len_dev[ids.id[threadIdx.x]] = 0;
 }
 
 // ----- weight repacking --------------------------------------------------------------------
@@ -712,14 +741,15 @@ int sled_launch_copy_gain(int dtype, const void* src, float* dst, int n, hipStre
     return SLED_OK;
 }
 
-int sled_launch_embed_norm(const sled_model* m, const int32_t* tokens, int T, float* h, void* X, size_t plane,
-                           const float* gain, hipStream_t st) {
-    if (m->s.dtype == SLED_BF16)
-        hipLaunchKernelGGL(embed_norm_kernel<true>, dim3(T), dim3(256), 0, st, tokens, m->embed, m->s.vocab, m->s.d_model,
-                           m->s.rms_eps, gain, h, X, plane);
-    else
-        hipLaunchKernelGGL(embed_norm_kernel<false>, dim3(T), dim3(256), 0, st, tokens, m->embed, m->s.vocab, m->s.d_model,
-                           m->s.rms_eps, gain, h, X, plane);
+int sled_launch_step_setup(const sled_model* m, const sled_kvpool* p, const sled_step_meta& meta, const int32_t* tokens, float* cs, int32_t* kvslot,
+                           int32_t* plan, int32_t* arrive, float* h, void* X, size_t plane, const float* gain, hipStream_t st) {
+    const bool bf = m->s.dtype == SLED_BF16;
+    step_setup a{p->len_dev, m->s.head_dim / 2, m->s.n_kv_heads, (double)m->s.rope_theta, reinterpret_cast<float2*>(cs), kvslot, plan, arrive,
+                 meta.B * m->s.n_kv_heads, tokens, m->embed, m->s.vocab, m->s.d_model, m->s.rms_eps, gain, h, X, plane, (meta.T + 3) / 4,
+                 bf ? (std::max(meta.n_work, meta.B * m->s.n_kv_heads) + 255) / 256 : 0};
+    const dim3 grid(a.rope_blocks + a.plan_blocks + meta.T);
+    if (bf) hipLaunchKernelGGL(step_setup_kernel<true>, grid, dim3(256), 0, st, meta, a);
+    else hipLaunchKernelGGL(step_setup_kernel<false>, grid, dim3(256), 0, st, meta, a);
     SLED_LAUNCH_CHECK();
     return SLED_OK;
 }
@@ -749,20 +779,6 @@ int sled_launch_copy_act_row(const sled_model* m, const void* X, size_t plane, i
         hipLaunchKernelGGL(copy_act_row_kernel<true>, dim3(grid), dim3(256), 0, st, X, plane, t, X1, plane1, d);
     else
         hipLaunchKernelGGL(copy_act_row_kernel<false>, dim3(grid), dim3(256), 0, st, X, plane, t, X1, plane1, d);
-    SLED_LAUNCH_CHECK();
-    return SLED_OK;
-}
-
-int sled_launch_rope_table(const sled_model* m, const sled_kvpool* p, const sled_step_meta& meta, float* cs, int32_t* kvslot,
-                           hipStream_t st) {
-    hipLaunchKernelGGL(rope_table_kernel, dim3(meta.T), dim3(64), 0, st, meta, p->len_dev, m->s.head_dim / 2,
-                       (double)m->s.rope_theta, reinterpret_cast<float2*>(cs), kvslot);
-    SLED_LAUNCH_CHECK();
-    return SLED_OK;
-}
-
-int sled_launch_attn_plan(const sled_model* m, const sled_kvpool* p, const sled_step_meta& meta, int32_t* plan, hipStream_t st) {
-    hipLaunchKernelGGL(attn_plan_kernel, dim3((meta.n_work + 63) / 64), dim3(64), 0, st, meta, p->len_dev, m->s.n_kv_heads, plan);
     SLED_LAUNCH_CHECK();
     return SLED_OK;
 }
@@ -801,45 +817,54 @@ int sled_launch_swiglu_reduce(const sled_model* m, const float* gu, int n_split,
 
 // `len`: device-side committed length of the request, its first position (ingest), or nullptr and `first` (export)
 template <bool INGEST>
-static int launch_kv_move(const sled_model* m, const sled_kvpool* p, void* k, void* v, const int32_t* len, int first, int n_tokens,
-                          const int32_t* pages_dev, hipStream_t st) {
-    // where the first token sits inside its page is not known here when the device knows the length: one page more
-    const dim3 grid((n_tokens + 30) / 16, m->s.n_layers);
-    const bool aligned = ((reinterpret_cast<uintptr_t>(k) | reinterpret_cast<uintptr_t>(v)) & 15) == 0;   // rows are multiples of 256 bytes
+static int launch_kv_move(const sled_model* m, const sled_kvpool* p, const sled_kv_piece* pieces, int n, hipStream_t st) {
     // a page's V of one layer, 4 KiB a head, for three workgroups on a CU or more
     const size_t stage = INGEST && m->s.dtype == SLED_BF16 && m->s.n_kv_heads <= 12 ? (size_t)m->s.n_kv_heads * 4096 : 0;
-    if (m->s.dtype == SLED_BF16)
-        hipLaunchKernelGGL((kv_move_kernel<true, INGEST>), grid, dim3(256), stage, st, k, v, len, first, n_tokens, m->s.n_kv_heads,
-                           m->s.head_dim, pages_dev, p->k_pool, p->v_pool, p->n_pages, aligned, stage > 0);
-    else
-        hipLaunchKernelGGL((kv_move_kernel<false, INGEST>), grid, dim3(256), 0, st, k, v, len, first, n_tokens, m->s.n_kv_heads,
-                           m->s.head_dim, pages_dev, p->k_pool, p->v_pool, p->n_pages, aligned, stage > 0);
-    SLED_LAUNCH_CHECK();
+    for (int i0 = 0; i0 < n; i0 += SLED_KV_PIECES) {
+        kv_pieces ks{};
+        const int here = std::min(n - i0, SLED_KV_PIECES);
+        int most = 0;
+        for (int i = 0; i < here; i++) {
+            ks.p[i] = pieces[i0 + i];
+            most = std::max(most, ks.p[i].n_tok);
+        }
+        // where the first token sits inside its page is not known here when the device knows the length: one page more
+        const dim3 grid((most + 30) / 16, m->s.n_layers, here);
+        if (m->s.dtype == SLED_BF16)
+            hipLaunchKernelGGL((kv_move_kernel<true, INGEST>), grid, dim3(256), stage, st, ks, m->s.n_kv_heads, m->s.head_dim, p->k_pool, p->v_pool,
+                               p->n_pages, stage > 0);
+        else
+            hipLaunchKernelGGL((kv_move_kernel<false, INGEST>), grid, dim3(256), 0, st, ks, m->s.n_kv_heads, m->s.head_dim, p->k_pool, p->v_pool,
+                               p->n_pages, false);
+        SLED_LAUNCH_CHECK();
+    }
     return SLED_OK;
 }
 
-int sled_launch_kv_ingest(const sled_model* m, const sled_kvpool* p, const void* k_src, const void* v_src, int n_tokens,
-                          int req_id, const int32_t* pages_dev, hipStream_t st) {
-    return launch_kv_move<true>(m, p, const_cast<void*>(k_src), const_cast<void*>(v_src), p->len_dev + req_id, 0, n_tokens, pages_dev, st);
+int sled_launch_kv_ingest(const sled_model* m, const sled_kvpool* p, const sled_kv_piece* pieces, int n, hipStream_t st) {
+    return launch_kv_move<true>(m, p, pieces, n, st);
 }
 
 int sled_launch_kv_export(const sled_model* m, const sled_kvpool* p, void* k_dst, void* v_dst, int first, int n_tokens,
                           const int32_t* pages_dev, hipStream_t st) {
-    return launch_kv_move<false>(m, p, k_dst, v_dst, nullptr, first, n_tokens, pages_dev, st);
+    const sled_kv_piece pc{k_dst, v_dst, pages_dev, nullptr, first, n_tokens};
+    return launch_kv_move<false>(m, p, &pc, 1, st);
 }
 
-int sled_launch_len_add(int32_t* len_dev, const int32_t* req_ids_dev, const int32_t* add_dev, const int32_t* accept_dev,
+int sled_launch_len_add(int32_t* len_dev, const int32_t* req_ids_dev, const int32_t* add_dev, const int32_t* fresh_dev, const int32_t* accept_dev,
                         int B, hipStream_t st) {
-    hipLaunchKernelGGL(len_add_kernel, dim3((B + 63) / 64), dim3(64), 0, st, len_dev, req_ids_dev, add_dev, accept_dev, B);
+    hipLaunchKernelGGL(len_add_kernel, dim3((B + 63) / 64), dim3(64), 0, st, len_dev, req_ids_dev, add_dev, fresh_dev, accept_dev, B);
     SLED_LAUNCH_CHECK();
     return SLED_OK;
 }
 
-int sled_launch_fill_i32(int32_t* p, int32_t v, size_t n, hipStream_t st) {
-    int grid = (int)((n + 255) / 256);
-    if (grid > 4096) grid = 4096;
-    if (grid < 1) grid = 1;
-    hipLaunchKernelGGL(fill_i32_kernel, dim3(grid), dim3(256), 0, st, p, v, n);
-    SLED_LAUNCH_CHECK();
+int sled_launch_len_zero(int32_t* len_dev, const int* req_ids /*host*/, int n, hipStream_t st) {
+    for (int i0 = 0; i0 < n; i0 += 128) {
+        len_ids ids{};
+        const int here = std::min(n - i0, 128);
+        for (int i = 0; i < here; i++) ids.id[i] = req_ids[i0 + i];
+        hipLaunchKernelGGL(len_zero_kernel, dim3(1), dim3(128), 0, st, len_dev, ids, here);
+        SLED_LAUNCH_CHECK();
+    }
     return SLED_OK;
 }

@@ -249,25 +249,30 @@ int sled_launch_pack_scales_w4(const void* src, void* dst, int rows, int K, int 
 // row t of an activation buffer -> row 0 of a one-tile buffer (the single row the LM head is asked for)
 int sled_launch_copy_act_row(const sled_model* m, const void* X, size_t plane, int t, void* X1, size_t plane1, int d,
                              hipStream_t st);
-int sled_launch_embed_norm(const sled_model* m, const int32_t* tokens, int T, float* h, void* X, size_t plane,
-                           const float* gain, hipStream_t st);
 int sled_launch_residual_norm(const sled_model* m, const float* partial, int n_split, int T, int T_pad, float* h, void* X,
                               size_t plane, const float* gain, hipStream_t st);
-// per packed row: the rotary table cs[T][head_dim/2] and kvslot[T] = 16 * page + slot of the row's position in the cache
-int sled_launch_rope_table(const sled_model* m, const sled_kvpool* p, const sled_step_meta& meta, float* cs, int32_t* kvslot,
-                           hipStream_t st);
-// one record of 12 ints per attention work item (see attn_plan_kernel)
-int sled_launch_attn_plan(const sled_model* m, const sled_kvpool* p, const sled_step_meta& meta, int32_t* plan, hipStream_t st);
+// everything a step needs before its first projection: the rotary table cs[T][head_dim/2] and kvslot[T] = 16 * page + slot of the row's position
+// in the cache, one record of 12 ints per attention work item and zeroed arrival counters (bf16 models), h and X of the first layer
+int sled_launch_step_setup(const sled_model* m, const sled_kvpool* p, const sled_step_meta& meta, const int32_t* tokens, float* cs, int32_t* kvslot,
+                           int32_t* plan, int32_t* arrive, float* h, void* X, size_t plane, const float* gain, hipStream_t st);
 int sled_launch_qkv_rope_store(const sled_model* m, const sled_kvpool* p, int T, int layer, const float* partial, int n_split,
                                int T_pad, const float* cs, const int32_t* kvslot, void* Q, size_t q_plane, hipStream_t st);
 int sled_launch_swiglu_reduce(const sled_model* m, const float* gu, int n_split, int T, int T_pad, void* A, size_t plane,
                               hipStream_t st);
-int sled_launch_kv_ingest(const sled_model* m, const sled_kvpool* p, const void* k_src, const void* v_src, int n_tokens,
-                          int req_id, const int32_t* pages_dev, hipStream_t st);
+// one request's share of an append or a read: n_tok tokens between the caller's k, v and the request's pages, from position *len (or first)
+struct sled_kv_piece {
+    void *k, *v;
+    const int32_t *pages, *len;
+    int first, n_tok;
+};
+constexpr int SLED_KV_PIECES = 16;   // of a launch
+int sled_launch_kv_ingest(const sled_model* m, const sled_kvpool* p, const sled_kv_piece* pieces, int n, hipStream_t st);
 int sled_launch_kv_export(const sled_model* m, const sled_kvpool* p, void* k_dst, void* v_dst, int first, int n_tokens,
                           const int32_t* pages_dev, hipStream_t st);
-int sled_launch_len_add(int32_t* len_dev, const int32_t* req_ids_dev, const int32_t* add_dev, const int32_t* accept_dev,
+// fresh_dev (or nullptr): nonzero where a request starts from length zero
+int sled_launch_len_add(int32_t* len_dev, const int32_t* req_ids_dev, const int32_t* add_dev, const int32_t* fresh_dev, const int32_t* accept_dev,
                         int B, hipStream_t st);
+int sled_launch_len_zero(int32_t* len_dev, const int* req_ids /*host*/, int n, hipStream_t st);
 
 // gemm.hip:  out = X[T, K] * W[N, K]^T
 enum { SLED_EPI_PARTIAL = 0, SLED_EPI_SWIGLU = 1, SLED_EPI_STORE = 2 };
@@ -291,7 +296,6 @@ int sled_launch_attention(const sled_model* m, const sled_kvpool* p, const sled_
                           size_t q_plane, const float* qkv_partial, int n_split, int T_pad, const float* cs,
                           const int32_t* kvslot, const int32_t* plan, float* part_o, float* part_ml, int32_t* arrive,
                           void* X_out, size_t x_plane, int QT, hipStream_t st);
-int sled_launch_fill_i32(int32_t* p, int32_t v, size_t n, hipStream_t st);
 
 // accept.hip
 size_t sled_accept_ws_bytes(int B, int T, int n_split);               // the least that is accepted
