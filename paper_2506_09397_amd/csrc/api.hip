@@ -1033,8 +1033,10 @@ extern "C" int sled_prefill(sled_model* m, sled_kvpool* p, int req_id, int n_tok
     hipStream_t st = static_cast<hipStream_t>(stream);
     const sled_shape& s = m->s;
     // Rows of one block.  Every block reads all keys before it, so longer blocks mean fewer passes over the cache:
-    // a prompt takes the most rows the attention kernel's five query tiles hold (80 stacked (head, row) pairs per kv
-    // head: 20 tokens at four query heads per kv head), not the k_max + 1 of a verification request.  A batch-invariant
+    // a prompt takes the most rows that four query tiles of the attention kernel hold (64 stacked (head, row) pairs per kv
+    // head: 16 tokens at four query heads per kv head), not the k_max + 1 of a verification request.  (Five tiles hold more, but their
+    // two page groups deal ten wavefronts out to four SIMDs: 700 tokens 28.4 us a layer against 26.5.  They are taken where four hold no
+    // more than a verification's block does: eight query heads per kv head.)  A batch-invariant
     // model keeps k_max + 1, the block its fixed summation order is defined for.
     const int G = s.n_q_heads / s.n_kv_heads;
     const int64_t reach = (int64_t)p->reqs[req_id].len_ub + n_tokens;  // every block of a slice may see that many keys
@@ -1055,7 +1057,7 @@ extern "C" int sled_prefill(sled_model* m, sled_kvpool* p, int req_id, int n_tok
     if (s.dtype == SLED_BF16 && !m->batch_invariant) {
         // long blocks only where they still leave a work item for every CU: a small workspace (short slices) is
         // better served by many short blocks (measured: 126-row slices 15 % slower with 20-row blocks)
-        const int big = std::max(per, 80 / G), big_qt = ceil_div(G * big, 16);
+        const int big = 64 / G > per ? 64 / G : std::max(per, 80 / G), big_qt = ceil_div(G * big, 16);
         if (big > per && (int64_t)most_blocks(big, big_qt) * s.n_kv_heads >= 256) {
             per = big;
             QT = big_qt;
@@ -1070,7 +1072,33 @@ extern "C" int sled_prefill(sled_model* m, sled_kvpool* p, int req_id, int n_tok
         if (fits(mid)) lo = mid;
         else hi = mid - 1;
     }
-    const int blocks_per_step = lo;
+    int blocks_per_step = lo;
+    // A prompt in several slices: as long as the workspace allows is not always best, since the projections round rows up to whole tiles and
+    // workgroups to whole rounds, and a last slice of a few rows costs the whole weight stream.  The slice length is the one whose
+    // slices, the last one included, are estimated to take least (8B shape, ms, longest slices of 20-row blocks / longest of 16 / these): 1500
+    // tokens and a workspace of 60 requests 48.3 / 42.5 / 42.5, 3000 and 200 80.0 / 81.8 / 78.2, 4001 and 112 116.4 / 110.5 / 110.3.
+    if (s.dtype == SLED_BF16 && !m->batch_invariant && ceil_div(n_tokens, per) > lo) {
+        constexpr double SLICE_US = 30.0;   // a layer's other kernels, whatever the rows
+        const int d = s.d_model, HD = s.n_q_heads * s.head_dim;
+        const struct { int N, K; sled_gemm_plan plan; } proj[4] = {{m->n_qkv, d, sled_gemm_make_plan(m, m->n_qkv, d, false)},
+                                                                   {d, HD, sled_gemm_make_plan(m, d, HD, false)},
+                                                                   {2 * s.d_ffn, d, sled_gemm_make_plan(m, 2 * s.d_ffn, d, false)},
+                                                                   {d, s.d_ffn, sled_gemm_make_plan(m, d, s.d_ffn, false)}};
+        auto slice_us = [&](int rows) {
+            double us = SLICE_US;
+            for (const auto& p4 : proj) us += sled_gemm_estimate_us(m, p4.plan, p4.N, p4.K, rows);
+            return us;
+        };
+        double best_us = -1.0;
+        for (int blocks = lo; blocks >= ceil_div(lo, 2); blocks--) {
+            const int rows = blocks * per, rest = n_tokens % rows;
+            const double us = n_tokens / rows * slice_us(rows) + (rest ? slice_us(rest) : 0.0);
+            if (best_us < 0 || us < best_us) {
+                best_us = us;
+                blocks_per_step = blocks;
+            }
+        }
+    }
     sled_request& rq = p->reqs[req_id];
     poll_readbacks(p);
     if ((rc = reset_fresh_lengths(p, 1, &req_id, st)) != SLED_OK) return rc;

@@ -1173,14 +1173,24 @@ extern "C" int sled_projection_slices(int n_out, int n_in, int T, int* slices /*
 // rows cost about the same at either height, and what the choice gives is better filled rounds: 372 rows x 4096 x 28672 are 336
 // workgroups in two rounds at 4 row tiles (187 us) and 224 in one round at 6 (142 us); 220 x 8192 x 57344 are 448 in two
 // rounds at either (415 and 556 us).
-static int tile_height(int N, int K, int T_pad, int split) {
+static double tile_us(int h, int N, int K, int T_pad, int split) {
     constexpr double FIXED_US = 9.0, STEP4_US = 0.40, STEP6_US = 0.59;
     const int n_col = (N / 32 + TILE_CT - 1) / TILE_CT, steps = (K / 16 / TILE_UNIT + split - 1) / split * TILE_UNIT;   // of the longest slice
-    auto us = [&](int h, double step_us) {
-        const int64_t wgs = (int64_t)n_col * ((T_pad / 32 + h - 1) / h) * split;
-        return (double)((wgs + 255) / 256) * (FIXED_US + steps * step_us);
-    };
-    return us(6, STEP6_US) < us(4, STEP4_US) ? 6 : 4;
+    const int64_t wgs = (int64_t)n_col * ((T_pad / 32 + h - 1) / h) * split;
+    return (double)((wgs + 255) / 256) * (FIXED_US + steps * (h == 6 ? STEP6_US : STEP4_US));
+}
+static int tile_height(int N, int K, int T_pad, int split) {
+    return tile_us(6, N, K, T_pad, split) < tile_us(4, N, K, T_pad, split) ? 6 : 4;
+}
+
+// The same estimate of a whole projection of T rows, partial sums included; up to 128 rows the weight stream and a launch.
+double sled_gemm_estimate_us(const sled_model* m, sled_gemm_plan base, int N, int K, int T) {
+    constexpr double LAUNCH_US = 9.0, STREAM_BYTES_PER_US = 5.0e6, PARTIAL_BYTES_PER_US = 4.0e6;
+    const int T_pad = (T + 31) / 32 * 32;
+    if (T_pad <= 128) return LAUNCH_US + (double)N * K * m->wbits / 8 / STREAM_BYTES_PER_US;
+    const int split = plan_for_rows(base, N, K, T_pad).split;
+    const double us = tile_us(m->wbits == 16 ? tile_height(N, K, T_pad, split) : 4, N, K, T_pad, split);
+    return us + (base.cap > 1 ? 2.0 * split * (double)T_pad * N * 4.0 / PARTIAL_BYTES_PER_US : 0.0);
 }
 
 extern "C" int sled_projection_rows(int n_out, int n_in, int T, int* rows /*host out*/) {
