@@ -80,7 +80,7 @@ __global__ __launch_bounds__(64 * (QT + 1) * attn_groups(QT)) void attn_bf16_ker
     __shared__ int sh_last;
 
     const int w = blockIdx.x;
-    // the work item's record, written once per step by attn_plan_kernel: one look-up instead of a chain of four
+    // the work item's record, written once per step by step_setup_kernel: one look-up instead of a chain of four
     const int32_t* rec = plan + 12 * w;
     const int b = rec[0], g = rec[1];
     const int page0 = rec[2], npg = rec[3];
