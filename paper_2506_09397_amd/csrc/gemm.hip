@@ -36,6 +36,7 @@
 //     anything else is they push the partial sums and activations, which the next kernel reads, out of Infinity Cache.  Layer
 //     times of the 8B shape without and with it, us: 58 rows 146.5-150 -> 140.6-143 (16-bit), 132 -> 128 (8-bit), 86 rows 170-173 -> 168,
 //     101 rows 188-190 -> 185; 70B shape, 220 rows 868-873 -> 857-862: the row kernels gain as much as the projections.
+//     The tile kernel keeps the ordinary order where two unequal row blocks share the weights (see its launch).
 //   - Split-K over blockIdx.y gives every CU work on the narrow projections; partial sums go to a
 //     [split, T, N] fp32 buffer that the following row kernel reduces in a fixed order (no float
 //     atomics: results are reproducible run to run).
@@ -510,8 +511,8 @@ constexpr int tile_ring(int RT, int CT, int U) { return std::min(160 / tile_stag
 // where accumulation registers are read into ordinary ones first.
 constexpr int tile_sums(int RT, int CT, int U) { return 2 * U * RT * CT / TILE_WAVES; }
 
-// RT, CT: row and column tiles of the workgroup; U: k-steps per stage
-template <int RT, int CT, int U, int EPI>
+// RT, CT: row and column tiles of the workgroup; U: k-steps per stage; KEEP: weights in the caches' ordinary order
+template <int RT, int CT, int U, int EPI, bool KEEP>
 __global__ __launch_bounds__(64 * TILE_WAVES, tile_sums(RT, CT, U) <= 8 ? 2 : 1) void gemm_tile_kernel(const bf16_t* __restrict__ Xp, size_t x_plane,
                                                                        const bf16_t* __restrict__ Wp, int NT, int KS, int n_col,
                                                                        int n_split, int n_zb, int T, int T_pad, int N,
@@ -576,7 +577,10 @@ __global__ __launch_bounds__(64 * TILE_WAVES, tile_sums(RT, CT, U) <= 8 ? 2 : 1)
         } else {
             const int a = j < XL ? 0 : j - XL;
             const unsigned dst = __builtin_amdgcn_readfirstlane(slot + (XT + a * TILE_WAVES) * 1024);
-            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(woff), "s"(wsrc[a]), "s"(dst) : "memory");
+            if constexpr (KEEP)
+                asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(woff), "s"(wsrc[a]), "s"(dst) : "memory");
+            else
+                asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(woff), "s"(wsrc[a]), "s"(dst) : "memory");
             wsrc[a] += wstep;
         }
     };
@@ -1049,10 +1053,10 @@ int launch_one(const gemm_args& a) {
     return SLED_OK;
 }
 
-template <int RT, int CT, int U, int EPI>
+template <int RT, int CT, int U, int EPI, bool KEEP>
 int launch_tile_one(const gemm_args& a) {
     static bool allowed = false;
-    auto kern = gemm_tile_kernel<RT, CT, U, EPI>;
+    auto kern = gemm_tile_kernel<RT, CT, U, EPI, KEEP>;
     if (!allowed) {
         SLED_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds));
         allowed = true;
@@ -1078,12 +1082,12 @@ int launch_kwave(int epi, const gemm_args& a) {
     return SLED_OK;
 }
 
-template <int RT, int CT = TILE_CT, int U = 1>
+template <int RT, int CT = TILE_CT, int U = 1, bool KEEP = false>
 int launch_tile(int epi, const gemm_args& a) {
     switch (epi) {
-        case SLED_EPI_PARTIAL: return launch_tile_one<RT, CT, U, SLED_EPI_PARTIAL>(a);
-        case SLED_EPI_SWIGLU: return launch_tile_one<RT, CT, U, SLED_EPI_SWIGLU>(a);
-        default: return launch_tile_one<RT, CT, U, SLED_EPI_STORE>(a);
+        case SLED_EPI_PARTIAL: return launch_tile_one<RT, CT, U, SLED_EPI_PARTIAL, KEEP>(a);
+        case SLED_EPI_SWIGLU: return launch_tile_one<RT, CT, U, SLED_EPI_SWIGLU, KEEP>(a);
+        default: return launch_tile_one<RT, CT, U, SLED_EPI_STORE, KEEP>(a);
     }
 }
 
@@ -1253,7 +1257,12 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
             a.n_zb = (mt_total + RT - 1) / RT;
             a.grid = dim3((a.n_col * a.n_split + 7) / 8 * 8 * a.n_zb, 1, 1);
             a.lds = (size_t)tile_ring(RT, TILE_CT, 1) * tile_stage_kib(RT, TILE_CT, 1) * 1024;
-            return RT == 6 ? launch_tile<6>(epilogue, a) : launch_tile<4>(epilogue, a);
+            if (RT == 6) return launch_tile<6>(epilogue, a);
+            // Two row blocks read the same weights, and where the second holds at most half the rows of the first it runs ahead of it: the weights
+            // it has passed must still be in a cache then, so they are loaded in the caches' ordinary order (steps of the 8B shape, past the order /
+            // in it: 144 rows 7.96 / 7.83 ms, 160 8.18 / 8.03, 192 8.23 / 8.20; with the second block fuller or more of them it is the other way
+            // round: 224 rows 8.49 / 8.54, 256 8.57 / 8.68, 384 11.77 / 11.81, 512 15.02 / 15.11).
+            return a.n_zb == 2 && mt_total - RT <= RT / 2 ? launch_tile<4, TILE_CT, 1, true>(epilogue, a) : launch_tile<4>(epilogue, a);
         }
         if (wide)
             return m->wbits == 8 ? launch_epi_wb<4, WIDE_KG, WIDE_CG, 8>(epilogue, a) : launch_epi_wb<4, WIDE_KG, WIDE_CG, 4>(epilogue, a);
