@@ -66,7 +66,7 @@ constexpr int AHEAD = DEPTH + 1;  // activation stages in flight beyond the one 
 constexpr int NXB = AHEAD + 1;    // LDS ring
 // Two workgroup shapes (KG k-groups = k-steps of 16 per stage, CG column groups of 64 columns):
 //   narrow  KG 4, CG 2: 128 columns, 64 k per stage.  Most workgroups per projection: the shape for one block of
-//           rows (up to 128) of 8- and 4-bit weights, for three row tiles of any weights, and for batch-invariant models at any size, where the chip has to be filled by column blocks and K slices alone.
+//           33 to 128 rows of 8- and 4-bit weights, for three row tiles of any weights, and for batch-invariant models at any size, where the chip has to be filled by column blocks and K slices alone.
 //   wide    KG 2, CG 4: 256 columns, 32 k per stage.  Per MFMA it fetches two thirds of the bytes (half the
 //           activations, the same weights): the shape for several row blocks of 8- and 4-bit weights, where the
 //           workgroups are many anyway and the L2 -> CU path, not HBM, is what the MFMAs wait for (bf16 weights: the
@@ -1268,8 +1268,10 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
             return m->wbits == 8 ? launch_epi_wb<4, WIDE_KG, WIDE_CG, 8>(epilogue, a) : launch_epi_wb<4, WIDE_KG, WIDE_CG, 4>(epilogue, a);
         // up to 32 rows, and 4-bit weights up to 64 in long slices: the k-wave kernel (whose results do not depend on the choice either,
         // so batch-invariant models take it too)
-        const int slice = KS / plan.split;   // whole and equal for every plan of one block of rows
-        if (mt_total <= 2 && KS % plan.split == 0 && slice % KW_MIN_STEPS == 0) {
+        const int slice = KS / plan.split;
+        if (mt_total <= 4 && (KS % plan.split || slice % KW_MIN_STEPS))   // every plan of one block of rows has equal slices of whole trips
+            SLED_FAIL(SLED_EINVAL, "gemm: %d k-steps in %d slices", KS, plan.split);
+        if (mt_total <= 2) {
             const bool deep = m->wbits == 4 && slice >= KW_DEEP_STEPS;
             a.n_col = (NT + KW_CT - 1) / KW_CT;
             if (mt_total == 1) {
@@ -1286,14 +1288,10 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
             a.n_col = (NT + SLIM_CT - 1) / SLIM_CT;
             a.grid = dim3((a.n_col * a.n_split + 7) / 8 * 8, 1, 1);
             a.lds = (size_t)tile_ring(MT, SLIM_CT, SLIM_U) * tile_stage_kib(MT, SLIM_CT, SLIM_U) * 1024;
-            switch (MT) {
-                case 2: return launch_tile<2, SLIM_CT, SLIM_U>(epilogue, a);
-                default: return launch_tile<4, SLIM_CT, SLIM_U>(epilogue, a);
-            }
+            return MT == 2 ? launch_tile<2, SLIM_CT, SLIM_U>(epilogue, a) : launch_tile<4, SLIM_CT, SLIM_U>(epilogue, a);
         }
         if (broad) return launch_epi<4, BROAD_KG, BROAD_CG>(epilogue, a);
         switch (MT) {
-            case 1: return launch_epi<1, NARROW_KG, NARROW_CG>(epilogue, a);
             case 2: return launch_epi<2, NARROW_KG, NARROW_CG>(epilogue, a);
             case 3: return launch_epi<3, NARROW_KG, NARROW_CG>(epilogue, a);
             default: return launch_epi<4, NARROW_KG, NARROW_CG>(epilogue, a);

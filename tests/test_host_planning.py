@@ -120,6 +120,7 @@ def test_projection_slices_of_the_benchmark_model():
             assert 1 <= s <= cap and s <= K // 256        # every slice holds at least one trip of the stage loop
             if T <= 128:
                 assert s == sled.sled_projection_slices(N, K, 1)[0]
+                assert K % (256 * s) == 0                     # equal slices of whole trips of 16 k-steps: what the kernels of one block of rows assume
     with pytest.raises(Exception):
         sled.sled_projection_slices(100, 4096, 10)
 
