@@ -760,6 +760,7 @@ __global__ __launch_bounds__(64 * TILE_WAVES, tile_sums(RT, CT, U) <= 8 ? 2 : 1)
 constexpr int KW_CT = 4, KW_WAVES = 4;
 constexpr int KW_MIN_STEPS = 16;     // k-steps of a slice come in multiples of this
 constexpr int KW_DEEP_STEPS = 256;   // 4-bit slices from here on are long: the 8B shape's gate/up and LM head have 256, its down projection 112
+static_assert(KW_DEEP_STEPS >= 8 * KW_WAVES, "eight sets are filled before the loop");
 constexpr int kw_lds(int RT) { return KW_WAVES * KW_CT * RT * 4096; }
 
 // SETS: k-steps whose operands are in registers or on their way
@@ -892,7 +893,7 @@ __global__ __launch_bounds__(64 * KW_WAVES, 1) void gemm_kwave_kernel(const bf16
     typedef integral_constant<int, SETS - 4> high;
     static_assert(SETS == 4 || SETS == 8, "the trips are written for one or two halves of four sets");
     request(low{}, 0);
-    if (SETS == 8 && n > 4) request(high{}, 4);
+    if (SETS == 8) request(high{}, 4);   // n is a multiple of 4 and at least KW_DEEP_STEPS / KW_WAVES here
     if (WB != 16) {
 #pragma unroll
         for (int a = 0; a < KW_CT; a++) wb[0][a] = widened(set[0], a);
@@ -906,10 +907,10 @@ __global__ __launch_bounds__(64 * KW_WAVES, 1) void gemm_kwave_kernel(const bf16
             trip(low{}, true, s);
             trip(high{}, true, s + 4);
         }
-        // 4, 8 or 12 steps are left
+        // 8 or 12 steps are left
         const bool third = s + 8 < n;
         trip(low{}, third, s);
-        if (s + 4 < n) trip(high{}, false, s);
+        trip(high{}, false, s);
         if (third) trip(low{}, false, s);
     }
 

@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 
 WEIGHTS = {16: synth.SynthWeights, 8: synth.SynthWeightsW8, 4: synth.SynthWeightsW4}
 # a vocabulary whose last column block holds two of its four column tiles
-SHAPES = {"tiny": synth.SHAPES["tiny_bf16"], "8b_layer": synth.scaled_shape(synth.SHAPES["llama8b"], n_layers=1, vocab=1024 + 64)}
+SHAPES = {"tiny": synth.SHAPES["tiny_bf16"], "8b_layer": synth.scaled_shape(synth.SHAPES["llama8b"], n_layers=1, vocab=1024 + 64),
+          # 272 k-steps, whole: 68 to a wavefront, so the eight-set loop of 4-bit weights ends with twelve steps left instead of eight
+          "272_steps": synth.scaled_shape(synth.SHAPES["llama8b"], n_layers=1, d_model=4352, d_ffn=1024, vocab=1024 + 64)}
 
 
 @pytest.mark.parametrize("shape", SHAPES)
