@@ -36,7 +36,7 @@
 //     anything else is they push the partial sums and activations, which the next kernel reads, out of Infinity Cache.  Layer
 //     times of the 8B shape without and with it, us: 58 rows 146.5-150 -> 140.6-143 (16-bit), 132 -> 128 (8-bit), 86 rows 170-173 -> 168,
 //     101 rows 188-190 -> 185; 70B shape, 220 rows 868-873 -> 857-862: the row kernels gain as much as the projections.
-//     The tile kernel keeps the ordinary order where two unequal row blocks share the weights (see its launch).
+//     The ordinary order is kept where two unequal row blocks share the weights and for models that a cache holds (see the launches).
 //   - Split-K over blockIdx.y gives every CU work on the narrow projections; partial sums go to a
 //     [split, T, N] fp32 buffer that the following row kernel reduces in a fixed order (no float
 //     atomics: results are reproducible run to run).
@@ -150,7 +150,7 @@ __device__ __forceinline__ void store_cols(const float4_t v, int tok, int n, int
 // tiles come with ONE load per stage, are widened to bf16 in registers, and the accumulators are multiplied by the
 // columns' scales on the way out.  4 (see w4_offset): one 8-byte load per stage for the codes and one 2-byte load
 // for the two rows' block scales, which the widening instruction applies.
-template <int MT, int EPI, int KG, int CG, int WB>
+template <int MT, int EPI, int KG, int CG, int WB, bool KEEP>
 __global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(const bf16_t* __restrict__ Xp, size_t x_plane,
                                                                const bf16_t* __restrict__ Wp,
                                                                const void* __restrict__ scale_v, int NT, int KS,
@@ -247,13 +247,18 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(const bf16_t* __r
     auto w_issue_one = [&](int buf, int stage, int a) {  // a: which of the stage's NWL + NSL weight-side loads
         const bf16_t* src = wsrc[a < NWL ? a : 0] + (size_t)stage * KG * NTW * WBLK;
         if (W4) {
-            if (a == 0)
-                asm volatile("global_load_dwordx2 %0, %1, off nt" : "=&v"(w4reg[buf]) : "v"(src) : "memory");
-            else
+            if (a == 0) {
+                if constexpr (KEEP)
+                    asm volatile("global_load_dwordx2 %0, %1, off" : "=&v"(w4reg[buf]) : "v"(src) : "memory");
+                else
+                    asm volatile("global_load_dwordx2 %0, %1, off nt" : "=&v"(w4reg[buf]) : "v"(src) : "memory");
+            } else
                 asm volatile("global_load_ushort %0, %1, off"
                              : "=&v"(sreg[buf])
                              : "v"(ssrc + (size_t)((ks_begin + kgi + stage * KG) >> 1) * NTW * 64)  // a k-block is two k-steps
                              : "memory");
+        } else if constexpr (KEEP) {
+            asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(wreg[buf][a]) : "v"(src) : "memory");
         } else {
             asm volatile("global_load_dwordx4 %0, %1, off nt" : "=&v"(wreg[buf][a]) : "v"(src) : "memory");
         }
@@ -763,8 +768,8 @@ constexpr int KW_DEEP_STEPS = 256;   // 4-bit slices from here on are long: the 
 static_assert(KW_DEEP_STEPS >= 8 * KW_WAVES, "eight sets are filled before the loop");
 constexpr int kw_lds(int RT) { return KW_WAVES * KW_CT * RT * 4096; }
 
-// SETS: k-steps whose operands are in registers or on their way
-template <int RT, int WB, int SETS>
+// SETS: k-steps whose operands are in registers or on their way; KEEP: weights in the caches' ordinary order
+template <int RT, int WB, int SETS, bool KEEP>
 __global__ __launch_bounds__(64 * KW_WAVES, 1) void gemm_kwave_kernel(const bf16_t* __restrict__ Xp, size_t x_plane,
                                                                       const unsigned char* __restrict__ Wp, const void* __restrict__ scale_v,
                                                                       int NT, int KS, int n_col, int n_split, int T, int T_pad, int N,
@@ -815,7 +820,9 @@ __global__ __launch_bounds__(64 * KW_WAVES, 1) void gemm_kwave_kernel(const bf16
         o.x[pl][b] = *reinterpret_cast<const bf16x8_t*>(xsrc[pl] + (size_t)s * (KW_WAVES * 1024) + xoff[b]);
     };
     auto load_w = [&](operands& o, int i, int s) {
-        o.w[i] = __builtin_nontemporal_load(reinterpret_cast<const wreg_t*>(wsrc + (size_t)s * KW_WAVES * rowb + woff[i]));
+        const wreg_t* p = reinterpret_cast<const wreg_t*>(wsrc + (size_t)s * KW_WAVES * rowb + woff[i]);
+        if constexpr (KEEP) o.w[i] = *p;
+        else o.w[i] = __builtin_nontemporal_load(p);
         if (WB == 4) o.sc[i] = *reinterpret_cast<const uint16_t*>(ssrc + (size_t)s * (KW_WAVES / 2) * (NT / 2) * 64 + soff[i]);
     };
 
@@ -1039,11 +1046,11 @@ struct gemm_args {
     int F_act;
 };
 
-template <int MT, int EPI, int KG, int CG, int WB>
+template <int MT, int EPI, int KG, int CG, int WB, bool KEEP>
 int launch_one(const gemm_args& a) {
     // more than 64 KiB of dynamic LDS has to be allowed once per kernel
     static bool allowed = false;
-    auto kern = gemm_bf16_kernel<MT, EPI, KG, CG, WB>;
+    auto kern = gemm_bf16_kernel<MT, EPI, KG, CG, WB, KEEP>;
     if (!allowed) {
         SLED_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds));
         allowed = true;
@@ -1068,10 +1075,10 @@ int launch_tile_one(const gemm_args& a) {
     return SLED_OK;
 }
 
-template <int RT, int WB, int SETS>
+template <int RT, int WB, int SETS, bool KEEP>
 int launch_kwave(int epi, const gemm_args& a) {
     static bool allowed = false;
-    auto kern = gemm_kwave_kernel<RT, WB, SETS>;
+    auto kern = gemm_kwave_kernel<RT, WB, SETS, KEEP>;
     if (!allowed) {
         SLED_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kw_lds(RT)));
         allowed = true;
@@ -1092,21 +1099,21 @@ int launch_tile(int epi, const gemm_args& a) {
     }
 }
 
-template <int MT, int KG, int CG, int WB>
+template <int MT, int KG, int CG, int WB, bool KEEP = false>
 int launch_epi_wb(int epi, const gemm_args& a) {
     switch (epi) {
-        case SLED_EPI_PARTIAL: return launch_one<MT, SLED_EPI_PARTIAL, KG, CG, WB>(a);
-        case SLED_EPI_SWIGLU: return launch_one<MT, SLED_EPI_SWIGLU, KG, CG, WB>(a);
-        default: return launch_one<MT, SLED_EPI_STORE, KG, CG, WB>(a);
+        case SLED_EPI_PARTIAL: return launch_one<MT, SLED_EPI_PARTIAL, KG, CG, WB, KEEP>(a);
+        case SLED_EPI_SWIGLU: return launch_one<MT, SLED_EPI_SWIGLU, KG, CG, WB, KEEP>(a);
+        default: return launch_one<MT, SLED_EPI_STORE, KG, CG, WB, KEEP>(a);
     }
 }
 
-template <int MT, int KG, int CG>
+template <int MT, int KG, int CG, bool KEEP = false>
 int launch_epi(int epi, const gemm_args& a) {
     switch (a.wbits) {
-        case 8: return launch_epi_wb<MT, KG, CG, 8>(epi, a);
-        case 4: return launch_epi_wb<MT, KG, CG, 4>(epi, a);
-        default: return launch_epi_wb<MT, KG, CG, 16>(epi, a);
+        case 8: return launch_epi_wb<MT, KG, CG, 8, KEEP>(epi, a);
+        case 4: return launch_epi_wb<MT, KG, CG, 4, KEEP>(epi, a);
+        default: return launch_epi_wb<MT, KG, CG, 16, KEEP>(epi, a);
     }
 }
 
@@ -1267,36 +1274,50 @@ int sled_launch_gemm(const sled_model* m, const void* X, size_t x_plane, const v
         }
         if (wide)
             return m->wbits == 8 ? launch_epi_wb<4, WIDE_KG, WIDE_CG, 8>(epilogue, a) : launch_epi_wb<4, WIDE_KG, WIDE_CG, 4>(epilogue, a);
-        // up to 32 rows, and 4-bit weights up to 64 in long slices: the k-wave kernel (whose results do not depend on the choice either,
-        // so batch-invariant models take it too)
         const int slice = KS / plan.split;
         if (mt_total <= 4 && (KS % plan.split || slice % KW_MIN_STEPS))   // every plan of one block of rows has equal slices of whole trips
             SLED_FAIL(SLED_EINVAL, "gemm: %d k-steps in %d slices", KS, plan.split);
-        if (mt_total <= 2) {
-            const bool deep = m->wbits == 4 && slice >= KW_DEEP_STEPS;
-            a.n_col = (NT + KW_CT - 1) / KW_CT;
-            if (mt_total == 1) {
-                switch (m->wbits) {
-                    case 8: return launch_kwave<1, 8, 4>(epilogue, a);
-                    case 4: return deep ? launch_kwave<1, 4, 8>(epilogue, a) : launch_kwave<1, 4, 4>(epilogue, a);
-                    default: return launch_kwave<1, 16, 4>(epilogue, a);
+        auto one_block = [&](auto keep_c) {
+            constexpr bool KEEP = decltype(keep_c)::value;
+            // up to 32 rows, and 4-bit weights up to 64 in long slices: the k-wave kernel (whose results do not depend on the choice either,
+            // so batch-invariant models take it too)
+            if (mt_total <= 2) {
+                const bool deep = m->wbits == 4 && slice >= KW_DEEP_STEPS;
+                a.n_col = (NT + KW_CT - 1) / KW_CT;
+                if (mt_total == 1) {
+                    switch (m->wbits) {
+                        case 8: return launch_kwave<1, 8, 4, KEEP>(epilogue, a);
+                        case 4: return deep ? launch_kwave<1, 4, 8, KEEP>(epilogue, a) : launch_kwave<1, 4, 4, KEEP>(epilogue, a);
+                        default: return launch_kwave<1, 16, 4, KEEP>(epilogue, a);
+                    }
                 }
+                if (deep) return launch_kwave<2, 4, 8, KEEP>(epilogue, a);
             }
-            if (deep) return launch_kwave<2, 4, 8>(epilogue, a);
-        }
-        // one block of 33 or more rows, 16-bit weights: the slim tile kernel (three row tiles: the narrow shape)
-        if (!wide && !broad && MT != 3 && m->wbits == 16 && !m->batch_invariant) {
-            a.n_col = (NT + SLIM_CT - 1) / SLIM_CT;
-            a.grid = dim3((a.n_col * a.n_split + 7) / 8 * 8, 1, 1);
-            a.lds = (size_t)tile_ring(MT, SLIM_CT, SLIM_U) * tile_stage_kib(MT, SLIM_CT, SLIM_U) * 1024;
-            return MT == 2 ? launch_tile<2, SLIM_CT, SLIM_U>(epilogue, a) : launch_tile<4, SLIM_CT, SLIM_U>(epilogue, a);
-        }
-        if (broad) return launch_epi<4, BROAD_KG, BROAD_CG>(epilogue, a);
-        switch (MT) {
-            case 2: return launch_epi<2, NARROW_KG, NARROW_CG>(epilogue, a);
-            case 3: return launch_epi<3, NARROW_KG, NARROW_CG>(epilogue, a);
-            default: return launch_epi<4, NARROW_KG, NARROW_CG>(epilogue, a);
-        }
+            // one block of 33 or more rows, 16-bit weights: the slim tile kernel (three row tiles: the narrow shape)
+            if (!broad && MT != 3 && m->wbits == 16 && !m->batch_invariant) {
+                a.n_col = (NT + SLIM_CT - 1) / SLIM_CT;
+                a.grid = dim3((a.n_col * a.n_split + 7) / 8 * 8, 1, 1);
+                a.lds = (size_t)tile_ring(MT, SLIM_CT, SLIM_U) * tile_stage_kib(MT, SLIM_CT, SLIM_U) * 1024;
+                return MT == 2 ? launch_tile<2, SLIM_CT, SLIM_U, KEEP>(epilogue, a) : launch_tile<4, SLIM_CT, SLIM_U, KEEP>(epilogue, a);
+            }
+            if (broad) return launch_epi<4, BROAD_KG, BROAD_CG>(epilogue, a);   // 98304 columns or more: seldom a model that a cache holds
+            switch (MT) {
+                case 2: return launch_epi<2, NARROW_KG, NARROW_CG, KEEP>(epilogue, a);
+                case 3: return launch_epi<3, NARROW_KG, NARROW_CG, KEEP>(epilogue, a);
+                default: return launch_epi<4, NARROW_KG, NARROW_CG, KEEP>(epilogue, a);
+            }
+        };
+        // A model whose matrices Infinity Cache (256 MB) holds beside a step's activations finds them there in the next step, if they are loaded in the
+        // caches' ordinary order.  Steps past the order / in it, us, 16-bit weights of 187 MB: one row 170 / 163, 25 195 / 185, 58 227 / 215, 101 275 / 266;
+        // of 218 MB 204 / 198, 237 / 226, 277 / 264, 337 / 331; of 248 MB 241 / 250, 280 / 283, 327 / 328, 398 / 403; 4-bit weights of 197 MB with
+        // their scales: 25 rows 277 / 260, 58 355 / 341, 101 498 / 485; of 229 MB 327 / 312, 421 / 408, 591 / 592 on one card and even on
+        // another; of 261 MB 379 / 382, 487 / 490, 684 / 686.  With more than one block of rows it is even or the other way round (250
+        // rows: 218 MB 490 / 494, 229 MB 846 / 861).
+        constexpr double KEEP_BYTES = 224e6;
+        const double weight_bytes = m->wbits / 8.0 + (m->wbits == 4 ? 1.0 / 32 : 0.0);
+        const double matrices = weight_bytes * (m->s.n_layers * ((double)m->n_qkv * m->s.d_model + (double)m->s.d_model * m->s.n_q_heads * m->s.head_dim + 3.0 * m->s.d_ffn * m->s.d_model)
+                                                + (double)m->s.vocab * m->s.d_model);
+        return mt_total <= 4 && matrices <= KEEP_BYTES ? one_block(std::true_type{}) : one_block(std::false_type{});
     }
     // fp32: no split, plain store (partial buffer with one slice has the same layout)
     dim3 grid((N + 4 * F32_NC - 1) / (4 * F32_NC), (T + F32_T - 1) / F32_T);
