@@ -669,8 +669,8 @@ int64_t attn_makespan(const std::vector<int>& np, const std::vector<int>& order,
     int64_t k = 0, end = 0;
     for (int i : order) {
         const int n = np[i], chunk = attn_chunk(n, tgt), pieces = ceil_div(n, chunk);
-        for (int g = 0; g < Hkv; g++)
-            for (int p0 = 0; p0 < n; p0 += chunk, k++) {
+        for (int p0 = 0; p0 < n; p0 += chunk)   // in the order run_forward issues them: a pair's items lie Hkv apart
+            for (int g = 0; g < Hkv; g++, k++) {
                 int64_t* h = heap.data() + (k % ATTN_XCDS) * PER;
                 std::pop_heap(h, h + PER, cmp);
                 h[PER - 1] += std::min(chunk, n - p0) + ATTN_ITEM_FIXED + (pieces > 1 ? ATTN_ITEM_SPLIT : 0);
