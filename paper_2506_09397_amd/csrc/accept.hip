@@ -894,10 +894,12 @@ int sled_launch_accept(int mode, int B, int T, const int* k_host, int vocab, flo
     for (int i = 0; i < B; i++) kp.k[i] = (uint8_t)k_host[i];
     QSrc qsrc{draft_q, q_ids, q_probs, q_m > 0 ? q_rest : nullptr, q_m};
     const float inv_tau = 1.0f / temperature;
-    // The scan in parts.  A cut at row c saves the rows from c on of every request that ends before c and costs a launch
-    // and its drain, about 8 us: made where the rows behind it are at least 64 MB x c (the longer the prefix, the fewer
-    // requests still get there), unless so few requests have long drafts that most workgroups of a part would be empty.
-    // 256 requests x 8 drafts x 128256 tokens, 62 % accepted: 204 us in one launch, 93 + 10 in three.
+    // The scan in parts.  A cut at row c saves the rows from c on of every request that ends before c and costs two launches and their
+    // drain: made where the rows behind it are at least 64 MB x c (the longer the prefix, the fewer requests still get there).  Whole calls with
+    // the first cut / without it, us, drafts 62 % accepted, by the MB behind row 2: 139 (64 requests x 2 to 8 drafts x 128256 tokens) 88 / 84,
+    // 144 (40 x 8) 75 / 76, 158 (96 x 0 to 8) 100 / 101, 172 (48 x 8) 83 / 85, 230 (64 x 8) 96 / 104, 344 (96 x 8) 118 / 142, 919 (256 x 8)
+    // 194 / 308; below the line 116 (56 x 2 to 8) 80 / 79.  With the second / without, by the MB behind row 4: 257 120 / 120, 298 125 / 126, 359 147 / 149,
+    // 314 (200 x 4 to 8) 165 / 168.  20 requests of 16 drafts among 180 of one (154 MB behind row 2): 140 / 150.
     auto rows_from = [&](int c) {
         int64_t n = 0;
         for (int i = 0; i < B; i++) n += std::max(0, k_host[i] + 1 - c);
@@ -908,7 +910,7 @@ int sled_launch_accept(int mode, int B, int T, const int* k_host, int vocab, flo
     const int n_tiles = (vocab + WTILE - 1) / WTILE;
     int cuts[4] = {0, 0, 0, 0}, n_part = 1;
     for (int c = 2; c <= 8 && c <= k_top; c *= 2)
-        if (rows_from(c) * vocab * 4 >= (int64_t)64000000 * c && (int64_t)B * (k_top + 1 - c) <= 4 * rows_from(c)) cuts[n_part++] = c;
+        if (rows_from(c) * vocab * 4 >= (int64_t)64000000 * c) cuts[n_part++] = c;
     // Segments per row: about 2048 workgroups in the (first) launch.  More of them are shorter than their own start and
     // reduction: 276 rows in 16 segments took 45 us for 141 MB, in 7 27 us.
     auto segments = [&]() {

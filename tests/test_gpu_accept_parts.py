@@ -118,3 +118,18 @@ def test_all_three_cuts():
         row += n + 1
     assert list(zip(a.tolist(), t.tolist())) == want
     assert sum(x > 8 for x, _ in want) > 10 and sum(x < 2 for x, _ in want) > 10
+
+
+def test_a_few_long_requests_among_short_ones_are_scanned_in_parts():
+    """20 requests of 16 drafts and 180 of one: 300 rows, 154 MB, lie behind row 2, and those of requests that end before are left out."""
+    vocab, k = 128256, [1] * 200
+    for i in range(0, 200, 10):
+        k[i] = 16
+    T = sum(k) + len(k)
+    c = synth.accept_case(k, vocab, 1.0, seed=4, device="cuda")
+    args = (sled.SAMPLE, k, vocab, c.logits, c.tokens, c.q, c.u_acc, c.u_smp, 0)
+    ws = sled.workspace(sled.sled_accept_workspace_bytes(len(k), T, vocab))
+    got = [x.tolist() for x in _run(*args, ws=ws)]
+    assert _unwritten(ws) > 300          # of 8 statistics a row
+    assert [x.tolist() for x in _run(*args, ws=sled.workspace(_stat_bytes(T, vocab)))] == got       # every row, in one launch
+    assert 0 < sum(got[0]) < sum(k)
