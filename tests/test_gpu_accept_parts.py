@@ -72,7 +72,8 @@ def _unwritten(ws):
 
 
 # the least workspace that is accepted has room for the statistics alone; one of 16 segments a row, the size for every call before the
-# sweeps had launches of their own, has room for the word on every request that the scan in parts needs, but not for the sweeps
+# sweeps had launches of their own, has room for the word on every request that the scan in parts needs, but not for the sweeps; the
+# least one and that word have room for the scan in parts with the five segments that 1800 rows get, not for the eight behind a cut
 @pytest.mark.parametrize("mode,B", [("greedy", 200), ("sample", 200), ("sample", 120)])
 def test_smaller_workspaces_and_the_static_one(mode, B):
     vocab, k = 128256, [8] * B
@@ -80,10 +81,14 @@ def test_smaller_workspaces_and_the_static_one(mode, B):
     c = synth.accept_case(k, vocab, 0.5, seed=B + 1, device="cuda")
     args = (m, k, vocab, c.logits, c.tokens, c.q, c.u_acc, c.u_smp, 0)
     want = [x.tolist() for x in _run(*args)]
-    for size in ("least", "earlier"):
-        ws = sled.workspace(_stat_bytes(T, vocab) if size == "least" else _stat_bytes(T, vocab, 16) + 256)
+    sizes = {"least": _stat_bytes(T, vocab), "earlier": _stat_bytes(T, vocab, 16) + 256}
+    if B == 200:
+        sizes["coarse"] = _stat_bytes(T, vocab) + 1024
+        assert sizes["coarse"] < _stat_bytes(T, vocab, 8)
+    for size, n_bytes in sizes.items():
+        ws = sled.workspace(n_bytes)
         assert [x.tolist() for x in _run(*args, ws=ws)] == want, size
-        if size == "earlier":
+        if size != "least":
             assert _unwritten(ws) > T // 4          # rows behind a rejection were left out
     with pytest.raises(sled.SledError):
         _run(*args, ws=sled.workspace(_stat_bytes(T, vocab))[:-256])
