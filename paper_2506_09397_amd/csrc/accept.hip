@@ -216,7 +216,10 @@ __device__ inline float expf_nonpos(float a) {
 
 // statistics of elements v0 .. v1-1 of a row, by the whole workgroup of 256; the sum of exponentials only with SAMPLE, and for a
 // result of its own (SHOWN) by expf
-// STREAM: rows of a batch that no cache holds are read past the replacement order.
+// STREAM: the scan in parts reads its rows past the caches' replacement order.  Part of them may be in Infinity Cache, since the LM head has just
+// written them, and is found there either way; what the scan reads does not push out the rest.  256 requests x 8 drafts x 128256 tokens (1.2 GB), us, in
+// the ordinary order / past it: the same logits again 190 / 185, three sets in turn 204 / 197, rows just written 238 / 217; 128 requests 122 / 127,
+// 136 / 135, 150 / 142.
 template <bool SAMPLE, bool SHOWN, bool STREAM = false>
 __device__ inline void scan_segment(const float* __restrict__ z, bool vec, int v0, int v1, float inv_tau, RowStat* __restrict__ dst) {
     auto e_to = [](float a) { return SHOWN ? expf(a) : expf_nonpos(a); };
@@ -918,7 +921,9 @@ int sled_launch_accept(int mode, int B, int T, const int* k_host, int vocab, flo
         return std::min(sled_accept_pick_split(T, vocab), (int)std::max<int64_t>(1, (2048 + rows_first / 2) / rows_first));
     };
     // Rows behind a cut are few and are cut finer, where the workspace holds as many statistics for all rows: eight segments (sixteen
-    // scan no faster, and the next test, which adds up a row's segments, takes 6.9 instead of 5.4 us).
+    // scan no faster, and the next test, which adds up a row's segments, takes 6.9 instead of 5.4 us).  They come before room for the sweeps in
+    // launches of their own (below) where the workspace has room for one of the two: 160 requests x 8 drafts x 32000 tokens in
+    // the 256 KiB of sled_accept_static 68 us so, 74 with coarse segments and those sweeps; 150 requests 71 and 71, 100 x 16 drafts 66 and 65.
     int n_split = segments();
     const int n_fine = std::min(8, sled_accept_pick_split(1, vocab));
     Split sp{n_split, n_fine, cuts[1], std::max(n_split, n_fine)};

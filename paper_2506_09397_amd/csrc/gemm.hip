@@ -32,10 +32,13 @@
 //     two streams are independent (it drains the counter before any LDS read that might alias a
 //     direct-to-LDS load).  Both kinds of loads are therefore issued from inline assembly in a
 //     fixed order, and the waits are written by hand from that order.
-//   - Weights are read past the caches' replacement order (nt) in all three kernels: a step streams gigabytes of them, and loaded as
+//   - Weights are read past the caches' replacement order (nt) in all kernels: a step streams gigabytes of them, and loaded as
 //     anything else is they push the partial sums and activations, which the next kernel reads, out of Infinity Cache.  Layer
 //     times of the 8B shape without and with it, us: 58 rows 146.5-150 -> 140.6-143 (16-bit), 132 -> 128 (8-bit), 86 rows 170-173 -> 168,
-//     101 rows 188-190 -> 185; 70B shape, 220 rows 868-873 -> 857-862: the row kernels gain as much as the projections.
+//     101 rows 188-190 -> 185; 70B shape, 220 rows 868-873 -> 857-862: the row kernels gain as much as the projections.  8 layers and the head
+//     without / with it, us: 8-bit 96 rows 1328 / 1289, 128 1531 / 1491, 256 2521 / 2446, 512 4407 / 4390; 4-bit 96 rows 1260 / 1235,
+//     256 2388 / 2379; batch-invariant 16-bit weights, whose row blocks share the narrow shape, 136 rows 2281 / 2279, 192 2401 / 2353,
+//     256 2994 / 2946, 512 5611 / 5561 (8-bit 136 rows 2215 / 2163, 4-bit 2099 / 2039): nowhere slower.
 //     The ordinary order is kept where two unequal row blocks share the weights and for models that a cache holds (see the launches).
 //   - Split-K over blockIdx.y gives every CU work on the narrow projections; partial sums go to a
 //     [split, T, N] fp32 buffer that the following row kernel reduces in a fixed order (no float
@@ -751,8 +754,8 @@ __global__ __launch_bounds__(64 * TILE_WAVES, tile_sums(RT, CT, U) <= 8 ? 2 : 1)
 // the end (64 KiB per row tile; writing them is what LDS is slowest at, 78 bytes per clock measured, 250 for reading).
 //   - Sum g of a result is that of the k-steps g, g + 4, ...; the four are added in ascending order: the sums of the narrow shape and of the
 //     slim tile, so a result does not depend on which kernel made it.
-//   - Measured inside the workgroups at one row, gate/up of 4096 x 28672: 1.4 us until the first loads are out, 29.4 us for the
-//     loop (8.0 TB/s while it runs), 1.6 us for the sums and SwiGLU, and 4.8 us for dispatch, the slowest workgroup and the end.
+//   - At one row, gate/up of 4096 x 28672 takes 37.4 us, 6.3 TB/s, the LM head 6.5 TB/s.  Inside a workgroup of gate/up: 1.4 us until the
+//     first loads are out, 29.4 us for the loop, 1.6 us for the sums and SwiGLU; the other 4.8 us are dispatch, the slowest workgroup and the end.
 //     Launch times, one row of 16-bit weights, slim tile of one row tile (which this replaced) against this: QKV 11.0 -> 11.2, O 9.6 -> 9.3,
 //     gate/up 38.9 -> 37.5, down 21.6 -> 21.1 us; 25 rows of 8-bit weights, narrow shape against this: 10.4 -> 10.0, 8.3 -> 7.5,
 //     27.5 -> 26.3, 16.9 -> 15.7; of 4-bit weights: 9.5 -> 8.9, 7.1 -> 6.9, 25.0 -> 21.0, 13.3 -> 13.0.
@@ -764,7 +767,10 @@ __global__ __launch_bounds__(64 * TILE_WAVES, tile_sums(RT, CT, U) <= 8 ? 2 : 1)
 //     Three row tiles lose everywhere (54.4 -> 57.3), four do not fit into the registers.
 constexpr int KW_CT = 4, KW_WAVES = 4;
 constexpr int KW_MIN_STEPS = 16;     // k-steps of a slice come in multiples of this
-constexpr int KW_DEEP_STEPS = 256;   // 4-bit slices from here on are long: the 8B shape's gate/up and LM head have 256, its down projection 112
+// 4-bit slices from here on are long.  Whole steps of models whose gate/up and head have slices of so many k-steps, with eight sets in the slices
+// from that length on against none, at 25 rows (four sets instead) and at 58 (the k-group kernel instead): 64 +1.3 and +5.1 %, 112 +1.9 and +4.2, 128 +0.4
+// and +1.8, 160 +0.9 and +2.1, 192 +1.7 and +1.1, 256 -1.7 and -4.7, 512 -2.3 and -7.6.
+constexpr int KW_DEEP_STEPS = 256;
 static_assert(KW_DEEP_STEPS >= 8 * KW_WAVES, "eight sets are filled before the loop");
 constexpr int kw_lds(int RT) { return KW_WAVES * KW_CT * RT * 4096; }
 

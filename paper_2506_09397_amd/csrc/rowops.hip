@@ -583,9 +583,7 @@ __global__ __launch_bounds__(256) void copy_act_row_kernel(const void* __restric
     }
 }
 
-// len[req_ids[i]] += add[i]            (accept == nullptr)
-// len[req_ids[i]] += accept[i] + 1     (otherwise)
-// committed lengths after an append (+ add[i]) or a commit (+ accept[i] + 1); `fresh`: the request starts from zero whatever the slot held
+// committed lengths after an append (+ add[i]) or, with `accept`, a commit (+ accept[i] + 1); `fresh`: the request starts from zero whatever the slot held
 __global__ void len_add_kernel(int32_t* __restrict__ len_dev, const int32_t* __restrict__ req_ids, const int32_t* __restrict__ add,
                                const int32_t* __restrict__ fresh, const int32_t* __restrict__ accept, int B) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
