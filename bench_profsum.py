@@ -36,11 +36,11 @@ def stats(d: str) -> None:
             continue
         print(f"{short(r['Name']):70s} {int(r['Calls']):7d} {t / 1e6:10.3f} {float(r['AverageNs']) / 1e3:9.2f} "
               f"{int(r['MinNs']) / 1e3:9.2f} {int(r['MaxNs']) / 1e3:9.2f} {100.0 * t / total:6.2f}")
-        if "gemm_bf16_kernel" in r["Name"] or "gemm_tile_kernel" in r["Name"]:
+        if any(k in r["Name"] for k in ("gemm_bf16_kernel", "gemm_tile_kernel", "gemm_kwave_kernel")):
             gemm_calls += int(r["Calls"])
             gemm_ns += t
     if gemm_calls:
-        print(f"\nall gemm_bf16_kernel and gemm_tile_kernel instances: {gemm_calls} launches, {gemm_ns / 1e6:.3f} ms, "
+        print(f"\nall projection kernels (gemm_kwave, gemm_tile, gemm_bf16): {gemm_calls} launches, {gemm_ns / 1e6:.3f} ms, "
               f"average {gemm_ns / gemm_calls / 1e3:.2f} us per launch")
 
 
@@ -92,7 +92,7 @@ def mfma(d: str) -> None:
         dur[(short(r["Kernel_Name"]), grid)].append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
     print(f"{'kernel':40s} {'grid':>9s} {'n':>5s} {'avg us':>9s} {'MFMA busy':>10s} {'clock GHz':>10s}")
     for key in sorted(busy, key=lambda k: -sum(busy[k])):
-        if ("gemm_bf16" not in key[0] and "gemm_tile" not in key[0]) or key not in act or key not in dur:
+        if not any(k in key[0] for k in ("gemm_bf16", "gemm_tile", "gemm_kwave")) or key not in act or key not in dur:
             continue
         b, a, t = sum(busy[key]) / len(busy[key]), sum(act[key]) / len(act[key]), sum(dur[key]) / len(dur[key])
         print(f"{key[0]:40s} {key[1]:9d} {len(busy[key]):5d} {t:9.1f} {b / (a / 8 * 1024):10.3f} {a / 8 / (t * 1e3):10.2f}")
